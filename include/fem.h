@@ -240,7 +240,11 @@ fem_status fem_set_adam_state(fem_solver* s, const float* h, const float* m1, co
  * evaluated at h(t). */
 fem_status fem_step(fem_solver* s, int32_t n_steps);
 /* Enqueue the remaining steps up to T as one captured HIP graph (replayed on
- * later calls from the same t). */
+ * later calls from the same t).  Small MaxCut and Max-k-SAT instances run
+ * whole ranges of steps in one kernel instead, each replica on one compute
+ * unit, whatever call enqueues them; a solver of nothing else needs no graph.
+ * Their tables (a re-ordered copy of the adjacency and about 100 bytes per
+ * step) are device memory of the solver. */
 fem_status fem_run(fem_solver* s);
 /* Enqueue steps [t, t_end) as one captured HIP graph. */
 fem_status fem_run_until(fem_solver* s, int32_t t_end);
@@ -326,23 +330,28 @@ fem_status fem_set_state(fem_solver* s, const void* buf, size_t bytes);
  * segments of the same rows, so that each XCD (workgroups are dealt to the
  * eight XCDs round-robin) gathers from its own columns of the marginal copy.
  * fem_get_tile reports the lanes actually used.  All shapes give
- * bit-identical fields. */
+ * bit-identical fields.  A solver starts with its small MaxCut and Max-k-SAT
+ * instances on kernels that no launch shape applies to (fem_run);
+ * fem_set_tile puts every instance on the shaped kernels, with the same
+ * fields. */
 typedef struct {
     int32_t vec, waves, rows, nt, lanes;
 } fem_tile;
 fem_status fem_get_tile(const fem_solver* s, fem_tile* t);
 fem_status fem_set_tile(fem_solver* s, const fem_tile* t);
 /* Autotune: time every valid shape twice for trial_steps steps from the same
- * state (restored afterwards), keep the shape with the fastest run, and cache it on disk under the key (kind, n,
+ * state (restored afterwards), keep the shape with the fastest run (the one
+ * it has, untimed, where no instance uses it), and cache it on disk under the key (kind, n,
  * nnz, R, q, dtype, instances, energies on/off, gradient mode) in
  * $FEM_TUNE_CACHE (default ~/.cache/femx/tune.txt).  use_cache = 1 returns a
  * cached choice without timing: the user's cache first, then the shapes
  * tuned on an MI355X that ship beside the library (data/tune_mi355x.txt). */
 fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_tile* chosen);
 
-/* Average duration in milliseconds of the step kernel over the last
+/* Average duration in milliseconds of one step in the step kernel over the last
  * fem_step/fem_run call, measured with HIP events on the solver's stream
- * (0 if not measured).  Enabled by fem_profile(s, 1). */
+ * (0 if not measured), and the number of steps; a kernel that runs a range of
+ * steps counts each of them.  Enabled by fem_profile(s, 1). */
 fem_status fem_profile(fem_solver* s, int32_t on);
 fem_status fem_profile_result(fem_solver* s, double* step_kernel_ms, int32_t* n_kernels);
 

@@ -192,7 +192,8 @@ __device__ __forceinline__ float sqrt_f(float x) { return __builtin_amdgcn_sqrtf
 // |y| < 0.55 (truncation below 1e-9 relative), else (1 - e)/(1 + e) with
 // e = exp(-|y|), where 1 - e >= 0.42 keeps its relative precision; the sign
 // of y restored
-__device__ __forceinline__ float tanh_half(float y)
+// (e and r = 1/(1 + e) are handed back: the next step needs them at y)
+__device__ __forceinline__ float tanh_half(float y, float& e, float& r)
 {
     const float a = fabsf(y);
     const float z = 0.5f * a, z2 = z * z;
@@ -202,9 +203,15 @@ __device__ __forceinline__ float tanh_half(float y)
     p = fmaf(p, z2, 2.0f / 15.0f);
     p = fmaf(p, z2, -1.0f / 3.0f);
     const float small = fmaf(p * z2, z, z);
-    const float e = exp_neg(a);
-    const float large = (1.0f - e) * rcp_f(1.0f + e);
+    e = exp_neg(a);
+    r = rcp_f(1.0f + e);
+    const float large = (1.0f - e) * r;
     return copysignf(a < 0.55f ? small : large, y);
+}
+__device__ __forceinline__ float tanh_half(float y)
+{
+    float e, r;
+    return tanh_half(y, e, r);
 }
 
 // ln(1 + e) for e >= 0: u = 1 + e rounded, then ln(u) e / (u - 1) (the

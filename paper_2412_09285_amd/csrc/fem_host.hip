@@ -24,6 +24,7 @@
 #include "../../include/fem.h"
 #include "fem_internal.h"
 #include "fem_dense.h"
+#include "fem_resident.h"
 
 using namespace fem;
 
@@ -390,6 +391,18 @@ static fem_status build_sat(int device, int32_t n_vars, int64_t n_clauses, const
 }
 
 // ------------------------------------------------------------------ solver --
+// The tiles of a set of instances and the chunks that their partial sums are
+// reduced by (an instance outside the set has no chunks).
+struct TileSet {
+    Tile* tiles = nullptr;
+    int32_t* chunk_off = nullptr;
+    int32_t* inst_chunk_off = nullptr;
+    int n_tiles = 0, n_chunks = 0;
+    // most tiles of one instance: up to ENERGY_FINISH_TILES the energies are
+    // reduced in one launch, beyond in two stages plus the combination
+    int max_inst_tiles = 0;
+};
+
 struct fem_solver {
     fem_problem* owner = nullptr;   // holds one reference
     const Problem* prob = nullptr;
@@ -419,10 +432,10 @@ struct fem_solver {
     LaunchGeom geo{};
     LaunchGeom egeo{};   // evaluation kernels: one replica per lane
     int lanes_log2 = 0;
-    Tile* d_tiles = nullptr;
-    int n_tiles = 0, n_chunks = 0;
-    int32_t* d_chunk_off = nullptr;
-    int32_t* d_inst_chunk_off = nullptr;
+    TileSet ts;   // the instances of the row-tiled step kernels
+    TileSet es;   // evaluation: every instance (ts itself where that is all)
+    // instances whose replicas run on one compute unit each (fem_resident.hip)
+    ResData res;
     // energies
     int NE = 2;
     double* epart = nullptr;
@@ -433,9 +446,6 @@ struct fem_solver {
     int n_records = 0;
     int last_energy_step = -1;
     double* d_wtot = nullptr;
-    // most tiles of one instance: up to ENERGY_FINISH_TILES the energies are
-    // reduced in one launch, beyond in two stages plus the combination
-    int max_inst_tiles = 0;
     // bMinCut column sums
     long long* cpart = nullptr;
     long long* ctmp = nullptr;
@@ -460,6 +470,7 @@ struct fem_solver {
     bool profile = false;
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
     size_t prof_used = 0;
+    int64_t prof_steps = 0;   // steps that the recorded intervals cover
     bool capturing = false;
 };
 
@@ -507,9 +518,13 @@ static bool valid_shape(const fem_solver* s, const TileShape& t)
 
 static void free_tiling(fem_solver* s)
 {
-    dfree(s->d_tiles);
-    dfree(s->d_chunk_off);
-    dfree(s->d_inst_chunk_off);
+    if (s->es.tiles == s->ts.tiles) s->es = TileSet{};
+    for (TileSet* x : {&s->ts, &s->es}) {
+        dfree(x->tiles);
+        dfree(x->chunk_off);
+        dfree(x->inst_chunk_off);
+        *x = TileSet{};
+    }
     dfree(s->epart);
     dfree(s->etmp);
     dfree(s->cpart);
@@ -536,24 +551,15 @@ static void drop_graphs(fem_solver* s)
 // (one workgroup per instance and 32 replicas reads all their partials)
 constexpr int ENERGY_FINISH_TILES = 256;
 
-static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
+// The tiles of every instance not marked in skip (null: all instances).
+static fem_status make_tiles(const Problem& p, int tile_rows, const uint8_t* skip, bool seg_major, TileSet& ts)
 {
-    const Problem& p = *s->prob;
-    free_tiling(s);
-    drop_graphs(s);
-    s->shape = shape;
-    const int per_lane = (s->kind == KIND_BMINCUT) ? 1 : shape.vec;
-    s->geo = make_geom(per_lane, s->R, shape.waves, shape.lanes);
-    s->geo.seg_major =
-        (s->geo.nseg > 1 && count_tiles(s, s->geo.teams_per_block * shape.rows) <= GRID_Y_MAX) ? 1 : 0;
-    s->lanes_log2 = 0;
-    while ((1 << s->lanes_log2) < s->geo.lanes) ++s->lanes_log2;
-    // the dense step kernel owns fixed row blocks (the padding of W)
-    const int tile_rows = s->dense ? DENSE_ROWS : s->geo.teams_per_block * shape.rows;
     std::vector<Tile> tiles;
     std::vector<int32_t> chunk_off{0}, inst_chunk_off{0};
-    for (int b = 0; b < s->n_inst; ++b) {
-        const int32_t r0 = p.inst_off[(size_t)b], r1 = p.inst_off[(size_t)b + 1];
+    ts = TileSet{};
+    for (int b = 0; b < p.n_inst; ++b) {
+        const int32_t r0 = p.inst_off[(size_t)b], r1 = skip && skip[b] ? r0 : p.inst_off[(size_t)b + 1];
+        const size_t first = tiles.size();
         int in_chunk = 0;
         for (int32_t r = r0; r < r1; r += tile_rows) {
             Tile t;
@@ -569,13 +575,10 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
         }
         if (in_chunk) chunk_off.push_back((int32_t)tiles.size());
         inst_chunk_off.push_back((int32_t)chunk_off.size() - 1);
+        ts.max_inst_tiles = std::max(ts.max_inst_tiles, (int)(tiles.size() - first));
     }
-    s->n_tiles = (int)tiles.size();
-    s->n_chunks = (int)chunk_off.size() - 1;
-    s->max_inst_tiles = 0;
-    for (int b = 0; b < s->n_inst; ++b)
-        s->max_inst_tiles = std::max(s->max_inst_tiles, chunk_off[(size_t)inst_chunk_off[(size_t)b + 1]] -
-                                                            chunk_off[(size_t)inst_chunk_off[(size_t)b]]);
+    ts.n_tiles = (int)tiles.size();
+    ts.n_chunks = (int)chunk_off.size() - 1;
     // XCD-aware dispatch order: position pos runs on XCD pos % 8; XCD x gets
     // the contiguous tile range [start_x, start_x + cnt_x), cnt_x differing by
     // at most one between XCDs, so every position holds exactly one tile.
@@ -588,28 +591,50 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
             start[x] = acc;
             acc += nt / X + (x < nt % X ? 1 : 0);
         }
-        for (size_t pos = 0; pos < nt; ++pos)
-            order[pos] = s->geo.seg_major ? tiles[pos] : tiles[start[pos % X] + pos / X];
+        for (size_t pos = 0; pos < nt; ++pos) order[pos] = seg_major ? tiles[pos] : tiles[start[pos % X] + pos / X];
     }
-    s->geo.n_tiles = s->n_tiles;
+    auto up = [](auto** d, const auto& v) -> hipError_t {
+        hipError_t e = dalloc(d, v.size());
+        if (e == hipSuccess && !v.empty()) e = hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice);
+        return e;
+    };
+    HIPCHK(up(&ts.tiles, order));
+    HIPCHK(up(&ts.chunk_off, chunk_off));
+    HIPCHK(up(&ts.inst_chunk_off, inst_chunk_off));
+    return FEM_OK;
+}
+
+static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
+{
+    const Problem& p = *s->prob;
+    free_tiling(s);
+    drop_graphs(s);
+    s->shape = shape;
+    const int per_lane = (s->kind == KIND_BMINCUT) ? 1 : shape.vec;
+    s->geo = make_geom(per_lane, s->R, shape.waves, shape.lanes);
+    s->geo.seg_major =
+        (s->geo.nseg > 1 && count_tiles(s, s->geo.teams_per_block * shape.rows) <= GRID_Y_MAX) ? 1 : 0;
+    s->lanes_log2 = 0;
+    while ((1 << s->lanes_log2) < s->geo.lanes) ++s->lanes_log2;
+    // the dense step kernel owns fixed row blocks (the padding of W)
+    const int tile_rows = s->dense ? DENSE_ROWS : s->geo.teams_per_block * shape.rows;
+    const bool mixed = !s->res.taken.empty();
+    STCHK(make_tiles(p, tile_rows, mixed ? s->res.taken.data() : nullptr, s->geo.seg_major != 0, s->ts));
+    if (mixed) STCHK(make_tiles(p, tile_rows, nullptr, s->geo.seg_major != 0, s->es));
+    else s->es = s->ts;
+    s->geo.n_tiles = s->ts.n_tiles;
     s->egeo = make_geom(1, s->R, shape.waves);
-    s->egeo.n_tiles = s->n_tiles;
-    HIPCHK(dalloc(&s->d_tiles, order.size()));
-    HIPCHK(hipMemcpy(s->d_tiles, order.data(), order.size() * sizeof(Tile), hipMemcpyHostToDevice));
-    HIPCHK(dalloc(&s->d_chunk_off, chunk_off.size()));
-    HIPCHK(hipMemcpy(s->d_chunk_off, chunk_off.data(), chunk_off.size() * 4, hipMemcpyHostToDevice));
-    HIPCHK(dalloc(&s->d_inst_chunk_off, inst_chunk_off.size()));
-    HIPCHK(hipMemcpy(s->d_inst_chunk_off, inst_chunk_off.data(), inst_chunk_off.size() * 4, hipMemcpyHostToDevice));
+    s->egeo.n_tiles = s->es.n_tiles;
     const size_t R = (size_t)s->R;
-    HIPCHK(dalloc(&s->epart, (size_t)s->n_tiles * s->NE * R));
-    HIPCHK(dalloc(&s->etmp, (size_t)s->n_chunks * s->NE * R));
-    HIPCHK(dalloc(&s->vpart, (size_t)s->n_tiles * R));
-    HIPCHK(dalloc(&s->vtmp, (size_t)s->n_chunks * R));
+    HIPCHK(dalloc(&s->epart, (size_t)s->ts.n_tiles * s->NE * R));
+    HIPCHK(dalloc(&s->etmp, (size_t)s->ts.n_chunks * s->NE * R));
+    HIPCHK(dalloc(&s->vpart, (size_t)s->es.n_tiles * R));
+    HIPCHK(dalloc(&s->vtmp, (size_t)s->es.n_chunks * R));
     if (s->kind == KIND_BMINCUT) {
-        HIPCHK(dalloc(&s->cpart, (size_t)s->n_tiles * R * s->q));
-        HIPCHK(dalloc(&s->ctmp, (size_t)s->n_chunks * R * s->q));
-        HIPCHK(dalloc(&s->spart, (size_t)s->n_tiles * R * s->q));
-        HIPCHK(dalloc(&s->stmp, (size_t)s->n_chunks * R * s->q));
+        HIPCHK(dalloc(&s->cpart, (size_t)s->ts.n_tiles * R * s->q));
+        HIPCHK(dalloc(&s->ctmp, (size_t)s->ts.n_chunks * R * s->q));
+        HIPCHK(dalloc(&s->spart, (size_t)s->es.n_tiles * R * s->q));
+        HIPCHK(dalloc(&s->stmp, (size_t)s->es.n_chunks * R * s->q));
     }
     return FEM_OK;
 }
@@ -634,9 +659,10 @@ static StepScalars step_scalars(const fem_solver* s, int t)
     sc.gamma_d = p.gradient == FEM_GRAD_MANIPULATED ? p.gamma_grad : 1.0;
     sc.inv_beta = (float)sc.inv_beta_d;
     sc.lam = (float)sc.lam_d;
+    const double bc2_sqrt = std::sqrt(1.0 - std::pow(p.adam_b2, nstep));
     sc.step_size = (float)(p.lr / (1.0 - std::pow(p.adam_b1, nstep)));
-    sc.bc2_sqrt = (float)std::sqrt(1.0 - std::pow(p.adam_b2, nstep));
-    sc.inv_bc2_sqrt = (float)(1.0 / std::sqrt(1.0 - std::pow(p.adam_b2, nstep)));
+    sc.bc2_sqrt = (float)bc2_sqrt;
+    sc.inv_bc2_sqrt = (float)(1.0 / bc2_sqrt);
     sc.b1 = (float)p.adam_b1;
     sc.one_m_b1 = (float)(1.0 - p.adam_b1);
     sc.b2 = (float)p.adam_b2;
@@ -665,7 +691,7 @@ static StepArgs base_args(const fem_solver* s)
     a.wdeg = p.wdeg;
     a.nrm = p.nrm;
     a.nw = p.nw;
-    a.tiles = s->d_tiles;
+    a.tiles = s->ts.tiles;
     a.h = s->h;
     a.m1 = s->m1;
     a.m2 = s->m2;
@@ -698,7 +724,7 @@ static double* energy_slot(fem_solver* s, int t)
 // marginal sums, or state counts of the read-out with manipulated gradients)
 static fem_status finish_colsums(fem_solver* s)
 {
-    HIPCHK(launch_seg_reduce<long long>(s->cpart, s->R * s->q, s->d_chunk_off, s->n_chunks, s->d_inst_chunk_off,
+    HIPCHK(launch_seg_reduce<long long>(s->cpart, s->R * s->q, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off,
                                         s->n_inst, s->ctmp, s->cfix, s->stream));
     HIPCHK(launch_colsum_combine(s->R, s->q, s->n_inst, s->cfix, s->manip ? 1.0 : 0x1p-40, s->csum, s->ctil,
                                  s->stream));
@@ -713,11 +739,11 @@ static fem_status readout_eval(fem_solver* s, const uint8_t* sigma_in, bool upda
         HIPCHK(launch_round(s->kind, s->n, s->R, s->q, s->h, s->srow, s->sigma, s->stream));
         sigma_in = s->sigma;
     }
-    HIPCHK(launch_eval(p, s->egeo, s->shape.waves, s->d_tiles, s->R, sigma_in, s->vpart, s->spart, s->stream));
-    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->d_chunk_off, s->n_chunks, s->d_inst_chunk_off, s->n_inst,
+    HIPCHK(launch_eval(p, s->egeo, s->shape.waves, s->es.tiles, s->R, sigma_in, s->vpart, s->spart, s->stream));
+    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->es.chunk_off, s->es.n_chunks, s->es.inst_chunk_off, s->n_inst,
                                      s->vtmp, s->vout, s->stream));
     if (s->kind == KIND_BMINCUT) {
-        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, s->d_chunk_off, s->n_chunks, s->d_inst_chunk_off,
+        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, s->es.chunk_off, s->es.n_chunks, s->es.inst_chunk_off,
                                       s->n_inst, s->stmp, s->sint, s->stream));
         HIPCHK(launch_sizes_widen((size_t)s->n_inst * s->R * s->q, s->sint, s->sout, s->stream));
     }
@@ -727,7 +753,52 @@ static fem_status readout_eval(fem_solver* s, const uint8_t* sigma_in, bool upda
     return FEM_OK;
 }
 
-static fem_status do_step(fem_solver* s)
+// An interval of the profile on the solver's stream, covering n steps: the
+// start is recorded here, *end is what the caller records after its launch
+// (null when not profiling).
+static fem_status profile_begin(fem_solver* s, int n, hipEvent_t* end)
+{
+    *end = nullptr;
+    if (!s->profile || s->capturing) return FEM_OK;
+    if (s->prof_used == s->prof_events.size()) {
+        hipEvent_t x, y;
+        HIPCHK(hipEventCreate(&x));
+        HIPCHK(hipEventCreate(&y));
+        s->prof_events.emplace_back(x, y);
+    }
+    HIPCHK(hipEventRecord(s->prof_events[s->prof_used].first, s->stream));
+    *end = s->prof_events[s->prof_used].second;
+    ++s->prof_used;
+    s->prof_steps += n;
+    return FEM_OK;
+}
+
+// Steps [s->t, t_end) of the resident instances, in one launch per class.
+static fem_status resident_steps(fem_solver* s, int t_end)
+{
+    ResArgs a{};
+    a.wtot = s->d_wtot;
+    a.h = s->h;
+    a.m1 = s->m1;
+    a.m2 = s->m2;
+    a.srow = s->srow;
+    a.grad = s->prm.keep_grad ? s->grad : nullptr;
+    a.eout = s->ehist ? s->ehist : s->eout;
+    a.erecord = s->ehist ? (int64_t)s->n_inst * 3 * s->R : 0;
+    a.energy_every = s->prm.energy_every;
+    a.R = s->R;
+    a.t0 = s->t;
+    a.t1 = t_end;
+    a.bf16 = s->dtype == FEM_BF16;
+    hipEvent_t e1 = nullptr;
+    if (s->res.all) STCHK(profile_begin(s, t_end - s->t, &e1));
+    HIPCHK(resident_launch(*s->prob, s->res, s->manip, a, s->stream));
+    if (e1) HIPCHK(hipEventRecord(e1, s->stream));
+    return FEM_OK;
+}
+
+// One step of the row-tiled kernels.
+static fem_status tiled_step(fem_solver* s)
 {
     const int t = s->t;
     StepArgs a = base_args(s);
@@ -736,48 +807,53 @@ static fem_status do_step(fem_solver* s)
     a.sc = step_scalars(s, t);
     const bool en = energy_due(s, t);
     a.epart = en ? s->epart : nullptr;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (s->profile && !s->capturing) {
-        if (s->prof_used == s->prof_events.size()) {
-            hipEvent_t x, y;
-            HIPCHK(hipEventCreate(&x));
-            HIPCHK(hipEventCreate(&y));
-            s->prof_events.emplace_back(x, y);
-        }
-        e0 = s->prof_events[s->prof_used].first;
-        e1 = s->prof_events[s->prof_used].second;
-        ++s->prof_used;
-        HIPCHK(hipEventRecord(e0, s->stream));
-    }
+    hipEvent_t e1 = nullptr;
+    STCHK(profile_begin(s, 1, &e1));
     if (s->manip)
         HIPCHK(launch_manip_step(s->kind, s->shape.vec, s->shape.nt != 0, s->geo, s->shape.waves, a, s->stream));
     else if (s->dense)
-        HIPCHK(launch_dense_step(*s->prob, s->dtype, en, s->shape.nt != 0, s->n_tiles, a, s->stream));
+        HIPCHK(launch_dense_step(*s->prob, s->dtype, en, s->shape.nt != 0, s->ts.n_tiles, a, s->stream));
     else
         HIPCHK(launch_step(s->kind, s->dtype, s->shape.vec, s->shape.nt != 0, s->geo, s->shape.waves, a, s->stream));
     if (e1) HIPCHK(hipEventRecord(e1, s->stream));
     if (en) {
         double* slot = energy_slot(s, t);
-        if (s->max_inst_tiles <= ENERGY_FINISH_TILES) {
-            HIPCHK(launch_energy_finish(s->kind, s->R, s->q, s->NE, s->n_inst, s->epart, s->d_chunk_off,
-                                        s->d_inst_chunk_off, s->d_wtot, s->csum, s->lam[(size_t)t],
+        if (s->ts.max_inst_tiles <= ENERGY_FINISH_TILES) {
+            HIPCHK(launch_energy_finish(s->kind, s->R, s->q, s->NE, s->n_inst, s->epart, s->ts.chunk_off,
+                                        s->ts.inst_chunk_off, s->d_wtot, s->csum, s->lam[(size_t)t],
                                         s->beta[(size_t)t], slot, s->stream));
         } else {
-            HIPCHK(launch_seg_reduce<double>(s->epart, s->NE * s->R, s->d_chunk_off, s->n_chunks,
-                                             s->d_inst_chunk_off, s->n_inst, s->etmp, s->eraw, s->stream));
-            HIPCHK(launch_energy_combine(s->kind, s->R, s->q, s->n_inst, s->eraw, s->d_wtot, s->csum,
+            HIPCHK(launch_seg_reduce<double>(s->epart, s->NE * s->R, s->ts.chunk_off, s->ts.n_chunks,
+                                             s->ts.inst_chunk_off, s->n_inst, s->etmp, s->eraw, s->stream));
+            HIPCHK(launch_energy_combine(s->kind, s->R, s->q, s->n_inst, s->ts.inst_chunk_off, s->eraw, s->d_wtot, s->csum,
                                          s->lam[(size_t)t], s->beta[(size_t)t], slot, s->stream));
         }
-        s->last_energy_step = t;
     }
     if (s->kind == KIND_BMINCUT) STCHK(finish_colsums(s));
-    s->t = t + 1;
-    if (eval_due(s, s->t)) STCHK(readout_eval(s, nullptr, true));
+    return FEM_OK;
+}
+
+// Enqueues the steps up to t_end: the stretch to the next read-out at a time,
+// the resident instances all of it in one launch, the others step by step.
+static fem_status do_steps(fem_solver* s, int t_end)
+{
+    const bool resident = !s->res.taken.empty();
+    while (s->t < t_end) {
+        int e = t_end;
+        if (s->prm.eval_every > 0) e = std::min(e, (s->t / s->prm.eval_every + 1) * s->prm.eval_every);
+        if (resident) STCHK(resident_steps(s, e));
+        for (; s->t < e; ++s->t) {
+            if (!s->res.all) STCHK(tiled_step(s));
+            if (energy_due(s, s->t)) s->last_energy_step = s->t;
+        }
+        if (eval_due(s, s->t)) STCHK(readout_eval(s, nullptr, true));
+    }
     return FEM_OK;
 }
 
 static fem_status init_marginals(fem_solver* s)
 {
+    if (s->res.all) return FEM_OK;   // resident instances form theirs from the fields
     StepArgs a = base_args(s);
     a.marg_nxt = s->marg[s->t & 1];
     if (s->manip)
@@ -809,6 +885,7 @@ static void destroy_solver(fem_solver* s)
         (void)hipEventDestroy(ev.second);
     }
     free_tiling(s);
+    resident_free(s->res);
     dfree(s->state);
     dfree(s->grad);
     void* m0 = s->marg[0];
@@ -1175,7 +1252,10 @@ void fem_params_default(fem_params* p)
     p->state_layout = FEM_STATE_INTERLEAVED;
 }
 
-fem_status fem_solver_create(const fem_problem* fp, const fem_params* prm, void* hip_stream, fem_solver** out)
+// evaluation: a solver that only evaluates configurations (it takes no steps,
+// so no instance is made resident)
+static fem_status create_solver(const fem_problem* fp, const fem_params* prm, void* hip_stream, bool evaluation,
+                                fem_solver** out)
 {
     if (!out) return fail(FEM_E_INVAL, "out is NULL");
     *out = nullptr;
@@ -1313,12 +1393,27 @@ fem_status fem_solver_create(const fem_problem* fp, const fem_params* prm, void*
     while (!valid_shape(s, sh) && sh.waves > 1) sh.waves /= 2;
     while (!valid_shape(s, sh) && sh.vec > 1) sh.vec /= 2;
     if (!valid_shape(s, sh)) return bail(fail(FEM_E_UNSUPPORTED, "no launch shape fits R = %d, q = %d", s->R, s->q));
+    if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS && IR <= ((size_t)1 << 30)) {   // a grid of IR blocks
+        if (resident_choose(p, s->res)) {
+            std::vector<ResStep> steps((size_t)P.steps + 1);   // read one step ahead
+            for (int t = 0; t < P.steps; ++t) steps[(size_t)t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
+            e = resident_build(p, steps, s->res);
+            if (e != hipSuccess)
+                return bail(fail(e == hipErrorOutOfMemory ? FEM_E_NOMEM : FEM_E_HIP, "resident instances: %s",
+                                 hipGetErrorString(e)));
+        }
+    }
     fem_status st = setup_tiling(s, sh);
     if (st != FEM_OK) return bail(st);
     st = reset_best(s);
     if (st != FEM_OK) return bail(st);
     *out = s;
     return FEM_OK;
+}
+
+fem_status fem_solver_create(const fem_problem* fp, const fem_params* prm, void* hip_stream, fem_solver** out)
+{
+    return create_solver(fp, prm, hip_stream, false, out);
 }
 
 void fem_solver_destroy(fem_solver* s) { destroy_solver(s); }
@@ -1401,8 +1496,7 @@ fem_status fem_step(fem_solver* s, int32_t n_steps)
         return fail(FEM_E_STATE, "step range [%d, %lld) exceeds the schedule of %d steps", s->t,
                     (long long)s->t + n_steps, s->prm.steps);
     HIPCHK(hipSetDevice(s->prob->device));
-    for (int32_t k = 0; k < n_steps; ++k) STCHK(do_step(s));
-    return FEM_OK;
+    return do_steps(s, s->t + n_steps);
 }
 
 fem_status fem_capture(fem_solver* s, int32_t t_end);
@@ -1416,11 +1510,9 @@ fem_status fem_run_until(fem_solver* s, int32_t t_end)
     if (t_end == s->t) return FEM_OK;
     HIPCHK(hipSetDevice(s->prob->device));
     const int t0 = s->t;
-    if (!s->stream) {
-        // graph capture needs a non-null stream: run eagerly on the null stream
-        for (int k = t0; k < t_end; ++k) STCHK(do_step(s));
-        return FEM_OK;
-    }
+    // graph capture needs a non-null stream: run eagerly on the null stream;
+    // resident steps are a launch or two per range and need no graph
+    if (!s->stream || s->res.all) return do_steps(s, t_end);
     STCHK(fem_capture(s, t_end));
     auto it = s->graphs.find(std::make_pair(t0, (int)t_end));
     HIPCHK(hipGraphLaunch(it->second, s->stream));
@@ -1442,14 +1534,13 @@ fem_status fem_capture(fem_solver* s, int32_t t_end)
     if (t_end < s->t || t_end > s->prm.steps)
         return fail(FEM_E_STATE, "t_end %d outside [%d, %d]", t_end, s->t, s->prm.steps);
     if (!s->stream) return fail(FEM_E_STATE, "graph capture needs a non-null stream");
-    if (t_end == s->t || s->graphs.count(std::make_pair((int)s->t, (int)t_end))) return FEM_OK;
+    if (t_end == s->t || s->res.all || s->graphs.count(std::make_pair((int)s->t, (int)t_end))) return FEM_OK;
     HIPCHK(hipSetDevice(s->prob->device));
     const int t0 = s->t;
     const int last = s->last_energy_step;
     HIPCHK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
     s->capturing = true;
-    fem_status st = FEM_OK;
-    for (int k = t0; k < t_end && st == FEM_OK; ++k) st = do_step(s);
+    fem_status st = do_steps(s, t_end);
     s->capturing = false;
     s->t = t0;
     s->last_energy_step = last;
@@ -1596,7 +1687,7 @@ fem_status fem_eval_int(const fem_problem* fp, int32_t R, const int32_t* sigma, 
     prm.steps = 1;
     prm.energy_every = 0;
     fem_solver* s = nullptr;
-    STCHK(fem_solver_create(fp, &prm, nullptr, &s));
+    STCHK(create_solver(fp, &prm, nullptr, true, &s));
     auto done = [&](fem_status st) {
         std::string keep = g_err;
         destroy_solver(s);
@@ -1766,9 +1857,10 @@ fem_status fem_get_tile(const fem_solver* s, fem_tile* t)
     return FEM_OK;
 }
 
-fem_status fem_set_tile(fem_solver* s, const fem_tile* t)
+// The launch shape of the row-tiled kernels; all_tiled: they also take over
+// the resident instances.
+static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool all_tiled)
 {
-    if (!s || !t) return fail(FEM_E_INVAL, "NULL argument");
     TileShape sh;
     sh.vec = s->kind == KIND_BMINCUT ? 1 : t->vec;
     sh.waves = t->waves;
@@ -1781,10 +1873,19 @@ fem_status fem_set_tile(fem_solver* s, const fem_tile* t)
                     t->rows, t->lanes, s->R);
     HIPCHK(hipSetDevice(s->prob->device));
     HIPCHK(hipStreamSynchronize(s->stream));
+    const bool take_over = all_tiled && !s->res.taken.empty();
+    if (take_over) resident_free(s->res);
     STCHK(setup_tiling(s, sh));
-    // column-sum partials are laid out per tile: rebuild them
-    if (s->fields_set && s->kind == KIND_BMINCUT) STCHK(init_marginals(s));
+    // column-sum partials are laid out per tile, and resident instances keep
+    // no marginal copy: rebuild them
+    if (s->fields_set && (s->kind == KIND_BMINCUT || take_over)) STCHK(init_marginals(s));
     return FEM_OK;
+}
+
+fem_status fem_set_tile(fem_solver* s, const fem_tile* t)
+{
+    if (!s || !t) return fail(FEM_E_INVAL, "NULL argument");
+    return apply_tile(s, t, true);
 }
 
 static std::string tune_cache_path()
@@ -1856,7 +1957,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
         if ((lookup_tuned(path, key, sh) && valid_shape(s, sh)) ||
             (lookup_tuned(packaged_tune_path(), key, sh) && valid_shape(s, sh))) {
             fem_tile t{sh.vec, sh.waves, sh.rows, sh.nt, sh.lanes};
-            STCHK(fem_set_tile(s, &t));
+            STCHK(apply_tile(s, &t, false));
             if (chosen) STCHK(fem_get_tile(s, chosen));
             return FEM_OK;
         }
@@ -1888,18 +1989,19 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
         }
     }
     std::vector<TileShape> cands;
+    if (s->res.all) cands.push_back(s->shape);   // no row-tiled steps: nothing to choose
     const int vecs[4] = {1, 2, 4, 8};
     const int wavess[4] = {2, 4, 8, 16};
     const int rowss[4] = {1, 2, 4, 8};
     const int laness[4] = {0, 32, 16, 8};
     // the dense step kernel has a fixed shape: only the non-temporal flag is
     // tried (the rest of the shape serves the read-out)
-    for (int ntf = 0; s->dense && ntf < 2; ++ntf) {
+    for (int ntf = 0; !s->res.all && s->dense && ntf < 2; ++ntf) {
         TileShape sh = s->shape;
         sh.nt = ntf;
         cands.push_back(sh);
     }
-    for (int vi = 0; !s->dense && vi < (s->kind == KIND_BMINCUT ? 1 : 4); ++vi)
+    for (int vi = 0; !s->res.all && !s->dense && vi < (s->kind == KIND_BMINCUT ? 1 : 4); ++vi)
         for (int ln : laness) {
             // a lane cap only matters where it splits the replicas
             const int per_lane = s->kind == KIND_BMINCUT ? 1 : vecs[vi];
@@ -1926,7 +2028,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
     fem_status st = FEM_OK;
     for (const TileShape& sh : cands) {
         fem_tile t{sh.vec, sh.waves, sh.rows, sh.nt, sh.lanes};
-        st = fem_set_tile(s, &t);
+        st = apply_tile(s, &t, false);
         if (st != FEM_OK) break;
         st = save_restore(false);
         if (st != FEM_OK) break;
@@ -1957,7 +2059,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     fem_tile bt{best_sh.vec, best_sh.waves, best_sh.rows, best_sh.nt, best_sh.lanes};
-    fem_status st2 = fem_set_tile(s, &bt);
+    fem_status st2 = apply_tile(s, &bt, false);
     if (st2 == FEM_OK) st2 = save_restore(false);
     dfree(backup);
     if (st != FEM_OK) return st;
@@ -1965,7 +2067,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
     FILE* f = std::fopen(path.c_str(), "a");
     if (f) {
         std::fprintf(f, "%s %d %d %d %d %d\n", key.c_str(), best_sh.vec, best_sh.waves, best_sh.rows, best_sh.nt,
-                     best_sh.lanes);
+                     s->geo.lanes);   // as fem_get_tile reports it (the same shape as an uncapped 0)
         std::fclose(f);
     }
     if (chosen) STCHK(fem_get_tile(s, chosen));
@@ -1977,6 +2079,7 @@ fem_status fem_profile(fem_solver* s, int32_t on)
     if (!s) return fail(FEM_E_INVAL, "solver is NULL");
     s->profile = on != 0;
     s->prof_used = 0;
+    s->prof_steps = 0;
     return FEM_OK;
 }
 
@@ -1991,9 +2094,10 @@ fem_status fem_profile_result(fem_solver* s, double* step_kernel_ms, int32_t* n_
         HIPCHK(hipEventElapsedTime(&ms, s->prof_events[k].first, s->prof_events[k].second));
         tot += ms;
     }
-    *step_kernel_ms = s->prof_used ? tot / (double)s->prof_used : 0.0;
-    if (n_kernels) *n_kernels = (int32_t)s->prof_used;
+    *step_kernel_ms = s->prof_steps ? tot / (double)s->prof_steps : 0.0;
+    if (n_kernels) *n_kernels = (int32_t)s->prof_steps;
     s->prof_used = 0;
+    s->prof_steps = 0;
     return FEM_OK;
 }
 

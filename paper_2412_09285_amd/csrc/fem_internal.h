@@ -205,7 +205,8 @@ hipError_t launch_seg_reduce(const T* part, int cols, const int32_t* chunk_off, 
 hipError_t launch_energy_finish(int kind, int R, int q, int NE, int n_inst, const double* part,
                                 const int32_t* chunk_off, const int32_t* inst_chunk_off, const double* wtot,
                                 const double* csum, double lam, double beta, double* eout, hipStream_t st);
-hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const double* raw,
+// (an instance without chunks keeps its energies)
+hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const int32_t* inst_chunk_off, const double* raw,
                                  const double* wtot, const double* csum, double lam, double beta,
                                  double* eout, hipStream_t st);
 // manipulated gradients (fem_manip.hip): the step kernel, and the read-out copy

@@ -689,6 +689,7 @@ __global__ void __launch_bounds__(256) energy_finish_kernel(int kind, int R, int
     const int r = blockIdx.y * 32 + (threadIdx.x & 31);
     const int sub = threadIdx.x >> 5;
     const int t0 = chunk_off[inst_chunk_off[inst]], t1 = chunk_off[inst_chunk_off[inst + 1]];
+    if (t0 == t1) return;   // its energies are not formed from tiles
     double acc[NE];
 #pragma unroll
     for (int k = 0; k < NE; ++k) acc[k] = 0.0;
@@ -730,13 +731,15 @@ __global__ void __launch_bounds__(256) energy_finish_kernel(int kind, int R, int
 }
 
 // energies: raw[inst][NE][R] -> eout[inst][3][R] = U, S, F
-__global__ void energy_combine_kernel(int kind, int R, int q, int n_inst, const double* __restrict__ raw,
+__global__ void energy_combine_kernel(int kind, int R, int q, int n_inst, const int32_t* __restrict__ inst_chunk_off,
+                                      const double* __restrict__ raw,
                                       const double* __restrict__ wtot, const double* __restrict__ csum,
                                       double lam, double beta, double* __restrict__ eout)
 {
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= n_inst * R) return;
     const int inst = idx / R, r = idx % R;
+    if (inst_chunk_off[inst] == inst_chunk_off[inst + 1]) return;   // its energies are not formed from tiles
     double U, S;
     if (kind == KIND_MAXCUT) {
         const double* x = raw + (size_t)inst * 2 * R;
@@ -1166,12 +1169,14 @@ hipError_t launch_energy_finish(int kind, int R, int q, int NE, int n_inst, cons
     return hipGetLastError();
 }
 
-hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const double* raw, const double* wtot,
+hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const int32_t* inst_chunk_off, const double* raw,
+                                 const double* wtot,
                                  const double* csum, double lam, double beta, double* eout, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
     const int n = n_inst * R;
-    energy_combine_kernel<<<(n + 255) / 256, 256, 0, st>>>(kind, R, q, n_inst, raw, wtot, csum, lam, beta, eout);
+    energy_combine_kernel<<<(n + 255) / 256, 256, 0, st>>>(kind, R, q, n_inst, inst_chunk_off, raw, wtot, csum, lam, beta,
+                                                            eout);
     return hipGetLastError();
 }
 

@@ -1,0 +1,718 @@
+// Resident anneals for small instances of the one-logit problems (MaxCut with
+// explicit or manipulated gradients, Max-k-SAT).
+//
+// Replicas never exchange anything, so one workgroup can carry one replica of
+// one instance through a whole range of steps: h and the moments stay in its
+// registers, the values neighbours read in its LDS, and the adjacency in LDS
+// too where it fits (else it streams from L2).  What bounds a step of a small
+// instance on the row-tiled kernels is latency: a launch, a chain of dependent
+// loads (row bounds, entries, neighbour rows) and one to four reduction
+// launches, for microseconds of arithmetic.  Here a step is the arithmetic and
+// the LDS reads of n rows on one compute unit, which is what bounds it: a
+// gather is one add, one LDS read, one conversion and one double add.
+//
+// Rows are taken by falling degree, one lane per row, entries in slices of 64
+// rows (lanes side by side, padded to the slice's longest row): a wave's
+// lanes finish together, and entry loads are contiguous.  Every row sums its
+// neighbours in CSR order in double, and the update is the tiled kernels', so
+// the fields are bit-identical to theirs.
+//
+// Measured per step with energies (MI355X; resident / best of six row-tiled
+// shapes), MaxCut +-1 at R = 16 and R = 512:
+//   n =  200, degree  20:  1.57 /  7.1 us    1.87 /  8.2 us
+//   n =  800, degree  48:  3.55 /  8.8 us    7.23 / 18.0 us
+//   n = 2000, degree  20:  3.81 /  9.6 us    8.18 / 16.2 us
+//   n = 8000, degree   3:  7.58 / 11.0 us   16.5  / 36.9 us
+// Max-3-SAT, 200 variables, 1200 clauses: 2.28 / 8.3 us and 2.88 / 10.3 us.
+#include "fem_resident.h"
+
+#include <algorithm>
+#include <cstring>
+#include <functional>
+#include <numeric>
+
+#include "fem_device.h"
+
+namespace fem {
+
+// Values per plane (see ResCtx): the positions and two constant slots, which
+// take the last two positions where the offsets end there.
+__host__ __device__ constexpr int res_zero_slot(int npos) { return npos < RES_MAX_ROWS ? npos : RES_MAX_ROWS; }
+__host__ __device__ constexpr int res_values(int npos) { return (res_zero_slot(npos) + 2 + 3) & ~3; }
+// Up to four rows per thread the values are double-buffered (one barrier per
+// step); beyond, LDS is kept for the entries and a step takes two barriers.
+__host__ __device__ constexpr int res_buffers(int rpt) { return rpt <= 4 ? 2 : 1; }
+
+// Element i of a table that no kernel writes, i uniform: through the constant
+// address space, so that it is a scalar load whatever the kernel stores.
+template <typename T>
+__device__ __forceinline__ T uniform_at(const T* p, int i)
+{
+    constexpr int N = sizeof(T) / 4;
+    struct Words {
+        uint32_t w[N];
+    } v;
+    const auto* q = (const __attribute__((address_space(4))) uint32_t*)(p + i);
+#pragma unroll
+    for (int k = 0; k < N; ++k) v.w[k] = q[k];
+    return __builtin_bit_cast(T, v);
+}
+
+// The parts of a resident kernel that do not depend on the problem kind.
+//
+// What neighbours read lies in planes of one float per position, chosen by
+// the entry's own offset, so that a gather is an add, a load and the sum:
+// MaxCut m and -m (the second only where a weight is -1), Max-k-SAT the
+// probability that a negative and that a positive literal is false.
+struct ResCtx {
+    ResInst in;
+    int r, T, tid, lane, wave, nwaves;
+    char* m;              // [buffers][planes][values]
+    int plane, buf;       // bytes per plane and per buffer
+    double* part;         // [2][16][2] energy terms per wave
+    uint2* adj;           // LDS copy of the entries
+    float4* wgt;          // ... and of the weights
+};
+
+// One workgroup = one (instance, replica).  Consecutive workgroups go to the
+// eight XCDs in turn, so an XCD gets a contiguous range of an instance's
+// replicas: neighbours in the state rows share cache lines.
+template <int RPT>
+__device__ __forceinline__ void res_ctx(const ResArgs& a, char* lds, ResCtx& c)
+{
+    const int ii = blockIdx.x / a.R, k = blockIdx.x % a.R, x = k & 7;
+    c.in = uniform_at(a.inst, ii);
+    c.r = x * (a.R >> 3) + min(x, a.R & 7) + (k >> 3);
+    c.T = blockDim.x;
+    c.tid = threadIdx.x;
+    c.lane = threadIdx.x & 63;
+    c.wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    c.nwaves = blockDim.x >> 6;
+    c.plane = res_values(c.in.npos) * 4;
+    c.buf = c.plane * a.planes;
+    c.part = reinterpret_cast<double*>(lds);
+    c.m = lds + RES_PART_BYTES;
+    c.adj = reinterpret_cast<uint2*>(c.m + res_buffers(RPT) * c.buf);
+    c.wgt = reinterpret_cast<float4*>(c.adj + c.in.n_adj);
+}
+
+// x plus x of the lane that a row rotation by N lanes brings here
+template <int N>
+__device__ __forceinline__ double add_ror(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x120 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x120 + N, 0xf, 0xf, true);
+    return x + __longlong_as_double(((long long)hi << 32) | (uint32_t)lo);
+}
+__device__ __forceinline__ double row16_sum(double x) { return add_ror<1>(add_ror<2>(add_ror<4>(add_ror<8>(x)))); }
+
+// The wave's sums of the two energy terms, in double and in a fixed order, to
+// its slots of part: the lower half-wave sums the first term, the upper the
+// second.
+__device__ __forceinline__ void res_partial(const ResCtx& c, int t, float e0, float e1)
+{
+    const bool up = c.lane >= 32;
+    const float other = __shfl_xor(up ? e0 : e1, 32, 64);
+    double x = row16_sum((double)(up ? e1 : e0) + (double)other);
+    x += __shfl_xor(x, 16, 64);
+    if ((c.lane & 31) == 0) c.part[((t & 1) * 16 + c.wave) * 2 + (up ? 1 : 0)] = x;
+}
+
+// Energies of step t from the waves' partial sums, after the step's barrier:
+// formed by the last wave (the one with the fewest neighbours) while the
+// others go on.
+__device__ __forceinline__ void res_energy(const ResArgs& a, const ResCtx& c, int t)
+{
+    const int w = c.lane & 31;
+    double x = w < c.nwaves ? c.part[((t & 1) * 16 + w) * 2 + (c.lane >> 5)] : 0.0;
+    x = row16_sum(x);   // at most 16 waves: one row of lanes per term
+    const long long b = __double_as_longlong(x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)b, 32);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 32);
+    const double S = __longlong_as_double(((long long)hi << 32) | lo);
+    if (c.lane == 0) {
+        const double U = a.kind == KIND_MAXCUT ? -a.wtot[c.in.inst] + 0.5 * x : x;
+        double* o = a.eout + (t / a.energy_every) * a.erecord + (size_t)c.in.inst * 3 * a.R + c.r;
+        o[0] = U;
+        o[a.R] = S;
+        o[2 * a.R] = U - S / uniform_at(a.steps, t).beta;
+    }
+}
+
+__device__ __forceinline__ float lds_val(const char* m, uint32_t off) { return *reinterpret_cast<const float*>(m + off); }
+
+// The gather of one row: sum_j W_ij m_j, four entries per round, CSR order.
+// first: the first two rounds, already loaded (entries beyond a slice belong
+// to the next one, or to the padding at the end of the array: never used).
+template <bool UNIT>
+struct ResRound {
+    uint2 e;
+    float4 w;   // weights, where they are not +-1
+};
+template <bool UNIT, typename AP, typename WP>
+__device__ __forceinline__ ResRound<UNIT> res_round_at(AP ap, WP wp, int at)
+{
+    ResRound<UNIT> q;
+    q.e = ap[at];
+    if constexpr (!UNIT) q.w = wp[at];
+    return q;
+}
+template <bool UNIT>
+__device__ __forceinline__ double res_add(const char* m, const ResRound<UNIT>& q, double acc)
+{
+    const float v[4] = {lds_val(m, q.e.x & 0xffffu), lds_val(m, q.e.x >> 16), lds_val(m, q.e.y & 0xffffu),
+                        lds_val(m, q.e.y >> 16)};
+    if constexpr (UNIT) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc += (double)v[u];
+    } else {
+        acc = fma((double)q.w.x, (double)v[0], acc);
+        acc = fma((double)q.w.y, (double)v[1], acc);
+        acc = fma((double)q.w.z, (double)v[2], acc);
+        acc = fma((double)q.w.w, (double)v[3], acc);
+    }
+    return acc;
+}
+
+__device__ __forceinline__ float res_bf16(float x, int bf16) { return bf16 ? bf16_to_f32(f32_to_bf16(x)) : x; }
+
+// MaxCut: phi = sum_j W_ij m_j, g = P(1-P) [2 phi + h/beta] (maxcut_step_kernel),
+// or with MANIP m_j = +-1 the read-out, g = gamma P(1-P) [c phi + h/beta]
+// (maxcut_manip_kernel).  UNIT: weights +-1, the sign in the entry's plane.
+template <int RPT, bool MANIP, bool UNIT, bool ALDS>
+__global__ void __launch_bounds__(1024) res_maxcut_kernel(ResArgs a)
+{
+    extern __shared__ __align__(16) char lds[];
+    constexpr bool TWO = res_buffers(RPT) == 2;
+    ResCtx c;
+    res_ctx<RPT>(a, lds, c);
+    // per row: the state, e = exp(-|h|) and 1/(1 + e), the normaliser
+    float h[RPT], m1[RPT], m2[RPT], ex[RPT], rc[RPT];
+    double cn[MANIP ? RPT : 1];
+    int row[RPT];
+    int2 sl[RPT];
+    const bool signs = a.planes == 2;
+    // the value neighbours read of row k, into the buffer at m
+    auto publish = [&](char* m, int k) {
+        float v;
+        if constexpr (MANIP) {
+            v = h[k] > 0.0f ? 1.0f : -1.0f;
+        } else {
+            v = res_bf16(tanh_half(h[k], ex[k], rc[k]), a.bf16);
+        }
+        float* p = reinterpret_cast<float*>(m) + k * c.T + c.tid;
+        *p = v;
+        if (signs) *reinterpret_cast<float*>(reinterpret_cast<char*>(p) + c.plane) = -v;
+    };
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        row[k] = a.perm[c.in.pos0 + k * c.T + c.tid];
+        sl[k] = uniform_at(a.slice, c.in.slice0 + k * c.nwaves + c.wave);
+        h[k] = m1[k] = m2[k] = ex[k] = rc[k] = 0.0f;
+        if constexpr (MANIP) cn[k] = 0.0;
+        if (row[k] >= 0) {
+            const size_t s = (size_t)row[k] * a.srow + c.r;
+            h[k] = a.h[s];
+            m1[k] = a.m1[s];
+            m2[k] = a.m2[s];
+            if constexpr (MANIP) {
+                const double l1 = a.nrm[row[k]];
+                cn[k] = l1 > 0.0 ? 1.0 / l1 : 0.0;
+            }
+            publish(c.m + (TWO ? (a.t0 & 1) * c.buf : 0), k);
+        }
+    }
+    if (c.tid < res_buffers(RPT))
+        reinterpret_cast<float*>(c.m + c.tid * c.buf)[res_zero_slot(c.in.npos)] = 0.0f;
+    if constexpr (ALDS) {
+        for (int k = c.tid; k < c.in.n_adj; k += c.T) {
+            c.adj[k] = a.adj[c.in.adj0 + k];
+            if constexpr (!UNIT) c.wgt[k] = a.wgt[c.in.adj0 + k];
+        }
+    }
+    __syncthreads();
+    StepScalars sc = uniform_at(a.steps, a.t0).sc;
+    for (int t = a.t0; t < a.t1; ++t) {
+        const bool en = !MANIP && a.energy_every > 0 && t % a.energy_every == 0;
+        const bool last = t + 1 == a.t1;
+        const char* mc = c.m + (TWO ? (t & 1) * c.buf : 0);
+        char* mn = c.m + (TWO ? ((t & 1) ^ 1) * c.buf : 0);
+        float e0 = 0.0f, e1 = 0.0f;
+        auto field = [&](int k, const ResRound<UNIT>& q0, const ResRound<UNIT>& q1) -> double {
+            double acc = 0.0;
+            const int rounds = sl[k].y;
+            if constexpr (ALDS) {
+                const uint2* ap = c.adj + sl[k].x * 64 + c.lane;
+                const float4* wp = c.wgt + sl[k].x * 64 + c.lane;
+#pragma unroll 4
+                for (int g = 0; g < rounds; ++g) acc = res_add<UNIT>(mc, res_round_at<UNIT>(ap, wp, g * 64), acc);
+            } else if constexpr (!UNIT) {
+                const uint2* ap = a.adj + c.in.adj0 + sl[k].x * 64 + c.lane;
+                const float4* wp = a.wgt + c.in.adj0 + sl[k].x * 64 + c.lane;
+#pragma unroll 2
+                for (int g = 0; g < rounds; ++g) acc = res_add<UNIT>(mc, res_round_at<UNIT>(ap, wp, g * 64), acc);
+            } else {
+                // entries from L2: two rounds ahead
+                const uint2* ap = a.adj + c.in.adj0 + sl[k].x * 64 + c.lane;
+                const float4* wp = nullptr;
+                ResRound<UNIT> x0 = q0, x1 = q1;
+                for (int g = 0; g < rounds; g += 2) {
+                    const ResRound<UNIT> n0 = res_round_at<UNIT>(ap, wp, (g + 2) * 64);
+                    const ResRound<UNIT> n1 = res_round_at<UNIT>(ap, wp, (g + 3) * 64);
+                    acc = res_add<UNIT>(mc, x0, acc);
+                    if (g + 1 < rounds) acc = res_add<UNIT>(mc, x1, acc);
+                    x0 = n0;
+                    x1 = n1;
+                }
+            }
+            return acc;
+        };
+        auto first = [&](int k, int g) -> ResRound<UNIT> {
+            ResRound<UNIT> q{};
+            q.e = a.adj[c.in.adj0 + (sl[k].x + g) * 64 + c.lane];
+            return q;
+        };
+        // the update of row k from its field
+        auto update = [&](int k, double acc) {
+            const float x = h[k], e = MANIP ? exp_neg(fabsf(x)) : ex[k];
+            const float r = MANIP ? rcp_f(1.0f + e) : rc[k];
+            const float pmin = e * r;   // min(P, 1 - P)
+            const float pq = pmin * r;  // P (1 - P)
+            float g;
+            if constexpr (MANIP) g = (float)(sc.gamma_d * ((double)pq * (cn[k] * acc + (double)x * sc.inv_beta_d)));
+            else g = (float)((double)pq * fma((double)x, sc.inv_beta_d, 2.0 * acc));
+            if (en && row[k] >= 0) {
+                const float m_own = copysignf((1.0f - e) * r, x);
+                e0 += (float)((double)m_own * acc);
+                e1 += log1p_f(e) + fabsf(x) * pmin;
+            }
+            h[k] = adam_update(x, g, m1[k], m2[k], sc);
+            if (row[k] >= 0) {
+                publish(mn, k);
+                if (last && a.grad) a.grad[(size_t)row[k] * a.R + c.r] = g;
+            }
+        };
+        ResRound<UNIT> q0{}, q1{};
+        if constexpr (!ALDS && UNIT) {
+            q0 = first(0, 0);
+            q1 = first(0, 1);
+        }
+        double acc[RPT];
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            if ((k * c.nwaves + c.wave) * 64 >= c.in.n) continue;   // no rows in this slice
+            ResRound<UNIT> n0{}, n1{};
+            if constexpr (!ALDS && UNIT) {
+                const int kn = k + 1 < RPT ? k + 1 : k;   // the next row's first rounds
+                n0 = first(kn, 0);
+                n1 = first(kn, 1);
+            }
+            acc[k] = field(k, q0, q1);
+            q0 = n0;
+            q1 = n1;
+            if constexpr (TWO) update(k, acc[k]);
+        }
+        if constexpr (!TWO) {
+            __syncthreads();   // every gather has read the old values
+#pragma unroll
+            for (int k = 0; k < RPT; ++k)
+                if ((k * c.nwaves + c.wave) * 64 < c.in.n) update(k, acc[k]);
+        }
+        if (en) res_partial(c, t, e0, e1);
+        sc = uniform_at(a.steps, t + 1).sc;   // the table has an entry beyond the last step
+        __syncthreads();
+        if (en && c.wave == c.nwaves - 1) res_energy(a, c, t);
+    }
+#pragma unroll
+    for (int k = 0; k < RPT; ++k)
+        if (row[k] >= 0) {
+            const size_t s = (size_t)row[k] * a.srow + c.r;
+            a.h[s] = h[k];
+            a.m1[s] = m1[k];
+            a.m2[s] = m2[k];
+        }
+}
+
+// Max-k-SAT (sat_step_kernel): W other literals per incidence; 8 bytes hold
+// two incidences of two literals or one of three.  Bit 31 of the first word
+// of an incidence is its own literal's sign, bit 15 marks the clause's owner.
+template <int RPT, int W, bool ALDS>
+__global__ void __launch_bounds__(1024) res_sat_kernel(ResArgs a)
+{
+    extern __shared__ __align__(16) char lds[];
+    ResCtx c;
+    res_ctx<RPT>(a, lds, c);
+    float h[RPT], m1[RPT], m2[RPT], ex[RPT], rc[RPT];
+    int row[RPT];
+    int2 sl[RPT];
+    // the probabilities that a negative and a positive literal of row k are
+    // false, from the stored form of its marginal
+    auto publish = [&](char* m, int k) {
+        ex[k] = exp_neg(fabsf(h[k]));
+        rc[k] = rcp_f(1.0f + ex[k]);
+        const float small = ex[k] * rc[k];   // sat_encode
+        const float s = res_bf16(h[k] > 0.0f ? -small : small, a.bf16);
+        float* p = reinterpret_cast<float*>(m) + k * c.T + c.tid;
+        *p = sat_u_bits(s, 0u);
+        *reinterpret_cast<float*>(reinterpret_cast<char*>(p) + c.plane) = sat_u_bits(s, SAT_POS);
+    };
+#pragma unroll
+    for (int k = 0; k < RPT; ++k) {
+        row[k] = a.perm[c.in.pos0 + k * c.T + c.tid];
+        sl[k] = uniform_at(a.slice, c.in.slice0 + k * c.nwaves + c.wave);
+        h[k] = m1[k] = m2[k] = ex[k] = rc[k] = 0.0f;
+        if (row[k] >= 0) {
+            const size_t s = (size_t)row[k] * a.srow + c.r;
+            h[k] = a.h[s];
+            m1[k] = a.m1[s];
+            m2[k] = a.m2[s];
+            publish(c.m + (a.t0 & 1) * c.buf, k);
+        }
+    }
+    // a padding record has a literal that is false with probability 0, an
+    // unused literal slot the factor 1
+    if (c.tid < 2) {
+        float* z = reinterpret_cast<float*>(c.m + c.tid * c.buf) + res_zero_slot(c.in.npos);
+        z[0] = 0.0f;
+        z[1] = 1.0f;
+    }
+    if constexpr (ALDS)
+        for (int k = c.tid; k < c.in.n_adj; k += c.T) c.adj[k] = a.adj[c.in.adj0 + k];
+    __syncthreads();
+    StepScalars sc = uniform_at(a.steps, a.t0).sc;
+    for (int t = a.t0; t < a.t1; ++t) {
+        const bool en = a.energy_every > 0 && t % a.energy_every == 0;
+        const bool last = t + 1 == a.t1;
+        const char* mc = c.m + (t & 1) * c.buf;
+        char* mn = c.m + ((t & 1) ^ 1) * c.buf;
+        float e0 = 0.0f, e1 = 0.0f;
+#pragma unroll
+        for (int k = 0; k < RPT; ++k) {
+            if ((k * c.nwaves + c.wave) * 64 >= c.in.n) continue;   // no rows in this slice
+            const int base = sl[k].x * 64 + c.lane;
+            const float x = h[k];
+            const float pmin = ex[k] * rc[k];   // min(P, 1 - P)
+            const float pq = pmin * rc[k];      // P (1 - P)
+            // own literal false, by its sign
+            const float u_neg = x > 0.0f ? 1.0f - pmin : pmin, u_pos = x > 0.0f ? pmin : 1.0f - pmin;
+            double d = 0.0;
+            auto add = [&](float cv, uint32_t e) {
+                d += (double)__uint_as_float(__float_as_uint(cv) ^ (e & 0x80000000u));
+                if (en) {
+                    const float uo = (int)e < 0 ? u_pos : u_neg;
+                    e0 += (e & 0x8000u) ? uo * cv : 0.0f;
+                }
+            };
+            const uint2* ap = ALDS ? c.adj + base : a.adj + c.in.adj0 + base;
+#pragma unroll 4
+            for (int g = 0; g < sl[k].y; ++g) {
+                const uint2 q = ap[g * 64];
+                const uint32_t p = q.x & 0x7fff7fffu, o = q.y & 0x7fff7fffu;
+                if constexpr (W == 2) {
+                    add(lds_val(mc, p & 0xffffu) * lds_val(mc, p >> 16), q.x);
+                    add(lds_val(mc, o & 0xffffu) * lds_val(mc, o >> 16), q.y);
+                } else {
+                    float cv = lds_val(mc, p & 0xffffu) * lds_val(mc, p >> 16);
+                    cv *= lds_val(mc, o & 0xffffu);
+                    add(cv, q.x);
+                }
+            }
+            const float g = (float)(sc.gamma_d * ((double)pq * fma((double)x, sc.inv_beta_d, d)));
+            if (en && row[k] >= 0) e1 += log1p_f(ex[k]) + fabsf(x) * pmin;
+            h[k] = adam_update(x, g, m1[k], m2[k], sc);
+            if (row[k] >= 0) {
+                publish(mn, k);
+                if (last && a.grad) a.grad[(size_t)row[k] * a.R + c.r] = g;
+            }
+        }
+        if (en) res_partial(c, t, e0, e1);
+        sc = uniform_at(a.steps, t + 1).sc;   // the table has an entry beyond the last step
+        __syncthreads();
+        if (en && c.wave == c.nwaves - 1) res_energy(a, c, t);
+    }
+#pragma unroll
+    for (int k = 0; k < RPT; ++k)
+        if (row[k] >= 0) {
+            const size_t s = (size_t)row[k] * a.srow + c.r;
+            a.h[s] = h[k];
+            a.m1[s] = m1[k];
+            a.m2[s] = m2[k];
+        }
+}
+
+// ------------------------------------------------------------------- host --
+// Workgroup, entries and LDS of an instance.
+struct ResPlan {
+    int threads = 64, rpt = 1;
+    int64_t n_adj = 0;       // entries of 8 bytes, padding included
+    size_t lds = 0;          // energy terms, values and (adj_lds) entries
+    bool adj_lds = false;
+    bool ok = false;
+};
+
+static ResPlan res_plan(const Problem& p, int b, int planes, bool unit, size_t dev_lds)
+{
+    ResPlan r;
+    const bool sat = p.kind == KIND_MAXSAT;
+    const int32_t row0 = p.inst_off[(size_t)b];
+    const int64_t n = p.inst_off[(size_t)b + 1] - row0;
+    if (p.kind == KIND_BMINCUT || n > (sat ? RES_MAX_ROWS_SAT : RES_MAX_ROWS)) return r;
+    while (r.threads < n && r.threads < 1024) r.threads <<= 1;
+    while ((int64_t)r.rpt * r.threads < n) r.rpt <<= 1;
+    const int64_t* ro = p.h_row_off.data() + row0;
+    std::vector<int32_t> deg((size_t)n);
+    for (int64_t i = 0; i < n; ++i) deg[(size_t)i] = (int32_t)std::min<int64_t>(ro[i + 1] - ro[i], 1 << 20);
+    std::sort(deg.begin(), deg.end(), std::greater<int32_t>());
+    const int per = !sat ? 4 : p.sat_width == 2 ? 2 : 1;
+    for (int64_t s = 0; s < n; s += 64) r.n_adj += (deg[(size_t)s] + per - 1) / per * 64;
+    r.lds = RES_PART_BYTES + (size_t)res_buffers(r.rpt) * planes * res_values(r.threads * r.rpt) * 4;
+    const size_t with = r.lds + (size_t)r.n_adj * (unit ? 8 : 24);
+    r.adj_lds = with <= dev_lds;
+    if (r.adj_lds) r.lds = with;
+    r.ok = r.lds <= dev_lds && (r.rpt <= 4 || (unit && r.adj_lds));
+    if (!r.adj_lds && r.n_adj > RES_MAX_STREAM) r.ok = false;
+    return r;
+}
+
+void resident_free(ResData& r)
+{
+    if (r.block) (void)hipFree(r.block);
+    r = ResData{};
+}
+
+// The rule: an instance is resident if its rows fit the registers of one
+// workgroup (RES_MAX_ROWS) and its entries fit LDS beside the values, or
+// number at most RES_MAX_STREAM and stream from L2.  It looks at the instance
+// alone, so an instance takes the same path by itself and inside a batch.
+// In LDS it won at every size measured (the table above).  Streaming, at
+// R = 16, resident against the best row-tiled shape: n = 2000 of degree 100
+// (51 k entries of 8 bytes) 11.4 / 12.5 us, n = 2000 of degree 120 (61 k)
+// 13.5 / 13.2 us, n = 1000 of degree 250 (63 k) 13.3 / 15.5 us, and at
+// R = 512 24 / 31, 29 / 35 and 29 / 46 us; beyond, one compute unit reads for
+// longer than the whole chip needs.  Eight rows per thread are instantiated
+// only where they fit the registers: +-1 weights, entries in LDS.
+bool resident_choose(const Problem& p, ResData& r)
+{
+    const bool sat = p.kind == KIND_MAXSAT;
+    int dev_lds = 0;
+    if (p.kind == KIND_BMINCUT ||
+        hipDeviceGetAttribute(&dev_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device) != hipSuccess)
+        return false;
+    r.pm1 = !sat && p.adj_pm1 != nullptr;
+    r.planes = sat ? 2 : 1;
+    for (size_t k = 0; r.pm1 && r.planes == 1 && k < p.h_adj.size(); ++k)
+        if ((uint32_t)p.h_adj[k].y & 0x80000000u) r.planes = 2;
+    r.dev_lds = (size_t)dev_lds;
+    r.taken.assign((size_t)p.n_inst, 0);
+    int n = 0;
+    for (int b = 0; b < p.n_inst; ++b)
+        n += r.taken[(size_t)b] = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds).ok ? 1 : 0;
+    r.all = n == p.n_inst;
+    if (!n) r = ResData{};
+    return n > 0;
+}
+
+hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r)
+{
+    hipError_t e = hipSuccess;
+    const bool sat = p.kind == KIND_MAXSAT;
+    std::vector<int> ids;
+    for (int b = 0; b < p.n_inst; ++b)
+        if (r.taken[(size_t)b]) ids.push_back(b);
+    auto rows_of = [&](int b) { return (int)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]); };
+    // larger instances first: the longest workgroups start first
+    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return rows_of(x) > rows_of(y); });
+    std::vector<ResInst> inst;
+    std::vector<int32_t> perm;
+    std::vector<int2> slice;
+    std::vector<uint2> adj;
+    std::vector<float4> wgt;
+    // entries per 8 bytes
+    const int per = !sat ? 4 : p.sat_width == 2 ? 2 : 1;
+    std::vector<int32_t> order, pos;
+    for (int b : ids) {
+        const int n = rows_of(b), row0 = p.inst_off[(size_t)b];
+        const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
+        const int threads = plan.threads, rpt = plan.rpt;
+        if (r.classes.empty() || r.classes.back().threads != threads || r.classes.back().rpt != rpt ||
+            r.classes.back().adj_lds != plan.adj_lds) {
+            ResClass c;
+            c.threads = threads;
+            c.rpt = rpt;
+            c.first = (int)inst.size();
+            c.adj_lds = plan.adj_lds;
+            r.classes.push_back(c);
+        }
+        r.classes.back().n_inst++;
+        r.classes.back().lds = std::max(r.classes.back().lds, plan.lds);
+        ResInst in{};
+        in.inst = b;
+        in.row0 = row0;
+        in.n = n;
+        in.npos = threads * rpt;
+        in.pos0 = (int32_t)perm.size();
+        in.slice0 = (int32_t)slice.size();
+        in.adj0 = (int64_t)adj.size();
+        const int64_t* ro = p.h_row_off.data() + row0;
+        order.resize((size_t)n);
+        std::iota(order.begin(), order.end(), 0);
+        std::stable_sort(order.begin(), order.end(),
+                         [&](int32_t x, int32_t y) { return ro[x + 1] - ro[x] > ro[y + 1] - ro[y]; });
+        pos.resize((size_t)n);
+        for (int k = 0; k < n; ++k) pos[(size_t)order[(size_t)k]] = k;
+        for (int k = 0; k < in.npos; ++k) perm.push_back(k < n ? row0 + order[(size_t)k] : -1);
+        const uint32_t zero = (uint32_t)res_zero_slot(in.npos) << 2, one = zero + 4;
+        const uint32_t plane = (uint32_t)res_values(in.npos) << 2;
+        auto lit = [&](uint32_t l) {   // a literal slot of an incidence record
+            const uint32_t var = l & SAT_VAR_MASK;
+            if (var == SAT_NONE) return one;
+            return ((uint32_t)pos[(size_t)var - (size_t)row0] << 2) + ((l & SAT_POS) ? plane : 0u);
+        };
+        auto sat_word = [&](uint32_t s0, uint32_t s1, bool own_pos, bool owner) {
+            return lit(s0) | (lit(s1) << 16) | (owner ? 0x8000u : 0u) | (own_pos ? 0x80000000u : 0u);
+        };
+        for (int s = 0; s < in.npos / 64; ++s) {
+            int64_t deg = 0;
+            for (int l = 0; l < 64; ++l) {
+                const int k = s * 64 + l;
+                if (k < n) deg = std::max(deg, ro[order[(size_t)k] + 1] - ro[order[(size_t)k]]);
+            }
+            const int rounds = (int)((deg + per - 1) / per);
+            const size_t at = adj.size();
+            slice.push_back(make_int2((int)((at - (size_t)in.adj0) / 64), rounds));
+            adj.resize(at + (size_t)rounds * 64);
+            if (!sat && !r.pm1) wgt.resize(at + (size_t)rounds * 64, make_float4(0, 0, 0, 0));
+            for (int l = 0; l < 64; ++l) {
+                const int k = s * 64 + l;
+                const int64_t k0 = k < n ? ro[order[(size_t)k]] : 0, k1 = k < n ? ro[order[(size_t)k] + 1] : 0;
+                for (int g = 0; g < rounds; ++g) {
+                    uint32_t w[2] = {0, 0};
+                    float wf[4] = {0, 0, 0, 0};
+                    for (int u = 0; u < per; ++u) {
+                        const int64_t q = k0 + (int64_t)g * per + u;
+                        if (!sat) {
+                            uint32_t ent = zero;
+                            if (q < k1) {
+                                const int2 ad = p.h_adj[(size_t)q];
+                                float we;
+                                std::memcpy(&we, &ad.y, 4);
+                                ent = ((uint32_t)pos[(size_t)(ad.x - row0)] << 2) + (r.pm1 && we < 0.0f ? plane : 0u);
+                                wf[u] = we;
+                            }
+                            w[u / 2] |= ent << (16 * (u & 1));
+                        } else if (p.sat_width == 2) {
+                            w[u] = zero | (one << 16);
+                            if (q < k1) {
+                                const uint32_t x = (uint32_t)p.h_inc2[(size_t)q].x, y = (uint32_t)p.h_inc2[(size_t)q].y;
+                                w[u] = sat_word(x & ~SAT_FLAG, y & ~SAT_FLAG, x & SAT_FLAG, y & SAT_FLAG);
+                            }
+                        } else {
+                            w[0] = zero | (one << 16);
+                            w[1] = one;
+                            if (q < k1) {
+                                const int4 rec = p.h_inc4[(size_t)q];
+                                w[0] = sat_word((uint32_t)rec.x, (uint32_t)rec.y, rec.w & 1, rec.w & 2);
+                                w[1] = lit((uint32_t)rec.z);
+                            }
+                        }
+                    }
+                    adj[at + (size_t)g * 64 + l] = make_uint2(w[0], w[1]);
+                    if (!sat && !r.pm1) wgt[at + (size_t)g * 64 + l] = make_float4(wf[0], wf[1], wf[2], wf[3]);
+                }
+            }
+        }
+        in.n_adj = (int32_t)(adj.size() - (size_t)in.adj0);
+        inst.push_back(in);
+    }
+    // entries are read two rounds ahead
+    adj.resize(adj.size() + 4 * 64);
+    if (!wgt.empty()) wgt.resize(wgt.size() + 4 * 64);
+    // one allocation and one transfer for all tables
+    std::vector<char> host;
+    auto put = [&](const auto& v) {
+        const size_t at = (host.size() + 255) & ~(size_t)255, bytes = v.size() * sizeof(v[0]);
+        host.resize(at + bytes);
+        if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
+        return at;
+    };
+    const size_t o_inst = put(inst), o_perm = put(perm), o_slice = put(slice), o_adj = put(adj), o_wgt = put(wgt),
+                 o_steps = put(steps);
+    if ((e = hipMalloc(&r.block, host.size())) != hipSuccess) {
+        r.block = nullptr;
+        return e;
+    }
+    if ((e = hipMemcpy(r.block, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) return e;
+    char* d = static_cast<char*>(r.block);
+    r.inst = reinterpret_cast<ResInst*>(d + o_inst);
+    r.perm = reinterpret_cast<int32_t*>(d + o_perm);
+    r.slice = reinterpret_cast<int2*>(d + o_slice);
+    r.adj = reinterpret_cast<uint2*>(d + o_adj);
+    r.wgt = reinterpret_cast<float4*>(d + o_wgt);
+    r.steps = reinterpret_cast<ResStep*>(d + o_steps);
+    return hipSuccess;
+}
+
+typedef void (*ResKernel)(ResArgs);
+
+template <bool MANIP, bool PM1, bool ALDS>
+static ResKernel maxcut_kernel(int rpt)
+{
+    switch (rpt) {
+    case 1: return res_maxcut_kernel<1, MANIP, PM1, ALDS>;
+    case 2: return res_maxcut_kernel<2, MANIP, PM1, ALDS>;
+    case 4: return res_maxcut_kernel<4, MANIP, PM1, ALDS>;
+    case 8:
+        if constexpr (PM1 && ALDS) return res_maxcut_kernel<8, MANIP, PM1, ALDS>;
+        return nullptr;
+    default: return nullptr;
+    }
+}
+
+template <int W, bool ALDS>
+static ResKernel sat_kernel(int rpt)
+{
+    switch (rpt) {
+    case 1: return res_sat_kernel<1, W, ALDS>;
+    case 2: return res_sat_kernel<2, W, ALDS>;
+    case 4: return res_sat_kernel<4, W, ALDS>;
+    default: return nullptr;
+    }
+}
+
+template <bool ALDS>
+static ResKernel pick(const Problem& p, bool pm1, bool manip, int rpt)
+{
+    if (p.kind == KIND_MAXSAT) return p.sat_width == 2 ? sat_kernel<2, ALDS>(rpt) : sat_kernel<3, ALDS>(rpt);
+    if (manip) return pm1 ? maxcut_kernel<true, true, ALDS>(rpt) : maxcut_kernel<true, false, ALDS>(rpt);
+    return pm1 ? maxcut_kernel<false, true, ALDS>(rpt) : maxcut_kernel<false, false, ALDS>(rpt);
+}
+
+hipError_t resident_launch(const Problem& p, const ResData& r, bool manip, ResArgs a, hipStream_t st)
+{
+    (void)hipGetLastError();   // drop stale errors of earlier calls
+    a.perm = r.perm;
+    a.slice = r.slice;
+    a.adj = r.adj;
+    a.wgt = r.wgt;
+    a.steps = r.steps;
+    a.nrm = p.nrm;
+    a.kind = p.kind;
+    a.planes = r.planes;
+    for (const ResClass& c : r.classes) {
+        a.inst = r.inst + c.first;
+        ResKernel k = c.adj_lds ? pick<true>(p, r.pm1, manip, c.rpt) : pick<false>(p, r.pm1, manip, c.rpt);
+        if (!k) return hipErrorInvalidValue;
+        if (c.lds > 64 * 1024) {
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds);
+            if (e != hipSuccess) return e;
+        }
+        k<<<dim3((unsigned)c.n_inst * (unsigned)a.R), dim3(c.threads), c.lds, st>>>(a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace fem
