@@ -24,6 +24,7 @@
 #include "../../include/fem.h"
 #include "fem_internal.h"
 #include "fem_dense.h"
+#include "fem_readout.h"
 #include "fem_resident.h"
 
 using namespace fem;
@@ -433,7 +434,7 @@ struct fem_solver {
     LaunchGeom egeo{};   // evaluation kernels: one replica per lane
     int lanes_log2 = 0;
     TileSet ts;   // the instances of the row-tiled step kernels
-    TileSet es;   // evaluation: every instance (ts itself where that is all)
+    TileSet es;   // byte evaluation: every instance (ts itself where that is all)
     // instances whose replicas run on one compute unit each (fem_resident.hip)
     ResData res;
     // energies
@@ -462,6 +463,12 @@ struct fem_solver {
     int* sint = nullptr;
     long long* sout = nullptr;
     double* best = nullptr;
+    // one-logit read-out on bit words (fem_readout.hip), where it applies
+    uint32_t* bits = nullptr;    // [n][bit_words(R)]
+    int32_t* count = nullptr;    // [inst][R], behind them
+    TileSet bs;
+    // best replica: double value [inst], int32 replica [inst], uint8 state [n]
+    char* pick = nullptr;
     // schedules
     std::vector<double> beta, lam;
     // graphs keyed by (t0, t1)
@@ -521,8 +528,6 @@ static void free_tiling(fem_solver* s)
     if (s->es.tiles == s->ts.tiles) s->es = TileSet{};
     for (TileSet* x : {&s->ts, &s->es}) {
         dfree(x->tiles);
-        dfree(x->chunk_off);
-        dfree(x->inst_chunk_off);
         *x = TileSet{};
     }
     dfree(s->epart);
@@ -593,14 +598,18 @@ static fem_status make_tiles(const Problem& p, int tile_rows, const uint8_t* ski
         }
         for (size_t pos = 0; pos < nt; ++pos) order[pos] = seg_major ? tiles[pos] : tiles[start[pos % X] + pos / X];
     }
-    auto up = [](auto** d, const auto& v) -> hipError_t {
-        hipError_t e = dalloc(d, v.size());
-        if (e == hipSuccess && !v.empty()) e = hipMemcpy(*d, v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice);
-        return e;
-    };
-    HIPCHK(up(&ts.tiles, order));
-    HIPCHK(up(&ts.chunk_off, chunk_off));
-    HIPCHK(up(&ts.inst_chunk_off, inst_chunk_off));
+    // one allocation (held by tiles) and one transfer
+    const size_t b0 = order.size() * sizeof(Tile), b1 = chunk_off.size() * 4, b2 = inst_chunk_off.size() * 4;
+    std::vector<char> host(b0 + b1 + b2);
+    if (b0) std::memcpy(host.data(), order.data(), b0);
+    std::memcpy(host.data() + b0, chunk_off.data(), b1);
+    std::memcpy(host.data() + b0 + b1, inst_chunk_off.data(), b2);
+    char* d = nullptr;
+    HIPCHK(dalloc(&d, host.size()));
+    ts.tiles = reinterpret_cast<Tile*>(d);
+    ts.chunk_off = reinterpret_cast<int32_t*>(d + b0);
+    ts.inst_chunk_off = reinterpret_cast<int32_t*>(d + b0 + b1);
+    HIPCHK(hipMemcpy(d, host.data(), host.size(), hipMemcpyHostToDevice));
     return FEM_OK;
 }
 
@@ -620,16 +629,18 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
     const int tile_rows = s->dense ? DENSE_ROWS : s->geo.teams_per_block * shape.rows;
     const bool mixed = !s->res.taken.empty();
     STCHK(make_tiles(p, tile_rows, mixed ? s->res.taken.data() : nullptr, s->geo.seg_major != 0, s->ts));
-    if (mixed) STCHK(make_tiles(p, tile_rows, nullptr, s->geo.seg_major != 0, s->es));
-    else s->es = s->ts;
+    if (!mixed) s->es = s->ts;
+    else if (!s->bits) STCHK(make_tiles(p, tile_rows, nullptr, s->geo.seg_major != 0, s->es));
     s->geo.n_tiles = s->ts.n_tiles;
     s->egeo = make_geom(1, s->R, shape.waves);
     s->egeo.n_tiles = s->es.n_tiles;
     const size_t R = (size_t)s->R;
     HIPCHK(dalloc(&s->epart, (size_t)s->ts.n_tiles * s->NE * R));
     HIPCHK(dalloc(&s->etmp, (size_t)s->ts.n_chunks * s->NE * R));
-    HIPCHK(dalloc(&s->vpart, (size_t)s->es.n_tiles * R));
-    HIPCHK(dalloc(&s->vtmp, (size_t)s->es.n_chunks * R));
+    if (!s->bits) {
+        HIPCHK(dalloc(&s->vpart, (size_t)s->es.n_tiles * R));
+        HIPCHK(dalloc(&s->vtmp, (size_t)s->es.n_chunks * R));
+    }
     if (s->kind == KIND_BMINCUT) {
         HIPCHK(dalloc(&s->cpart, (size_t)s->ts.n_tiles * R * s->q));
         HIPCHK(dalloc(&s->ctmp, (size_t)s->ts.n_chunks * R * s->q));
@@ -731,15 +742,10 @@ static fem_status finish_colsums(fem_solver* s)
     return FEM_OK;
 }
 
-// round the current fields, evaluate, update the anytime bests (all on device)
-static fem_status readout_eval(fem_solver* s, const uint8_t* sigma_in, bool update_best)
+// integer evaluation of the byte configurations sigma into vout (and sout)
+static fem_status eval_bytes(fem_solver* s, const uint8_t* sigma)
 {
-    const Problem& p = *s->prob;
-    if (!sigma_in) {
-        HIPCHK(launch_round(s->kind, s->n, s->R, s->q, s->h, s->srow, s->sigma, s->stream));
-        sigma_in = s->sigma;
-    }
-    HIPCHK(launch_eval(p, s->egeo, s->shape.waves, s->es.tiles, s->R, sigma_in, s->vpart, s->spart, s->stream));
+    HIPCHK(launch_eval(*s->prob, s->egeo, s->shape.waves, s->es.tiles, s->R, sigma, s->vpart, s->spart, s->stream));
     HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->es.chunk_off, s->es.n_chunks, s->es.inst_chunk_off, s->n_inst,
                                      s->vtmp, s->vout, s->stream));
     if (s->kind == KIND_BMINCUT) {
@@ -747,6 +753,22 @@ static fem_status readout_eval(fem_solver* s, const uint8_t* sigma_in, bool upda
                                       s->n_inst, s->stmp, s->sint, s->stream));
         HIPCHK(launch_sizes_widen((size_t)s->n_inst * s->R * s->q, s->sint, s->sout, s->stream));
     }
+    return FEM_OK;
+}
+
+// round the current fields, evaluate, update the anytime bests (all on device)
+static fem_status readout_eval(fem_solver* s, bool update_best)
+{
+    const Problem& p = *s->prob;
+    if (s->bits) {
+        const size_t IR = (size_t)s->n_inst * s->R;
+        HIPCHK(launch_pack_bits(s->n, s->R, s->h, s->srow, s->bits, s->count, IR, s->stream));
+        HIPCHK(launch_eval_bits(p, s->R, s->bs.tiles, s->bs.n_tiles, s->bits, s->count, s->stream));
+        HIPCHK(launch_count_finish(s->kind, IR, s->count, s->vout, update_best ? s->best : nullptr, s->stream));
+        return FEM_OK;
+    }
+    HIPCHK(launch_round(s->kind, s->n, s->R, s->q, s->h, s->srow, s->sigma, s->stream));
+    STCHK(eval_bytes(s, s->sigma));
     if (update_best)
         HIPCHK(launch_best_update(s->kind, s->R, s->n_inst, s->q, s->prm.lambda, s->vout, s->sout, p.v2, s->best,
                                   s->stream));
@@ -846,7 +868,7 @@ static fem_status do_steps(fem_solver* s, int t_end)
             if (!s->res.all) STCHK(tiled_step(s));
             if (energy_due(s, s->t)) s->last_energy_step = s->t;
         }
-        if (eval_due(s, s->t)) STCHK(readout_eval(s, nullptr, true));
+        if (eval_due(s, s->t)) STCHK(readout_eval(s, true));
     }
     return FEM_OK;
 }
@@ -904,6 +926,9 @@ static void destroy_solver(fem_solver* s)
     dfree(s->sint);
     dfree(s->sout);
     dfree(s->best);
+    dfree(s->bits);
+    dfree(s->pick);
+    dfree(s->bs.tiles);
     fem_problem* owner = s->owner;
     delete s;
     problem_unref(owner);
@@ -1379,6 +1404,13 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     ALLOC(s->sigma, (size_t)s->n * s->R);
     ALLOC(s->vout, IR);
     ALLOC(s->best, IR);
+    if (!evaluation) {
+        ALLOC(s->pick, (size_t)s->n_inst * 12 + (size_t)s->n);
+        if (bit_evaluation(p)) {
+            ALLOC(s->bits, (size_t)s->n * bit_words(s->R) + IR);
+            s->count = reinterpret_cast<int32_t*>(s->bits + (size_t)s->n * bit_words(s->R));
+        }
+    }
     if (s->kind == KIND_BMINCUT) {
         ALLOC(s->cfix, IR * s->q);
         ALLOC(s->csum, IR * s->q);
@@ -1405,6 +1437,10 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     }
     fem_status st = setup_tiling(s, sh);
     if (st != FEM_OK) return bail(st);
+    if (s->bits) {
+        st = make_tiles(p, bit_tile_rows(s->n, s->R), nullptr, false, s->bs);
+        if (st != FEM_OK) return bail(st);
+    }
     st = reset_best(s);
     if (st != FEM_OK) return bail(st);
     *out = s;
@@ -1703,7 +1739,7 @@ fem_status fem_eval_int(const fem_problem* fp, int32_t R, const int32_t* sigma, 
         dfree(d_sig);
         return done(fail(FEM_E_HIP, "sigma upload: %s", hipGetErrorString(e)));
     }
-    fem_status st = readout_eval(s, s->sigma, false);
+    fem_status st = eval_bytes(s, s->sigma);
     std::vector<double> v;
     std::vector<long long> sz;
     if (st == FEM_OK) st = fetch_eval(s, v, sz);
@@ -1720,43 +1756,30 @@ fem_status fem_best(fem_solver* s, int32_t* replica, int64_t* value, int32_t* si
     if (!s || !replica || !value) return fail(FEM_E_INVAL, "NULL argument");
     if (!s->fields_set) return fail(FEM_E_STATE, "no fields set");
     HIPCHK(hipSetDevice(s->prob->device));
-    STCHK(readout_eval(s, nullptr, false));
-    std::vector<double> v;
-    std::vector<long long> sz;
-    STCHK(fetch_eval(s, v, sz));
-    std::vector<uint8_t> sg;
-    if (sigma) {
-        sg.resize((size_t)s->n * s->R);
-        HIPCHK(hipMemcpy(sg.data(), s->sigma, sg.size(), hipMemcpyDeviceToHost));
+    STCHK(readout_eval(s, false));
+    // the best replica of every instance is chosen and its configuration
+    // gathered on the device: the copy back is a byte per node
+    const size_t B = (size_t)s->n_inst;
+    double* d_value = reinterpret_cast<double*>(s->pick);
+    int32_t* d_replica = reinterpret_cast<int32_t*>(s->pick + B * 8);
+    uint8_t* d_config = reinterpret_cast<uint8_t*>(s->pick + B * 12);
+    HIPCHK(launch_pick(s->kind, s->R, s->n_inst, s->q, s->prm.lambda, s->vout, s->sout, s->prob->v2, d_value, d_replica,
+                       s->stream));
+    if (sigma)
+        HIPCHK(launch_config(s->kind, s->n, s->q, s->h, s->srow, s->n_inst, s->prob->inst_off_d, d_replica, d_config,
+                             s->stream));
+    std::vector<char> out(B * 12 + (sigma ? (size_t)s->n : 0));
+    HIPCHK(hipMemcpyAsync(out.data(), s->pick, out.size(), hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    std::memcpy(replica, out.data() + B * 8, B * 4);
+    for (size_t b = 0; b < B; ++b) {
+        double v;
+        std::memcpy(&v, out.data() + b * 8, 8);
+        value[b] = value_of(s, v);
     }
-    const double lamf = s->prm.lambda;
-    for (int b = 0; b < s->n_inst; ++b) {
-        int br = 0;
-        double bs = std::numeric_limits<double>::infinity();
-        for (int r = 0; r < s->R; ++r) {
-            const size_t k = (size_t)b * s->R + r;
-            double score;
-            if (s->kind == KIND_MAXCUT) score = -v[k];
-            else if (s->kind == KIND_MAXSAT) score = v[k];
-            else {
-                double pen = -s->prob->inst_v2[(size_t)b];
-                for (int c = 0; c < s->q; ++c) {
-                    const double x = (double)sz[k * s->q + c];
-                    pen += x * x;
-                }
-                score = v[k] + lamf * pen;
-            }
-            if (score < bs) {
-                bs = score;
-                br = r;
-            }
-        }
-        replica[b] = br;
-        value[b] = value_of(s, v[(size_t)b * s->R + br]);
-        if (sigma) {
-            const int32_t i0 = s->prob->inst_off[(size_t)b], i1 = s->prob->inst_off[(size_t)b + 1];
-            for (int32_t i = i0; i < i1; ++i) sigma[i] = sg[(size_t)i * s->R + br];
-        }
+    if (sigma) {
+        const uint8_t* c = reinterpret_cast<const uint8_t*>(out.data() + B * 12);
+        for (int32_t i = 0; i < s->n; ++i) sigma[i] = c[i];
     }
     return FEM_OK;
 }
