@@ -27,6 +27,7 @@
 // reduction).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -82,12 +83,6 @@ __device__ __forceinline__ U4 philox(uint32_t c0, uint32_t c1, uint32_t c2, uint
 }
 
 __device__ __forceinline__ float upm1(uint32_t w) { return (float)(w >> 8) * 0x1p-23f - 1.0f; }
-
-// value of x in lane k of the wave (k a compile-time constant after unrolling)
-__device__ __forceinline__ float lane_val(float x, int k)
-{
-    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), k));
-}
 
 // ------------------------------------------------------------- forward ----
 // features of node i from the replica's fields state[i * stride]
@@ -186,21 +181,25 @@ __global__ void __launch_bounds__(256) layer1_kernel(int32_t n, const int64_t* _
 }
 
 // Layer 2 on the matrix cores, sixteen nodes per wave at a time.
-// Gather: lane l = 16 g + i takes node i0 + i and hidden units 16 g .. 16 g +
-// 15 of its own and its neighbours' layer-1 pre-activation rows (four float4
-// of a 256-byte row, ReLU applied on load, two neighbours in flight); every
-// a(H1) sum runs in CSR order, as in a single-node evaluation.
+// Gather: lane l = 16 g + i takes node i0 + i and the hidden units 16 c + 4 g ..
+// + 3 (c = 0..3) of its own and its neighbours' layer-1 pre-activation rows
+// (four float4 of a 256-byte row, ReLU applied on load, two neighbours in
+// flight): the four lanes of a node read 64 contiguous bytes at a time (with
+// units 16 g .. 16 g + 15 per lane they read 16 bytes of four segments, and
+// the kernel took 97 instead of 77 us on 135 k nodes of mean degree 6.5);
+// every a(H1) sum runs in CSR order, as in a single-node evaluation.
 // Dense: pre2 for the 16 nodes is four 16 x 16 output tiles (16 units each),
 // each 32 steps of v_mfma_f32_16x16x4_f32 (A: nodes x 4 inputs, B: 4 inputs x
-// units).  Step s of the H1 half takes the inputs 16 g' + s (g' = 0..3), so a
-// lane supplies its own s-th gathered value as its A element and nothing is
-// staged; the a(H1) half follows.  [A2; B2] (128 x 64, float) sits in LDS
-// with rows padded to W2_LD = 65 floats, which puts the four input rows of a
-// step in distinct banks.  Output element (node 4 g + v, unit 16 t + i) is
-// register v of lane l in tile t.  Each output depends on its own node's
-// inputs only, in a fixed order.
+// units).  Step s = 4 c + u of the H1 half takes the inputs unit_of(g', s) (g'
+// = 0..3), so a lane supplies its own s-th gathered value as its A element and
+// nothing is staged; the a(H1) half follows.  [A2; B2] (128 x 64, float) sits
+// in LDS with rows padded to W2_LD = 68 floats, which puts the four input rows
+// of a step, four apart, in distinct banks.  Output element (node 4 g + v,
+// unit 16 t + i) is register v of lane l in tile t.  Each output depends on
+// its own node's inputs only, in a fixed order.
 constexpr int L2_NB = 16;
-constexpr int W2_LD = 65;
+constexpr int W2_LD = 68;
+__device__ __forceinline__ int unit_of(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) layer2_kernel(int32_t n, const int64_t* __restrict__ row_off,
                                                      const int2* __restrict__ adj, const float* __restrict__ inv_deg,
                                                      const uint16_t* __restrict__ w, const float* __restrict__ pre1,
@@ -235,23 +234,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             ag[u] = 0.0f;
         }
         if (i < n) {
-            const float4* hp = reinterpret_cast<const float4*>(pre1 + (size_t)i * HID + 16 * g);
+            const float4* hp = reinterpret_cast<const float4*>(pre1 + (size_t)i * HID) + g;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const float4 v = hp[c];
+                const float4 v = hp[4 * c];
                 hs[4 * c] = relu(v.x); hs[4 * c + 1] = relu(v.y); hs[4 * c + 2] = relu(v.z); hs[4 * c + 3] = relu(v.w);
             }
             int64_t k = row_off[i];
             const int64_t kend = row_off[i + 1];
             for (; k + 2 <= kend; k += 2) {
                 const int2 e0 = adj[k], e1 = adj[k + 1];
-                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID + 16 * g);
-                const float4* p1 = reinterpret_cast<const float4*>(pre1 + (size_t)e1.x * HID + 16 * g);
+                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID) + g;
+                const float4* p1 = reinterpret_cast<const float4*>(pre1 + (size_t)e1.x * HID) + g;
                 float4 v0[4], v1[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    v0[c] = p0[c];
-                    v1[c] = p1[c];
+                    v0[c] = p0[4 * c];
+                    v1[c] = p1[4 * c];
                 }
                 const float w0 = __int_as_float(e0.y), w1 = __int_as_float(e1.y);
 #pragma unroll
@@ -268,11 +267,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             }
             if (k < kend) {
                 const int2 e0 = adj[k];
-                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID + 16 * g);
+                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID) + g;
                 const float w0 = __int_as_float(e0.y);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float4 v = p0[c];
+                    const float4 v = p0[4 * c];
                     ag[4 * c] = fmaf(w0, relu(v.x), ag[4 * c]);
                     ag[4 * c + 1] = fmaf(w0, relu(v.y), ag[4 * c + 1]);
                     ag[4 * c + 2] = fmaf(w0, relu(v.z), ag[4 * c + 2]);
@@ -283,9 +282,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
 #pragma unroll
             for (int u = 0; u < 16; ++u) ag[u] *= id;
             if (a2out) {
-                float4* ap = reinterpret_cast<float4*>(a2out + (size_t)i * HID + 16 * g);
+                float4* ap = reinterpret_cast<float4*>(a2out + (size_t)i * HID) + g;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) ap[c] = make_float4(ag[4 * c], ag[4 * c + 1], ag[4 * c + 2], ag[4 * c + 3]);
+                for (int c = 0; c < 4; ++c) ap[4 * c] = make_float4(ag[4 * c], ag[4 * c + 1], ag[4 * c + 2], ag[4 * c + 3]);
             }
         }
         // dense part, the whole wave
@@ -299,7 +298,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[s], sW[(16 * g + s) * W2_LD + 16 * t + li], acc[t],
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[s], sW[unit_of(g, s) * W2_LD + 16 * t + li], acc[t],
                                                               0, 0, 0);
         }
 #pragma unroll
@@ -308,7 +307,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                    ag[s], sW[(HID + 16 * g + s) * W2_LD + 16 * t + li], acc[t], 0, 0, 0);
+                    ag[s], sW[(HID + unit_of(g, s)) * W2_LD + 16 * t + li], acc[t], 0, 0, 0);
         }
         // z = relu(pre2) . c + d: per lane over its 4 tiles, then over the 16
         // lanes of its row group (fixed butterfly)
@@ -748,200 +747,288 @@ inf_layer2_kernel(int32_t n, int32_t R, const int64_t* __restrict__ row_off, con
 // ------------------------------------------------------------ training ----
 __device__ __forceinline__ float softplusf(float x) { return fmaxf(x, 0.0f) + log1pf(expf(-fabsf(x))); }
 
-// per instance: L = mean softplus(z) - y z
-__global__ void __launch_bounds__(256) loss_kernel(const int32_t* __restrict__ inst_off, const float* __restrict__ z,
-                                                   const int32_t* __restrict__ y, double* __restrict__ L)
+// per instance (one workgroup): L = mean softplus(z) - y z, and
+// dz_i = (sigmoid(z_i) - y_i) / (N_b B)
+__global__ void __launch_bounds__(1024) loss_kernel(const int32_t* __restrict__ inst_off, int32_t B,
+                                                    const float* __restrict__ z, const int32_t* __restrict__ y,
+                                                    float* __restrict__ dz, double* __restrict__ L)
 {
-    __shared__ double s0[256];
+    __shared__ double s0[1024];
     const int b = blockIdx.x;
     const int i0 = inst_off[b], i1 = inst_off[b + 1];
+    const float nb = (float)(i1 - i0);
     double a0 = 0.0;
-    for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) a0 += (double)(softplusf(z[i]) - (float)y[i] * z[i]);
+    for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+        const float zi = z[i], yi = (float)y[i];
+        a0 += (double)(softplusf(zi) - yi * zi);
+        const float sg = 1.0f / (1.0f + expf(-zi));
+        dz[i] = (sg - yi) / (nb * (float)B);
+    }
     s0[threadIdx.x] = a0;
     __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
+    for (int s = 512; s > 0; s >>= 1) {
         if ((int)threadIdx.x < s) s0[threadIdx.x] += s0[threadIdx.x + s];
         __syncthreads();
     }
     if (threadIdx.x == 0) L[b] = s0[0] / (double)(i1 > i0 ? i1 - i0 : 1);
 }
 
-// dz_i = (sigmoid(z_i) - y_i) / (N_b * B)
-__global__ void dz_kernel(int32_t n, const int32_t* __restrict__ inst_of, const int32_t* __restrict__ inst_off,
-                          int32_t B, const float* __restrict__ z, const int32_t* __restrict__ y,
-                          float* __restrict__ dz)
-{
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
-        const int b = inst_of[i];
-        const float sg = 1.0f / (1.0f + expf(-z[i]));
-        const float nb = (float)(inst_off[b + 1] - inst_off[b]);
-        dz[i] = (sg - (float)y[i]) / (nb * (float)B);
-    }
-}
-
-// dpre2 = dz c [pre2 > 0]; dH1 (own term) = dpre2 A2^T; da2s = (dpre2 B2^T) / max(deg, 1)
+// dpre2 = dz c [pre2 > 0] (formed where it is needed, not stored);
+// dH1 (own term) = dpre2 A2^T, da2s = (dpre2 B2^T) / max(deg, 1), on the matrix
+// cores as layer 2 (same lane layout, the transposed weights in LDS).  Bound
+// by its three 256-byte rows per node: 135 k nodes take 42 us (2.5 TB/s);
+// with a broadcast and two multiply-adds per (unit, unit) it took 114 us.
 __global__ void __launch_bounds__(256) back2_kernel(int32_t n, const float* __restrict__ inv_deg,
                                                     const uint16_t* __restrict__ w, const float* __restrict__ dz,
-                                                    const float* __restrict__ pre2, float* __restrict__ dpre2,
-                                                    float* __restrict__ dh1s, float* __restrict__ da2s)
+                                                    const float* __restrict__ pre2, float* __restrict__ dh1s,
+                                                    float* __restrict__ da2s)
 {
-    __shared__ float sA[HID * (HID + 1)], sB[HID * (HID + 1)];   // padded rows: conflict-free row reads
+    __shared__ float sW[2 * HID * W2_LD];   // row j < 64: A2[:][j], row 64 + j: B2[:][j]
     for (int t = threadIdx.x; t < HID * HID; t += blockDim.x) {
         const int k = t / HID, j = t % HID;
-        sA[k * (HID + 1) + j] = bf(w[OFF_A2 + t]);
-        sB[k * (HID + 1) + j] = bf(w[OFF_B2 + t]);
+        sW[j * W2_LD + k] = bf(w[OFF_A2 + t]);
+        sW[(HID + j) * W2_LD + k] = bf(w[OFF_B2 + t]);
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63;
+    const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int nw = (gridDim.x * blockDim.x) >> 6;
-    const float cl = bf(w[OFF_c + lane]);
-    for (int i = wave; i < n; i += nw) {
-        const float p2 = pre2[(size_t)i * HID + lane];
-        const float dp = p2 > 0.0f ? dz[i] * cl : 0.0f;
-        float ha = 0.0f, hb = 0.0f;
+    float cl[16];
 #pragma unroll
-        for (int j = 0; j < HID; ++j) {
-            const float v = lane_val(dp, j);
-            ha = fmaf(sA[lane * (HID + 1) + j], v, ha);
-            hb = fmaf(sB[lane * (HID + 1) + j], v, hb);
+    for (int s = 0; s < 16; ++s) cl[s] = bf(w[OFF_c + unit_of(g, s)]);
+    for (int i0 = wave * L2_NB; i0 < n; i0 += nw * L2_NB) {
+        const int i = i0 + li;
+        float dp[16];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) dp[s] = 0.0f;
+        if (i < n) {
+            const float dzi = dz[i];
+            const float4* pp = reinterpret_cast<const float4*>(pre2 + (size_t)i * HID) + g;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float4 v = pp[4 * c];
+                dp[4 * c] = v.x > 0.0f ? dzi * cl[4 * c] : 0.0f;
+                dp[4 * c + 1] = v.y > 0.0f ? dzi * cl[4 * c + 1] : 0.0f;
+                dp[4 * c + 2] = v.z > 0.0f ? dzi * cl[4 * c + 2] : 0.0f;
+                dp[4 * c + 3] = v.w > 0.0f ? dzi * cl[4 * c + 3] : 0.0f;
+            }
         }
-        dpre2[(size_t)i * HID + lane] = dp;
-        dh1s[(size_t)i * HID + lane] = ha;
-        da2s[(size_t)i * HID + lane] = hb * inv_deg[i];
+        v4f ha[4], hb[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) ha[t] = hb[t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int s = 0; s < 16; ++s) {
+            __builtin_amdgcn_sched_barrier(0);   // one step's weight loads at a time
+            const int row = unit_of(g, s) * W2_LD + li;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                ha[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dp[s], sW[row + 16 * t], ha[t], 0, 0, 0);
+                hb[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(dp[s], sW[HID * W2_LD + row + 16 * t], hb[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int node = i0 + 4 * g + v;
+            if (node < n) {
+                const float id = inv_deg[node];
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    dh1s[(size_t)node * HID + 16 * t + li] = ha[t][v];
+                    da2s[(size_t)node * HID + 16 * t + li] = hb[t][v] * id;
+                }
+            }
+        }
     }
 }
 
-// dpre1_j = [pre1_j > 0] (dH1s_j + sum_{i in N(j)} W_ij da2s_i)
+// dpre1_j = [pre1_j > 0] (dH1s_j + sum_{i in N(j)} W_ij da2s_i): four nodes per
+// wave, sixteen lanes and one float4 each per row, so that a load brings four
+// neighbour rows.
 __global__ void __launch_bounds__(256) back1_kernel(int32_t n, const int64_t* __restrict__ row_off,
                                                     const int2* __restrict__ adj, const float* __restrict__ pre1,
                                                     const float* __restrict__ dh1s, const float* __restrict__ da2s,
                                                     float* __restrict__ dpre1)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int nw = (gridDim.x * blockDim.x) >> 6;
-    for (int j = wave; j < n; j += nw) {
-        float g = dh1s[(size_t)j * HID + lane];
+    const int li = threadIdx.x & 15;
+    const int team = (blockIdx.x * blockDim.x + threadIdx.x) >> 4, teams = (gridDim.x * blockDim.x) >> 4;
+    const float4* own = reinterpret_cast<const float4*>(dh1s) + li;
+    const float4* rows = reinterpret_cast<const float4*>(da2s) + li;
+    const float4* act = reinterpret_cast<const float4*>(pre1) + li;
+    float4* out = reinterpret_cast<float4*>(dpre1) + li;
+    for (int j = team; j < n; j += teams) {
+        const size_t at = (size_t)j * (HID / 4);
+        float4 g = own[at];
+        const float4 p = act[at];
+        auto add = [&](const int2& e, const float4& v) {
+            const float wij = __int_as_float(e.y);
+            g.x = fmaf(wij, v.x, g.x);
+            g.y = fmaf(wij, v.y, g.y);
+            g.z = fmaf(wij, v.z, g.z);
+            g.w = fmaf(wij, v.w, g.w);
+        };
         int64_t k = row_off[j];
         const int64_t kend = row_off[j + 1];
         for (; k + 4 <= kend; k += 4) {
-            const int2 e0 = adj[k], e1 = adj[k + 1], e2 = adj[k + 2], e3 = adj[k + 3];
-            const float v0 = da2s[(size_t)e0.x * HID + lane], v1 = da2s[(size_t)e1.x * HID + lane];
-            const float v2 = da2s[(size_t)e2.x * HID + lane], v3 = da2s[(size_t)e3.x * HID + lane];
-            g = fmaf(__int_as_float(e0.y), v0, g);
-            g = fmaf(__int_as_float(e1.y), v1, g);
-            g = fmaf(__int_as_float(e2.y), v2, g);
-            g = fmaf(__int_as_float(e3.y), v3, g);
+            int2 e[4];
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = adj[k + u];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = rows[(size_t)e[u].x * (HID / 4)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add(e[u], v[u]);
         }
         for (; k < kend; ++k) {
             const int2 e = adj[k];
-            g = fmaf(__int_as_float(e.y), da2s[(size_t)e.x * HID + lane], g);
+            add(e, rows[(size_t)e.x * (HID / 4)]);
         }
-        dpre1[(size_t)j * HID + lane] = pre1[(size_t)j * HID + lane] > 0.0f ? g : 0.0f;
+        out[at] = make_float4(p.x > 0.0f ? g.x : 0.0f, p.y > 0.0f ? g.y : 0.0f, p.z > 0.0f ? g.z : 0.0f,
+                              p.w > 0.0f ? g.w : 0.0f);
     }
 }
 
-// Weight gradients as sums of outer products over the rows; workgroup b owns
-// the contiguous row range [b*n/G, (b+1)*n/G) and writes one partial vector.
+// Weight gradients as sums of outer products over the rows, on the matrix
+// cores: [H1 | a(H1)]^T dpre2 is 4 x 4 tiles of 16 x 16 for either half and
+// [x | a(x)]^T dpre1 four tiles, four rows per v_mfma_f32_16x16x4_f32.  Lane
+// 16 g + i holds, of row 4 s + g, the units 4 i .. 4 i + 3 of every array (one
+// float4 each, a wave reads four whole rows per load), so tile (a, b) pairs
+// the units 4 m + a with 4 c + b.  Wave v of the launch owns the contiguous
+// rows [v n / V, (v + 1) n / V); a workgroup adds its four waves in order and
+// writes one partial vector.  Bound by its four 256-byte rows per node: 135 k
+// nodes take 54 us (2.6 TB/s), 128 us with one multiply-add per lane and
+// product out of LDS.
 struct WgradArgs {
     int32_t n;
-    const float *X, *A1agg, *pre1, *a2, *pre2, *dz, *dpre2, *dpre1;
+    const float *X, *A1agg, *pre1, *a2, *pre2, *dz, *dpre1;
+    const uint16_t* w;
     float* part;   // [G][NP]
 };
 
-__global__ void __launch_bounds__(256) wgrad_kernel(WgradArgs a)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) wgrad_kernel(WgradArgs a)
 {
-    constexpr int RB = 16;   // rows staged per round
-    __shared__ float sH1[RB][HID], sA2[RB][HID], sD2[RB][HID], sD1[RB][HID], sH2[RB][HID];
-    __shared__ float sX[RB][D_IN], sA1[RB][D_IN], sdz[RB];
-    const int t = threadIdx.x;
-    const int G = gridDim.x;
-    const int64_t r0 = (int64_t)a.n * blockIdx.x / G, r1 = (int64_t)a.n * (blockIdx.x + 1) / G;
-    float gA2[16], gB2[16], gA1[2], gB1[2];
+    __shared__ float sum[NP];
+    const int lane = threadIdx.x & 63, g = lane >> 4, li = lane & 15;
+    const int wl = threadIdx.x >> 6;
+    const int64_t V = (int64_t)gridDim.x * 4, wave = (int64_t)blockIdx.x * 4 + wl;
+    const int64_t r0 = a.n * wave / V, r1 = a.n * (wave + 1) / V;
+    v4f gA[4][4], gB[4][4], gX[4];
+    float gb2[4], gc[4], cl[4], gd = 0.0f;
 #pragma unroll
-    for (int k = 0; k < 16; ++k) gA2[k] = gB2[k] = 0.0f;
-    gA1[0] = gA1[1] = gB1[0] = gB1[1] = 0.0f;
-    float gb2 = 0.0f, gc = 0.0f, gb1 = 0.0f, gd = 0.0f;
-    for (int64_t base = r0; base < r1; base += RB) {
-        const int nr = (int)((r1 - base) < RB ? (r1 - base) : RB);
-        for (int e = t; e < RB * HID; e += blockDim.x) {
-            const int rr = e / HID, c = e % HID;
-            if (rr < nr) {
-                const size_t k = (size_t)(base + rr) * HID + c;
-                sH1[rr][c] = fmaxf(a.pre1[k], 0.0f);
-                sA2[rr][c] = a.a2[k];
-                sD2[rr][c] = a.dpre2[k];
-                sD1[rr][c] = a.dpre1[k];
-                sH2[rr][c] = fmaxf(a.pre2[k], 0.0f);
-            }
+    for (int u = 0; u < 4; ++u) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) gA[u][v] = gB[u][v] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        gX[u] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+        gb2[u] = gc[u] = 0.0f;
+        cl[u] = bf(a.w[OFF_c + 4 * li + u]);
+    }
+    struct Rows {
+        float4 p1, a2, p2, d1;
+        float x, dz;
+    };
+    auto load = [&](int64_t r) {   // row r + g; zeros past the range contribute nothing
+        Rows q{};
+        if (r + g < r1) {
+            const size_t at = (size_t)(r + g) * (HID / 4) + li;
+            q.p1 = reinterpret_cast<const float4*>(a.pre1)[at];
+            q.a2 = reinterpret_cast<const float4*>(a.a2)[at];
+            q.p2 = reinterpret_cast<const float4*>(a.pre2)[at];
+            q.d1 = reinterpret_cast<const float4*>(a.dpre1)[at];
+            q.x = li < D_IN ? a.X[(size_t)(r + g) * D_IN + li] : a.A1agg[(size_t)(r + g) * D_IN + li - D_IN];
+            q.dz = a.dz[r + g];
         }
-        for (int e = t; e < RB * D_IN; e += blockDim.x) {
-            const int rr = e / D_IN, c = e % D_IN;
-            if (rr < nr) {
-                sX[rr][c] = a.X[(size_t)(base + rr) * D_IN + c];
-                sA1[rr][c] = a.A1agg[(size_t)(base + rr) * D_IN + c];
-            }
+        return q;
+    };
+    Rows q = load(r0);
+    for (int64_t r = r0; r < r1; r += 4) {
+        const Rows nx = load(r + 4);   // in flight during this round's products
+        const float h1[4] = {fmaxf(q.p1.x, 0.0f), fmaxf(q.p1.y, 0.0f), fmaxf(q.p1.z, 0.0f), fmaxf(q.p1.w, 0.0f)};
+        const float av[4] = {q.a2.x, q.a2.y, q.a2.z, q.a2.w};
+        const float p2[4] = {q.p2.x, q.p2.y, q.p2.z, q.p2.w};
+        const float d1[4] = {q.d1.x, q.d1.y, q.d1.z, q.d1.w};
+        float dp[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            dp[u] = p2[u] > 0.0f ? q.dz * cl[u] : 0.0f;
+            gb2[u] += dp[u];
+            gc[u] = fmaf(q.dz, fmaxf(p2[u], 0.0f), gc[u]);
         }
-        if (t < RB && t < nr) sdz[t] = a.dz[base + t];
-        __syncthreads();
-        for (int rr = 0; rr < nr; ++rr) {
+        gd += q.dz;
 #pragma unroll
-            for (int q = 0; q < 16; ++q) {
-                const int e = t * 16 + q, k = e / HID, j = e % HID;
-                gA2[q] = fmaf(sH1[rr][k], sD2[rr][j], gA2[q]);
-                gB2[q] = fmaf(sA2[rr][k], sD2[rr][j], gB2[q]);
-            }
+        for (int u = 0; u < 4; ++u) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int e = t * 2 + q, k = e / HID, j = e % HID;
-                gA1[q] = fmaf(sX[rr][k], sD1[rr][j], gA1[q]);
-                gB1[q] = fmaf(sA1[rr][k], sD1[rr][j], gB1[q]);
+            for (int v = 0; v < 4; ++v) {
+                gA[u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(h1[u], dp[v], gA[u][v], 0, 0, 0);
+                gB[u][v] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[u], dp[v], gB[u][v], 0, 0, 0);
             }
-            if (t < HID) {
-                gb2 += sD2[rr][t];
-                gc = fmaf(sdz[rr], sH2[rr][t], gc);
-                gb1 += sD1[rr][t];
+            gX[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(q.x, d1[u], gX[u], 0, 0, 0);
+        }
+        q = nx;
+    }
+    // the four row groups of the vectors, in a fixed butterfly
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        gb2[u] += __shfl_xor(gb2[u], 16, 64);
+        gb2[u] += __shfl_xor(gb2[u], 32, 64);
+        gc[u] += __shfl_xor(gc[u], 16, 64);
+        gc[u] += __shfl_xor(gc[u], 32, 64);
+    }
+    gd += __shfl_xor(gd, 16, 64);
+    gd += __shfl_xor(gd, 32, 64);
+    for (int turn = 0; turn < 4; ++turn) {
+        if (wl == turn) {
+            auto put = [&](int at, float x) { sum[at] = turn ? sum[at] + x : x; };
+            // tile register v of lane 16 g + i: row index 4 g + v, column i
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int m = 4 * g + v;
+#pragma unroll
+                for (int ub = 0; ub < 4; ++ub) {
+                    const int j = 4 * li + ub;
+#pragma unroll
+                    for (int ua = 0; ua < 4; ++ua) {
+                        put(OFF_A2 + (4 * m + ua) * HID + j, gA[ua][ub][v]);
+                        put(OFF_B2 + (4 * m + ua) * HID + j, gB[ua][ub][v]);
+                    }
+                    put((m < D_IN ? OFF_A1 + m * HID : OFF_B1 + (m - D_IN) * HID) + j, gX[ub][v]);
+                    if (m == 0) put(OFF_b1 + j, gX[ub][v]);   // input 0 is the constant 1
+                }
             }
-            if (t == 0) gd += sdz[rr];
+            if (g == 0) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    put(OFF_b2 + 4 * li + u, gb2[u]);
+                    put(OFF_c + 4 * li + u, gc[u]);
+                }
+            }
+            if (lane == 0) put(OFF_d, gd);
         }
         __syncthreads();
     }
     float* p = a.part + (size_t)blockIdx.x * NP;
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        p[OFF_A2 + t * 16 + q] = gA2[q];
-        p[OFF_B2 + t * 16 + q] = gB2[q];
-    }
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        p[OFF_A1 + t * 2 + q] = gA1[q];
-        p[OFF_B1 + t * 2 + q] = gB1[q];
-    }
-    if (t < HID) {
-        p[OFF_b2 + t] = gb2;
-        p[OFF_c + t] = gc;
-        p[OFF_b1 + t] = gb1;
-    }
-    if (t == 0) p[OFF_d] = gd;
+    for (int k = threadIdx.x; k < NP; k += 256) p[k] = sum[k];
 }
 
-__global__ void wgrad_reduce_kernel(int G, const float* __restrict__ part, float* __restrict__ grad)
+// Sums the partial vectors in double (thread (s, p): partials s, s + 8, ...,
+// then the eight in order), and applies Adam to the master weights: 32
+// parameters per workgroup.  A chain of 512 dependent-latency loads per
+// parameter took 127 us; this takes 8.
+__global__ void __launch_bounds__(256) grad_adam_kernel(int G, const float* __restrict__ part, float* __restrict__ grad,
+                                                        float* __restrict__ theta, float* __restrict__ m1,
+                                                        float* __restrict__ m2, uint16_t* __restrict__ wbf,
+                                                        float step_size, float bc2_sqrt, float b1, float b2, float eps)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NP) return;
+    __shared__ double lds[256];
+    const int p = blockIdx.x * 32 + (threadIdx.x & 31), sub = threadIdx.x >> 5;
     double s = 0.0;
-    for (int b = 0; b < G; ++b) s += (double)part[(size_t)b * NP + p];
-    grad[p] = (float)s;
-}
-
-__global__ void adam_w_kernel(float* __restrict__ theta, float* __restrict__ m1, float* __restrict__ m2,
-                              const float* __restrict__ g, uint16_t* __restrict__ wbf, float step_size,
-                              float bc2_sqrt, float b1, float b2, float eps)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= NP) return;
-    const float gg = g[p];
+    if (p < NP)
+#pragma unroll 16
+        for (int b = sub; b < G; b += 8) s += (double)part[(size_t)b * NP + p];
+    lds[threadIdx.x] = s;
+    __syncthreads();
+    if (sub != 0 || p >= NP) return;
+    for (int k = 1; k < 8; ++k) s += lds[k * 32 + threadIdx.x];
+    const float gg = (float)s;
+    grad[p] = gg;
     const float a = b1 * m1[p] + (1.0f - b1) * gg;
     const float v = b2 * m2[p] + (1.0f - b2) * (gg * gg);
     m1[p] = a;
@@ -951,10 +1038,16 @@ __global__ void adam_w_kernel(float* __restrict__ theta, float* __restrict__ m1,
     wbf[p] = to_bf16(th);
 }
 
-__global__ void round_weights_kernel(const float* __restrict__ theta, uint16_t* __restrict__ wbf)
+// new master weights: their bfloat16 form, and cleared Adam moments
+__global__ void round_weights_kernel(const float* __restrict__ theta, uint16_t* __restrict__ wbf,
+                                     float* __restrict__ m1, float* __restrict__ m2)
 {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < NP) wbf[p] = to_bf16(theta[p]);
+    if (p < NP) {
+        wbf[p] = to_bf16(theta[p]);
+        m1[p] = 0.0f;
+        m2[p] = 0.0f;
+    }
 }
 
 }  // namespace
@@ -989,10 +1082,10 @@ struct fem_mpnn {
     size_t cap = 0;      // rows the work buffers hold
     size_t cap_inst = 0;
     float *X = nullptr, *A1agg = nullptr, *inv_deg = nullptr, *pre1 = nullptr, *a2 = nullptr, *pre2 = nullptr,
-          *z = nullptr, *dz = nullptr, *dpre2 = nullptr, *dh1s = nullptr, *da2s = nullptr, *dpre1 = nullptr;
+          *z = nullptr, *dz = nullptr, *dh1s = nullptr, *da2s = nullptr, *dpre1 = nullptr;
     float* state = nullptr;   // one replica's fields (training input)
-    int32_t *y = nullptr, *inst_of = nullptr, *inst_off = nullptr;
-    double* L = nullptr;
+    int32_t* y = nullptr;
+    double* L = nullptr;      // instance losses, with the gradient behind them
     float* tbuf = nullptr;   // inference: graph and replica inputs with their aggregates
     size_t tcap = 0;         // floats tbuf holds
 };
@@ -1007,8 +1100,9 @@ static void mfree(T*& p)
 static void free_work(fem_mpnn* m)
 {
     mfree(m->X); mfree(m->A1agg); mfree(m->inv_deg); mfree(m->pre1); mfree(m->a2); mfree(m->pre2);
-    mfree(m->z); mfree(m->dz); mfree(m->dpre2); mfree(m->dh1s); mfree(m->da2s); mfree(m->dpre1);
-    mfree(m->state); mfree(m->y); mfree(m->inst_of); mfree(m->inst_off); mfree(m->L);
+    mfree(m->z); mfree(m->dz); mfree(m->dh1s); mfree(m->da2s); mfree(m->dpre1);
+    mfree(m->state); mfree(m->y); mfree(m->L);
+    m->grad = nullptr;
     m->cap = 0;
     m->cap_inst = 0;
 }
@@ -1026,15 +1120,13 @@ static fem_status ensure_work(fem_mpnn* m, size_t n, size_t n_inst)
     MCHK(hipMalloc(&m->pre2, c * HID * 4));
     MCHK(hipMalloc(&m->z, c * 4));
     MCHK(hipMalloc(&m->dz, c * 4));
-    MCHK(hipMalloc(&m->dpre2, c * HID * 4));
     MCHK(hipMalloc(&m->dh1s, c * HID * 4));
     MCHK(hipMalloc(&m->da2s, c * HID * 4));
     MCHK(hipMalloc(&m->dpre1, c * HID * 4));
     MCHK(hipMalloc(&m->state, c * 4));
     MCHK(hipMalloc(&m->y, c * 4));
-    MCHK(hipMalloc(&m->inst_of, c * 4));
-    MCHK(hipMalloc(&m->inst_off, (ci + 1) * 4));
-    MCHK(hipMalloc(&m->L, ci * 8));
+    MCHK(hipMalloc(&m->L, ci * 8 + NP * 4));
+    m->grad = reinterpret_cast<float*>(m->L + ci);
     m->cap = n;
     m->cap_inst = n_inst;
     return FEM_OK;
@@ -1086,14 +1178,12 @@ fem_status fem_mpnn_create(int device, const float* theta0, int32_t n_params, fe
     if (e != hipSuccess) return bail(mfail(FEM_E_HIP, "hipSetDevice", e));
     if ((e = hipMalloc(&m->theta, NP * 4)) != hipSuccess || (e = hipMalloc(&m->wbf, NP * 2)) != hipSuccess ||
         (e = hipMalloc(&m->m1, NP * 4)) != hipSuccess || (e = hipMalloc(&m->m2, NP * 4)) != hipSuccess ||
-        (e = hipMalloc(&m->grad, NP * 4)) != hipSuccess ||
         (e = hipMalloc(&m->part, (size_t)WG_BLOCKS * NP * 4)) != hipSuccess)
         return bail(mfail(FEM_E_NOMEM, "device allocation", e));
-    if ((e = hipMemcpy(m->theta, theta0, NP * 4, hipMemcpyHostToDevice)) != hipSuccess ||
-        (e = hipMemset(m->m1, 0, NP * 4)) != hipSuccess || (e = hipMemset(m->m2, 0, NP * 4)) != hipSuccess)
+    if ((e = hipMemcpy(m->theta, theta0, NP * 4, hipMemcpyHostToDevice)) != hipSuccess)
         return bail(mfail(FEM_E_HIP, "upload of the parameters", e));
     (void)hipGetLastError();
-    round_weights_kernel<<<(NP + 255) / 256, 256>>>(m->theta, m->wbf);
+    round_weights_kernel<<<(NP + 255) / 256, 256>>>(m->theta, m->wbf, m->m1, m->m2);
     if ((e = hipDeviceSynchronize()) != hipSuccess) return bail(mfail(FEM_E_HIP, "round_weights_kernel", e));
     *out = m;
     return FEM_OK;
@@ -1105,7 +1195,7 @@ void fem_mpnn_destroy(fem_mpnn* m)
     (void)hipSetDevice(m->device);
     free_work(m);
     mfree(m->tbuf);
-    mfree(m->theta); mfree(m->wbf); mfree(m->m1); mfree(m->m2); mfree(m->grad); mfree(m->part);
+    mfree(m->theta); mfree(m->wbf); mfree(m->m1); mfree(m->m2); mfree(m->part);
     delete m;
 }
 
@@ -1122,11 +1212,9 @@ fem_status fem_mpnn_set_params(fem_mpnn* m, const float* theta)
     if (!m || !theta) return mfail(FEM_E_INVAL, "NULL argument");
     MCHK(hipSetDevice(m->device));
     MCHK(hipMemcpy(m->theta, theta, NP * 4, hipMemcpyHostToDevice));
-    MCHK(hipMemset(m->m1, 0, NP * 4));
-    MCHK(hipMemset(m->m2, 0, NP * 4));
     m->adam_t = 0;
     (void)hipGetLastError();
-    round_weights_kernel<<<(NP + 255) / 256, 256>>>(m->theta, m->wbf);
+    round_weights_kernel<<<(NP + 255) / 256, 256>>>(m->theta, m->wbf, m->m1, m->m2);
     MCHK(hipDeviceSynchronize());
     return FEM_OK;
 }
@@ -1159,48 +1247,51 @@ fem_status fem_mpnn_train_step(fem_mpnn* m, const fem_problem* fp, const float* 
     const Problem& p = fp->p;
     if (p.kind != KIND_MAXCUT) return mfail(FEM_E_UNSUPPORTED, "the warm-start network is for MaxCut problems");
     if (!(lr > 0.0) || draw0 < 0) return mfail(FEM_E_INVAL, "need lr > 0 and draw0 >= 0");
-    for (int32_t i = 0; i < p.n; ++i)
-        if (labels[i] != 0 && labels[i] != 1) return mfail(FEM_E_INVAL, "labels must be 0 or 1");
+    int32_t other = 0;   // bits that a label of 0 or 1 does not have
+    for (int32_t i = 0; i < p.n; ++i) other |= labels[i] & ~1;
+    if (other) return mfail(FEM_E_INVAL, "labels must be 0 or 1");
     MCHK(hipSetDevice(m->device));
     const int32_t n = p.n, B = p.n_inst;
     fem_status s = ensure_work(m, (size_t)n, (size_t)B);
     if (s != FEM_OK) return s;
-    std::vector<int32_t> inst_of((size_t)n);
-    for (int32_t b = 0; b < B; ++b)
-        for (int32_t i = p.inst_off[(size_t)b]; i < p.inst_off[(size_t)b + 1]; ++i) inst_of[(size_t)i] = b;
     MCHK(hipMemcpy(m->state, state, (size_t)n * 4, hipMemcpyHostToDevice));
     MCHK(hipMemcpy(m->y, labels, (size_t)n * 4, hipMemcpyHostToDevice));
-    MCHK(hipMemcpy(m->inst_of, inst_of.data(), (size_t)n * 4, hipMemcpyHostToDevice));
-    MCHK(hipMemcpy(m->inst_off, p.inst_off.data(), (size_t)(B + 1) * 4, hipMemcpyHostToDevice));
     // one forward over the union: the random features are keyed by the node's
     // index in the batch and the draw
     s = forward(m, p, m->state, 1, seed, draw0, true, nullptr);
     if (s != FEM_OK) return s;
     (void)hipGetLastError();
-    loss_kernel<<<B, 256>>>(m->inst_off, m->z, m->y, m->L);
-    dz_kernel<<<(n + 255) / 256, 256>>>(n, m->inst_of, m->inst_off, B, m->z, m->y, m->dz);
-    back2_kernel<<<grid_rows(n, 4), 256>>>(n, m->inv_deg, m->wbf, m->dz, m->pre2, m->dpre2, m->dh1s, m->da2s);
-    back1_kernel<<<grid_rows(n, 4), 256>>>(n, p.row_off, p.adj, m->pre1, m->dh1s, m->da2s, m->dpre1);
-    WgradArgs wa{n, m->X, m->A1agg, m->pre1, m->a2, m->pre2, m->dz, m->dpre2, m->dpre1, m->part};
-    wgrad_kernel<<<WG_BLOCKS, 256>>>(wa);
-    wgrad_reduce_kernel<<<(NP + 255) / 256, 256>>>(WG_BLOCKS, m->part, m->grad);
-    MCHK(hipGetLastError());
-    // loss on the host from the per-instance values
-    std::vector<double> L((size_t)B);
-    MCHK(hipMemcpy(L.data(), m->L, L.size() * 8, hipMemcpyDeviceToHost));
-    double tot = 0.0;
-    for (int32_t b = 0; b < B; ++b) tot += L[(size_t)b] / B;
-    if (loss) *loss = tot;
-    if (grad_out) MCHK(hipMemcpy(grad_out, m->grad, NP * 4, hipMemcpyDeviceToHost));
+    loss_kernel<<<B, 1024>>>(p.inst_off_d, B, m->z, m->y, m->dz, m->L);
+    back2_kernel<<<grid_rows((n + L2_NB - 1) / L2_NB, 4), 256>>>(n, m->inv_deg, m->wbf, m->dz, m->pre2, m->dh1s,
+                                                                m->da2s);
+    back1_kernel<<<grid_rows((n + 3) / 4, 4), 256>>>(n, p.row_off, p.adj, m->pre1, m->dh1s, m->da2s, m->dpre1);
+    WgradArgs wa{n, m->X, m->A1agg, m->pre1, m->a2, m->pre2, m->dz, m->dpre1, m->wbf, m->part};
+    // at least sixteen rows a wave: a partial vector costs as much to write
+    // and read as 37 rows
+    const int G = (int)std::min<int64_t>(WG_BLOCKS, ((int64_t)n + 63) / 64);
+    wgrad_kernel<<<G, 256>>>(wa);
     // Adam on the master weights (torch.optim.Adam defaults 0.9 / 0.999 / 1e-8)
-    m->adam_t += 1;
+    const int64_t t = m->adam_t + 1;
     const double b1 = 0.9, b2 = 0.999;
-    const float step = (float)(lr / (1.0 - std::pow(b1, (double)m->adam_t)));
-    const float bc2s = (float)std::sqrt(1.0 - std::pow(b2, (double)m->adam_t));
-    adam_w_kernel<<<(NP + 255) / 256, 256>>>(m->theta, m->m1, m->m2, m->grad, m->wbf, step, bc2s, (float)b1,
-                                             (float)b2, 1e-8f);
+    const float step = (float)(lr / (1.0 - std::pow(b1, (double)t)));
+    const float bc2s = (float)std::sqrt(1.0 - std::pow(b2, (double)t));
+    grad_adam_kernel<<<(NP + 31) / 32, 256>>>(G, m->part, m->grad, m->theta, m->m1, m->m2, m->wbf, step, bc2s, (float)b1,
+                                              (float)b2, 1e-8f);
     MCHK(hipGetLastError());
-    MCHK(hipDeviceSynchronize());
+    m->adam_t = t;
+    // the per-instance losses and the gradient in one copy, which also waits
+    // for the step; the loss is their mean
+    const size_t g0 = (size_t)((char*)m->grad - (char*)m->L);
+    std::vector<char> out(grad_out ? g0 + NP * 4 : (size_t)B * 8);
+    MCHK(hipMemcpy(out.data(), m->L, out.size(), hipMemcpyDeviceToHost));
+    double tot = 0.0;
+    for (int32_t b = 0; b < B; ++b) {
+        double Lb;
+        std::memcpy(&Lb, out.data() + (size_t)b * 8, 8);
+        tot += Lb / B;
+    }
+    if (loss) *loss = tot;
+    if (grad_out) std::memcpy(grad_out, out.data() + g0, NP * 4);
     return FEM_OK;
 }
 
