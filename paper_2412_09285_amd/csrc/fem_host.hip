@@ -399,9 +399,7 @@ struct TileSet {
     int32_t* chunk_off = nullptr;
     int32_t* inst_chunk_off = nullptr;
     int n_tiles = 0, n_chunks = 0;
-    // most tiles of one instance: up to ENERGY_FINISH_TILES the energies are
-    // reduced in one launch, beyond in two stages plus the combination
-    int max_inst_tiles = 0;
+    int max_inst_tiles = 0;   // most tiles of one instance
 };
 
 struct fem_solver {
@@ -440,8 +438,7 @@ struct fem_solver {
     // energies
     int NE = 2;
     double* epart = nullptr;
-    double* etmp = nullptr;
-    double* eraw = nullptr;
+    double* etmp = nullptr;    // its sums per chunk
     double* eout = nullptr;    // last energies [inst][3][R]
     double* ehist = nullptr;   // [records][inst][3][R]
     int n_records = 0;
@@ -450,7 +447,6 @@ struct fem_solver {
     // bMinCut column sums
     long long* cpart = nullptr;
     long long* ctmp = nullptr;
-    long long* cfix = nullptr;
     double* csum = nullptr;
     double* ctil = nullptr;
     // evaluation
@@ -552,10 +548,6 @@ static void drop_graphs(fem_solver* s)
 // tiles an XCD receives form one contiguous row range; with several segments
 // the grid is segment-major (consecutive blocks = segments of one tile; while
 // the tile count fits grid.y) and the tiles keep their natural order.
-// instances of at most this many tiles take the one-launch energy reduction
-// (one workgroup per instance and 32 replicas reads all their partials)
-constexpr int ENERGY_FINISH_TILES = 256;
-
 // The tiles of every instance not marked in skip (null: all instances).
 static fem_status make_tiles(const Problem& p, int tile_rows, const uint8_t* skip, bool seg_major, TileSet& ts)
 {
@@ -731,14 +723,42 @@ static double* energy_slot(fem_solver* s, int t)
     return s->eout;
 }
 
-// bMinCut: C(s), C~(s) of the marginal copy currently in cpart (fixed-point
-// marginal sums, or state counts of the read-out with manipulated gradients)
-static fem_status finish_colsums(fem_solver* s)
+// Instances of more tiles are summed per chunk of 64 first: 400 tiles finish in
+// one launch of 4.8 us, 1500 take 8.4, 6250 take 16.7, against 9.5 in two.
+constexpr int FINISH_TILES = 1024;
+
+// The energies of step t (t >= 0; -1: none) from epart, and for bMinCut C(s)
+// and C~(s) of the marginal copy currently in cpart (fixed-point marginal
+// sums, or state counts of the read-out with manipulated gradients).
+static fem_status finish(fem_solver* s, int t)
 {
-    HIPCHK(launch_seg_reduce<long long>(s->cpart, s->R * s->q, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off,
-                                        s->n_inst, s->ctmp, s->cfix, s->stream));
-    HIPCHK(launch_colsum_combine(s->R, s->q, s->n_inst, s->cfix, s->manip ? 1.0 : 0x1p-40, s->csum, s->ctil,
-                                 s->stream));
+    const bool columns = s->kind == KIND_BMINCUT;
+    if (t < 0 && !columns) return FEM_OK;
+    FinishArgs a{};
+    if (s->ts.max_inst_tiles > FINISH_TILES) {
+        HIPCHK(launch_chunks(s->epart, t >= 0 ? s->NE * s->R : 0, s->cpart, columns ? s->R * s->q : 0, s->ts.chunk_off,
+                             s->ts.n_chunks, s->etmp, s->ctmp, s->stream));
+        a.epart = s->etmp;
+        a.cpart = s->ctmp;
+    } else {
+        a.epart = s->epart;
+        a.cpart = s->cpart;
+        a.chunk_off = s->ts.chunk_off;
+    }
+    a.inst_chunk_off = s->ts.inst_chunk_off;
+    a.wtot = s->d_wtot;
+    a.csum = s->csum;
+    a.ctil = s->ctil;
+    if (t >= 0) {
+        a.eout = energy_slot(s, t);
+        a.lam = s->lam[(size_t)t];
+        a.beta = s->beta[(size_t)t];
+    }
+    a.scale = s->manip ? 1.0 : 0x1p-40;
+    a.kind = s->kind;
+    a.R = s->R;
+    a.q = s->q;
+    HIPCHK(launch_finish(a, s->n_inst, t >= 0, columns, s->stream));
     return FEM_OK;
 }
 
@@ -838,21 +858,7 @@ static fem_status tiled_step(fem_solver* s)
     else
         HIPCHK(launch_step(s->kind, s->dtype, s->shape.vec, s->shape.nt != 0, s->geo, s->shape.waves, a, s->stream));
     if (e1) HIPCHK(hipEventRecord(e1, s->stream));
-    if (en) {
-        double* slot = energy_slot(s, t);
-        if (s->ts.max_inst_tiles <= ENERGY_FINISH_TILES) {
-            HIPCHK(launch_energy_finish(s->kind, s->R, s->q, s->NE, s->n_inst, s->epart, s->ts.chunk_off,
-                                        s->ts.inst_chunk_off, s->d_wtot, s->csum, s->lam[(size_t)t],
-                                        s->beta[(size_t)t], slot, s->stream));
-        } else {
-            HIPCHK(launch_seg_reduce<double>(s->epart, s->NE * s->R, s->ts.chunk_off, s->ts.n_chunks,
-                                             s->ts.inst_chunk_off, s->n_inst, s->etmp, s->eraw, s->stream));
-            HIPCHK(launch_energy_combine(s->kind, s->R, s->q, s->n_inst, s->ts.inst_chunk_off, s->eraw, s->d_wtot, s->csum,
-                                         s->lam[(size_t)t], s->beta[(size_t)t], slot, s->stream));
-        }
-    }
-    if (s->kind == KIND_BMINCUT) STCHK(finish_colsums(s));
-    return FEM_OK;
+    return finish(s, en ? t : -1);
 }
 
 // Enqueues the steps up to t_end: the stretch to the next read-out at a time,
@@ -884,8 +890,7 @@ static fem_status init_marginals(fem_solver* s)
         HIPCHK(launch_dense_i8_init(*s->prob, a, s->stream));
     else
         HIPCHK(launch_init_marginals(s->kind, s->dtype, s->geo, s->shape.waves, a, s->vals, s->stream));
-    if (s->kind == KIND_BMINCUT) STCHK(finish_colsums(s));
-    return FEM_OK;
+    return finish(s, -1);
 }
 
 static fem_status reset_best(fem_solver* s)
@@ -914,11 +919,9 @@ static void destroy_solver(fem_solver* s)
     void* m1v = s->marg[1];
     if (m0) (void)hipFree(m0);
     if (m1v) (void)hipFree(m1v);
-    dfree(s->eraw);
     dfree(s->eout);
     dfree(s->ehist);
     dfree(s->d_wtot);
-    dfree(s->cfix);
     dfree(s->csum);
     dfree(s->ctil);
     dfree(s->sigma);
@@ -1394,7 +1397,6 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         }
         if (e != hipSuccess) return bail(fail(FEM_E_HIP, "clearing the marginal copy: %s", hipGetErrorString(e)));
     }
-    ALLOC(s->eraw, IR * s->NE);
     ALLOC(s->eout, IR * 3);
     if (P.record_energies && P.energy_every > 0) {
         s->n_records = (P.steps + P.energy_every - 1) / P.energy_every;
@@ -1412,7 +1414,6 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         }
     }
     if (s->kind == KIND_BMINCUT) {
-        ALLOC(s->cfix, IR * s->q);
         ALLOC(s->csum, IR * s->q);
         ALLOC(s->ctil, IR * s->q);
         ALLOC(s->sint, IR * s->q);

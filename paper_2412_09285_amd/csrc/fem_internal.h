@@ -199,25 +199,30 @@ template <typename T>
 hipError_t launch_seg_reduce(const T* part, int cols, const int32_t* chunk_off, int n_chunks,
                              const int32_t* inst_chunk_off, int n_inst, T* tmp, T* out,
                              hipStream_t st);
-// the same energies from the per-tile partials in one launch (instances of
-// few tiles): part [tile][NE][R], tiles of instance b from chunk
-// inst_chunk_off[b] to inst_chunk_off[b + 1]
-hipError_t launch_energy_finish(int kind, int R, int q, int NE, int n_inst, const double* part,
-                                const int32_t* chunk_off, const int32_t* inst_chunk_off, const double* wtot,
-                                const double* csum, double lam, double beta, double* eout, hipStream_t st);
-// (an instance without chunks keeps its energies)
-hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const int32_t* inst_chunk_off, const double* raw,
-                                 const double* wtot, const double* csum, double lam, double beta,
-                                 double* eout, hipStream_t st);
+// What follows a step (energies, bMinCut column sums), from the per-tile
+// partials of every instance that has tiles.
+struct FinishArgs {
+    const double* epart;          // [tile or chunk][NE][R]
+    const long long* cpart;       // [tile or chunk][R][q]
+    const int32_t* inst_chunk_off;   // chunks of instance b: [inst_chunk_off[b], inst_chunk_off[b + 1])
+    const int32_t* chunk_off;     // not null: the arrays are per tile, chunk c has [chunk_off[c], chunk_off[c + 1])
+    const double* wtot;
+    double* csum;                 // [inst][R][q]: cpart summed, times scale
+    double* ctil;                 // csum minus its mean over the states
+    double* eout;                 // [inst][3][R]: U, S, F of the step, with the csum before it
+    double lam, beta;
+    double scale;                 // 2^-40 for fixed-point marginal sums, 1 for state counts
+    int32_t kind, R, q;
+};
+// epart and cpart (cols 0: absent) summed per chunk of tiles
+hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart, int ccols, const int32_t* chunk_off,
+                         int n_chunks, double* esum, long long* csum, hipStream_t st);
+hipError_t launch_finish(const FinishArgs& a, int n_inst, bool energies, bool columns, hipStream_t st);
 // manipulated gradients (fem_manip.hip): the step kernel, and the read-out copy
 // of a.h (sign bits or argmax states, with per-tile state counts for bMinCut)
 hipError_t launch_manip_step(int kind, int vec, bool nt, const LaunchGeom& g, int waves, const StepArgs& a,
                              hipStream_t st);
 hipError_t launch_manip_init(int kind, const LaunchGeom& g, int waves, const StepArgs& a, hipStream_t st);
-// csum = fx * scale (2^-40 for fixed-point marginal sums, 1 for state counts),
-// ctil = csum minus its mean over the states
-hipError_t launch_colsum_combine(int R, int q, int n_inst, const long long* fx, double scale, double* csum,
-                                 double* ctil, hipStream_t st);
 hipError_t launch_round(int kind, int32_t n, int32_t R, int32_t q, const float* h, int64_t srow, uint8_t* sigma,
                         hipStream_t st);
 // n rows of w floats: dst[i ds + c] = src[i ss + c] (src not null), and zeros

@@ -671,113 +671,113 @@ static hipError_t seg_reduce2(const T* part, int cols, const int32_t* chunk_off,
     return hipGetLastError();
 }
 
-// Energies straight from the per-tile partials [tile][NE][R], one launch:
-// block (inst, replica group of 32) sums the instance's tiles in 8 strided
-// sub-sums added in fixed order, then forms U, S, F.  For instances of few
-// tiles, where the two-stage reduction and the combination cost three
-// launches for a few thousand values.
-template <int NE>
-__global__ void __launch_bounds__(256) energy_finish_kernel(int kind, int R, int q, const double* __restrict__ part,
-                                                            const int32_t* __restrict__ chunk_off,
-                                                            const int32_t* __restrict__ inst_chunk_off,
-                                                            const double* __restrict__ wtot,
-                                                            const double* __restrict__ csum, double lam,
-                                                            double beta, double* __restrict__ eout)
+// What follows a step: energies from the per-tile partials epart [tile][NE][R],
+// and for bMinCut the column sums of the new marginals from cpart
+// [tile][R][q] (the energies of the step use the sums before it).  One launch
+// (finish_kernel): a workgroup takes one instance and a few replicas
+// (FINISH_COLS columns of either array, or one replica's q states), its
+// threads stride over the instance's tiles, and a fixed tree adds them.
+// Instances of many tiles leave too few workgroups for that: there chunks of
+// up to 64 tiles are summed first (chunk_kernel, both arrays in one launch) and
+// the finish runs over the chunks.  Every launch costs 4.5-5 us with hardly
+// any work in it; one per array, reduction stage and combination cost 14.6 us
+// behind every step of the large problems (now 9.5), 14 us behind a bMinCut
+// step of 4720 nodes (now 4.8) and 27 us behind one of 200 k nodes with
+// energies (now 10).
+constexpr int FINISH_THREADS = 1024, FINISH_COLS = 8;
+
+// Sum over the `rows` threads that hold the same column (thread = row * cols +
+// col), in a fixed tree; every thread of row 0 returns its column's total.
+template <typename T>
+__device__ __forceinline__ T column_tree(T x, T* lds, int cols, int rows)
 {
-    __shared__ double lds[NE][256];
-    const int inst = blockIdx.x;
-    const int r = blockIdx.y * 32 + (threadIdx.x & 31);
-    const int sub = threadIdx.x >> 5;
-    const int t0 = chunk_off[inst_chunk_off[inst]], t1 = chunk_off[inst_chunk_off[inst + 1]];
-    if (t0 == t1) return;   // its energies are not formed from tiles
-    double acc[NE];
-#pragma unroll
-    for (int k = 0; k < NE; ++k) acc[k] = 0.0;
-    if (r < R)
-        for (int t = t0 + sub; t < t1; t += 8)
-#pragma unroll
-            for (int k = 0; k < NE; ++k) acc[k] += part[((size_t)t * NE + k) * R + r];
-#pragma unroll
-    for (int k = 0; k < NE; ++k) lds[k][threadIdx.x] = acc[k];
+    lds[threadIdx.x] = x;
     __syncthreads();
-    if (sub == 0 && r < R) {
-        double x[NE];
+    for (int o = rows >> 1; o > 0; o >>= 1) {
+        if ((int)threadIdx.x < o * cols) lds[threadIdx.x] += lds[threadIdx.x + o * cols];
+        __syncthreads();
+    }
+    x = lds[threadIdx.x];
+    __syncthreads();
+    return x;
+}
+
+template <int NE, bool COL>
+__global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
+{
+    __shared__ double lds[FINISH_THREADS];
+    __shared__ double e_sum[NE > 0 ? NE : 1][FINISH_COLS];
+    __shared__ double c_sum[32 > FINISH_COLS ? 32 : FINISH_COLS];
+    const int tid = threadIdx.x;
+    const int G = COL ? (a.q < FINISH_COLS ? FINISH_COLS / a.q : 1) : FINISH_COLS;   // replicas
+    const int groups = (a.R + G - 1) / G;
+    const int inst = blockIdx.x / groups, r0 = (blockIdx.x % groups) * G;
+    int t0 = a.inst_chunk_off[inst], t1 = a.inst_chunk_off[inst + 1];
+    if (a.chunk_off) {   // tiles, not chunk sums
+        t0 = a.chunk_off[t0];
+        t1 = a.chunk_off[t1];
+    }
+    if (t0 == t1) return;   // nothing of this instance is formed from tiles
+    if constexpr (NE > 0) {
+        const int rows = FINISH_THREADS / G, g = tid & (G - 1), sub = tid / G;
+        double acc[NE];
+#pragma unroll
+        for (int k = 0; k < NE; ++k) acc[k] = 0.0;
+        if (r0 + g < a.R) {
+#pragma unroll 4
+            for (int t = t0 + sub; t < t1; t += rows)
+#pragma unroll
+                for (int k = 0; k < NE; ++k) acc[k] += a.epart[((size_t)t * NE + k) * a.R + r0 + g];
+        }
 #pragma unroll
         for (int k = 0; k < NE; ++k) {
-            double v = lds[k][threadIdx.x];
-            for (int s = 1; s < 8; ++s) v += lds[k][s * 32 + threadIdx.x];
-            x[k] = v;
+            const double v = column_tree<double>(acc[k], lds, G, rows);
+            if (tid < G) e_sum[k][tid] = v;
         }
-        // U, S, F as energy_combine_kernel forms them
-        double U, S;
-        if (kind == KIND_MAXCUT) {
-            U = -wtot[inst] + 0.5 * x[0];
-            S = x[1];
-        } else if (kind == KIND_MAXSAT) {
-            U = x[0];
-            S = x[1];
-        } else {
-            const double* C = csum + ((size_t)inst * R + r) * q;
-            double c2 = 0.0;
-            for (int s = 0; s < q; ++s) c2 += C[s] * C[s];
-            U = x[0] + lam * (c2 - x[1]);
-            S = x[NE - 1];
+        if (tid < G && r0 + tid < a.R) {
+            const int r = r0 + tid;
+            double U, S;
+            if (a.kind == KIND_MAXCUT) {
+                U = -a.wtot[inst] + 0.5 * e_sum[0][tid];
+                S = e_sum[1][tid];
+            } else if (a.kind == KIND_MAXSAT) {
+                U = e_sum[0][tid];
+                S = e_sum[1][tid];
+            } else {
+                const double* C = a.csum + ((size_t)inst * a.R + r) * a.q;
+                double c2 = 0.0;
+                for (int s = 0; s < a.q; ++s) c2 += C[s] * C[s];
+                U = e_sum[0][tid] + a.lam * (c2 - e_sum[1][tid]);
+                S = e_sum[NE - 1][tid];
+            }
+            double* o = a.eout + (size_t)inst * 3 * a.R;
+            o[r] = U;
+            o[a.R + r] = S;
+            o[2 * a.R + r] = U - S / a.beta;
         }
-        double* o = eout + (size_t)inst * 3 * R;
-        o[r] = U;
-        o[R + r] = S;
-        o[2 * R + r] = U - S / beta;
     }
-}
-
-// energies: raw[inst][NE][R] -> eout[inst][3][R] = U, S, F
-__global__ void energy_combine_kernel(int kind, int R, int q, int n_inst, const int32_t* __restrict__ inst_chunk_off,
-                                      const double* __restrict__ raw,
-                                      const double* __restrict__ wtot, const double* __restrict__ csum,
-                                      double lam, double beta, double* __restrict__ eout)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_inst * R) return;
-    const int inst = idx / R, r = idx % R;
-    if (inst_chunk_off[inst] == inst_chunk_off[inst + 1]) return;   // its energies are not formed from tiles
-    double U, S;
-    if (kind == KIND_MAXCUT) {
-        const double* x = raw + (size_t)inst * 2 * R;
-        U = -wtot[inst] + 0.5 * x[r];
-        S = x[R + r];
-    } else if (kind == KIND_MAXSAT) {
-        const double* x = raw + (size_t)inst * 2 * R;
-        U = x[r];
-        S = x[R + r];
-    } else {
-        const double* x = raw + (size_t)inst * 3 * R;
-        const double* C = csum + ((size_t)inst * R + r) * q;
-        double c2 = 0.0;
-        for (int s = 0; s < q; ++s) c2 += C[s] * C[s];
-        U = x[r] + lam * (c2 - x[R + r]);
-        S = x[2 * R + r];
+    if constexpr (COL) {
+        __syncthreads();   // the energies have read the old sums
+        // 2^-40 fixed point (or state counts): exact in any order
+        const int cols = G * a.q, rows = FINISH_THREADS / cols, c = tid % cols, sub = tid / cols;
+        const int all = a.R * a.q, at = r0 * a.q + c;
+        long long acc = 0;
+        if (at < all) {
+#pragma unroll 4
+            for (int t = t0 + sub; t < t1; t += rows) acc += a.cpart[(size_t)t * all + at];
+        }
+        const long long v = column_tree<long long>(acc, reinterpret_cast<long long*>(lds), cols, rows);
+        if (tid < cols) c_sum[tid] = (double)v * a.scale;
+        __syncthreads();
+        if (tid < cols && at < all) {
+            const double* C = c_sum + (tid / a.q) * a.q;
+            double mean = 0.0;
+            for (int s = 0; s < a.q; ++s) mean += C[s];
+            mean /= a.q;
+            a.csum[(size_t)inst * all + at] = c_sum[tid];
+            a.ctil[(size_t)inst * all + at] = c_sum[tid] - mean;
+        }
     }
-    double* o = eout + (size_t)inst * 3 * R;
-    o[r] = U;
-    o[R + r] = S;
-    o[2 * R + r] = U - S / beta;
-}
-
-// column sums: fixed point -> C (double) and centred C~ (float)
-__global__ void colsum_combine_kernel(int R, int q, int n_inst, const long long* __restrict__ fx, double scale,
-                                      double* __restrict__ csum, double* __restrict__ ctil)
-{
-    const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n_inst * R) return;
-    const long long* x = fx + (size_t)idx * q;
-    double mean = 0.0;
-    for (int s = 0; s < q; ++s) {
-        const double c = (double)x[s] * scale;
-        csum[(size_t)idx * q + s] = c;
-        mean += c;
-    }
-    mean /= q;
-    for (int s = 0; s < q; ++s) ctil[(size_t)idx * q + s] = csum[(size_t)idx * q + s] - mean;
 }
 
 // ================================================ read-out & evaluation ===
@@ -1147,45 +1147,54 @@ hipError_t launch_seg_reduce(const T* part, int cols, const int32_t* chunk_off, 
 }
 template hipError_t launch_seg_reduce<double>(const double*, int, const int32_t*, int, const int32_t*, int,
                                               double*, double*, hipStream_t);
-template hipError_t launch_seg_reduce<long long>(const long long*, int, const int32_t*, int, const int32_t*, int,
-                                                 long long*, long long*, hipStream_t);
 template hipError_t launch_seg_reduce<int>(const int*, int, const int32_t*, int, const int32_t*, int, int*, int*,
                                            hipStream_t);
 
-hipError_t launch_energy_finish(int kind, int R, int q, int NE, int n_inst, const double* part,
-                                const int32_t* chunk_off, const int32_t* inst_chunk_off, const double* wtot,
-                                const double* csum, double lam, double beta, double* eout, hipStream_t st)
+// Sums of the tiles of each chunk: columns [0, ecols) of epart, then [0, ccols)
+// of cpart, 32 per workgroup (eight sub-sums, added in order).
+__global__ void __launch_bounds__(256) chunk_kernel(const double* __restrict__ epart, int ecols,
+                                                    const long long* __restrict__ cpart, int ccols,
+                                                    const int32_t* __restrict__ chunk_off, double* __restrict__ esum,
+                                                    long long* __restrict__ csum)
+{
+    __shared__ double lds[256];
+    const int eblocks = (ecols + 31) / 32;
+    const int t0 = chunk_off[blockIdx.x], t1 = chunk_off[blockIdx.x + 1], sub = threadIdx.x >> 5;
+    auto sum = [&](const auto* part, int cols, int c, auto* out, auto* l) {
+        typename std::remove_pointer<decltype(out)>::type acc = 0;
+        if (c < cols) {
+#pragma unroll 4
+            for (int t = t0 + sub; t < t1; t += 8) acc += part[(size_t)t * cols + c];
+        }
+        l[threadIdx.x] = acc;
+        __syncthreads();
+        if (sub == 0 && c < cols) {
+            for (int k = 1; k < 8; ++k) acc += l[k * 32 + threadIdx.x];
+            out[(size_t)blockIdx.x * cols + c] = acc;
+        }
+    };
+    const int c = (int)(threadIdx.x & 31);
+    if ((int)blockIdx.y < eblocks) sum(epart, ecols, (int)blockIdx.y * 32 + c, esum, lds);
+    else sum(cpart, ccols, ((int)blockIdx.y - eblocks) * 32 + c, csum, reinterpret_cast<long long*>(lds));
+}
+
+hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart, int ccols, const int32_t* chunk_off,
+                         int n_chunks, double* esum, long long* csum, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
-    const dim3 g(n_inst, (R + 31) / 32);
-    if (NE == 2)
-        energy_finish_kernel<2><<<g, 256, 0, st>>>(kind, R, q, part, chunk_off, inst_chunk_off, wtot, csum, lam, beta,
-                                                   eout);
-    else if (NE == 3)
-        energy_finish_kernel<3><<<g, 256, 0, st>>>(kind, R, q, part, chunk_off, inst_chunk_off, wtot, csum, lam, beta,
-                                                   eout);
-    else
-        return hipErrorInvalidValue;
+    const dim3 g(n_chunks, (ecols + 31) / 32 + (ccols + 31) / 32);
+    chunk_kernel<<<g, 256, 0, st>>>(epart, ecols, cpart, ccols, chunk_off, esum, csum);
     return hipGetLastError();
 }
 
-hipError_t launch_energy_combine(int kind, int R, int q, int n_inst, const int32_t* inst_chunk_off, const double* raw,
-                                 const double* wtot,
-                                 const double* csum, double lam, double beta, double* eout, hipStream_t st)
+hipError_t launch_finish(const FinishArgs& a, int n_inst, bool energies, bool columns, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
-    const int n = n_inst * R;
-    energy_combine_kernel<<<(n + 255) / 256, 256, 0, st>>>(kind, R, q, n_inst, inst_chunk_off, raw, wtot, csum, lam, beta,
-                                                            eout);
-    return hipGetLastError();
-}
-
-hipError_t launch_colsum_combine(int R, int q, int n_inst, const long long* fx, double scale, double* csum,
-                                 double* ctil, hipStream_t st)
-{
-    (void)hipGetLastError();   // drop stale errors of earlier calls
-    const int n = n_inst * R;
-    colsum_combine_kernel<<<(n + 255) / 256, 256, 0, st>>>(R, q, n_inst, fx, scale, csum, ctil);
+    const int G = columns ? (a.q < FINISH_COLS ? FINISH_COLS / a.q : 1) : FINISH_COLS;
+    const unsigned grid = (unsigned)n_inst * (unsigned)((a.R + G - 1) / G);
+    if (columns && energies) finish_kernel<3, true><<<grid, FINISH_THREADS, 0, st>>>(a);
+    else if (columns) finish_kernel<0, true><<<grid, FINISH_THREADS, 0, st>>>(a);
+    else if (energies) finish_kernel<2, false><<<grid, FINISH_THREADS, 0, st>>>(a);
     return hipGetLastError();
 }
 
