@@ -92,23 +92,6 @@ struct TileShape {
     int lanes = 0;   // cap on lanes per team (power of two <= 64; 0 = 64)
 };
 
-// Default launch shape before tuning: four waves, four rows per team, and as
-// many replicas per lane as keep a team's row within one wave.
-inline TileShape default_shape(int kind, int R)
-{
-    TileShape t;
-    t.waves = 4;
-    t.rows = 4;
-    if (kind == KIND_BMINCUT) {
-        t.vec = 1;
-        return t;
-    }
-    if (R % 4 == 0 && R >= 128) t.vec = 4;
-    else if (R % 2 == 0 && R >= 64) t.vec = 2;
-    else t.vec = 1;
-    return t;
-}
-
 // Per-step scalars, computed on the host in double and passed as float.
 struct StepScalars {
     double inv_beta_d;   // 1/beta and lambda in double for the gradient combination
@@ -152,6 +135,78 @@ inline LaunchGeom make_geom(int per_lane, int R, int waves, int max_lanes = 64)
     g.nseg = (need + g.lanes - 1) / g.lanes;
     g.teams_per_block = waves * (64 / g.lanes);
     return g;
+}
+
+// Launch shape of the integer evaluation (fem_eval_int and its allocation-free
+// form, whose scratch limit counts on these tiles): four waves, four rows per
+// team, as many replicas per lane as keep a team's row within one wave.
+inline TileShape eval_shape(int kind, int R)
+{
+    TileShape t;
+    if (kind == KIND_BMINCUT) return t;
+    if (R % 4 == 0 && R >= 128) t.vec = 4;
+    else if (R % 2 == 0 && R >= 64) t.vec = 2;
+    return t;
+}
+
+// Default launch shape before tuning: values per lane, waves, rows per team,
+// lanes per team and non-temporal state access by size, from sweeps of 500 ..
+// 300000 rows and R = 16 .. 512 on an MI355X (microseconds per step, the other
+// choice first).
+//  * One row per team while that leaves few workgroups, up to four beyond
+//    (`blocks` workgroups for the next doubling): 9000 rows at R = 16 with four
+//    rows 19.7, with one 13.3.
+//  * As many values per lane as still fill the chip: MaxCut 50000 rows, R = 32,
+//    one value 36, two 26; 300000 rows, one 119, four 89.  Max-k-SAT stays at
+//    two (rounds of four incidences): 20000 variables, R = 64, 44 / 34.
+//  * MaxCut in float32 at R >= 192: eight replica segments, one per XCD, while
+//    a segment of the marginals fits its 4 MB L2 (30000 rows, R = 256: 81 /
+//    72; R = 512, 7.7 MB: 142 / 149).
+//  * Manipulated gradients (short rows of bits): two waves and one row up to
+//    larger grids, 30000 rows of degree 20, R = 100: 38 / 31.
+//  * bMinCut: fewer lanes where a full wave leaves too many idle; at q >= 16,
+//    where a lane's states alone are a cache line, down to eight (R = 100, 2400
+//    nodes, q = 16: 86 / 56), else 32 (R = 150, 4720 nodes, q = 8: 67 / 62).
+//  * State past the Infinity Cache is not found there again: non-temporal
+//    from 256 MB of state and marginals on (bMinCut 200000 nodes, q = 8, R = 16:
+//    404 / 334; at exactly 256 MB, MaxCut 50000 rows, R = 256: 111 / 111).
+inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, int marg_bytes)
+{
+    TileShape t;
+    const double vals = (double)n * R * (kind == KIND_BMINCUT ? q : 1);
+    t.waves = 4;
+    t.nt = vals * (12 + 2 * marg_bytes) > 256e6 && !(kind == KIND_BMINCUT && q >= 16) ? 1 : 0;
+    int cap = 4;
+    double blocks = 1024;
+    if (kind == KIND_BMINCUT) {
+        blocks = 448;
+        double best = 0.0;
+        for (int l = 64; l >= (q >= 16 ? 8 : 32); l >>= 1) {
+            const LaunchGeom g = make_geom(1, R, t.waves, l);
+            const double used = (double)R / ((double)g.nseg * g.lanes);
+            if (used > best * 1.05) {
+                best = used;
+                t.lanes = l;
+            }
+        }
+    } else if (kind == KIND_MAXSAT) {
+        t.vec = R % 2 == 0 && R >= 64 && vals >= 1e6 ? 2 : 1;
+    } else if (manip) {
+        t.vec = R % 4 == 0 && vals >= 4e5 ? 4 : R % 2 == 0 && vals >= 1e5 ? 2 : 1;
+        t.waves = 2;
+        blocks = 8192;
+        cap = 2;
+    } else {
+        t.vec = R % 4 == 0 && (vals >= 4e6 || R >= 128) ? 4 : R % 2 == 0 && vals >= 4e5 ? 2 : 1;
+        if (R >= 192 && marg_bytes == 4 && vals * 4 / 8 <= 4e6) {
+            const int l = pow2ceil((R / t.vec + 7) / 8);
+            t.lanes = l < 64 ? l : 64;
+        }
+    }
+    const LaunchGeom g = make_geom(t.vec, R, t.waves, t.lanes);
+    t.rows = 1;
+    while (t.rows < cap && (double)n * g.nseg >= blocks * g.teams_per_block * 2 * t.rows) t.rows <<= 1;
+    return t;
 }
 
 // Arguments shared by the step kernels.
@@ -217,7 +272,8 @@ struct FinishArgs {
 // epart and cpart (cols 0: absent) summed per chunk of tiles
 hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart, int ccols, const int32_t* chunk_off,
                          int n_chunks, double* esum, long long* csum, hipStream_t st);
-hipError_t launch_finish(const FinishArgs& a, int n_inst, bool energies, bool columns, hipStream_t st);
+// max_tiles: most tiles (or chunks) of one instance
+hipError_t launch_finish(const FinishArgs& a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st);
 // manipulated gradients (fem_manip.hip): the step kernel, and the read-out copy
 // of a.h (sign bits or argmax states, with per-tile state counts for bMinCut)
 hipError_t launch_manip_step(int kind, int vec, bool nt, const LaunchGeom& g, int waves, const StepArgs& a,

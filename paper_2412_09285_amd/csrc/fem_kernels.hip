@@ -686,26 +686,38 @@ static hipError_t seg_reduce2(const T* part, int cols, const int32_t* chunk_off,
 // energies (now 10).
 constexpr int FINISH_THREADS = 1024, FINISH_COLS = 8;
 
-// Sum over the `rows` threads that hold the same column (thread = row * cols +
-// col), in a fixed tree; every thread of row 0 returns its column's total.
-template <typename T>
-__device__ __forceinline__ T column_tree(T x, T* lds, int cols, int rows)
+// Sums over the `rows` threads that hold the same column (thread = row * cols +
+// col), in a fixed tree: through LDS down to one wave, then between its
+// lanes.  Threads of row 0 get their column's totals.  Rows beyond the tiles
+// add zeros, so the result does not depend on how many there are.
+template <typename T, int K>
+__device__ __forceinline__ void column_tree(T (&x)[K], T* lds, int cols, int rows)
 {
-    lds[threadIdx.x] = x;
+    const int n = blockDim.x, t = threadIdx.x;
+#pragma unroll
+    for (int k = 0; k < K; ++k) lds[k * n + t] = x[k];
     __syncthreads();
-    for (int o = rows >> 1; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o * cols) lds[threadIdx.x] += lds[threadIdx.x + o * cols];
+    int o = (rows >> 1) * cols;
+    for (; o >= 64; o >>= 1) {
+        if (t < o)
+#pragma unroll
+            for (int k = 0; k < K; ++k) lds[k * n + t] += lds[k * n + t + o];
         __syncthreads();
     }
-    x = lds[threadIdx.x];
+    if (t < 64) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) x[k] = lds[k * n + t];
+        for (; o >= cols; o >>= 1)
+#pragma unroll
+            for (int k = 0; k < K; ++k) x[k] += __shfl_down(x[k], o, 64);
+    }
     __syncthreads();
-    return x;
 }
 
 template <int NE, bool COL>
 __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
 {
-    __shared__ double lds[FINISH_THREADS];
+    __shared__ double lds[FINISH_THREADS * (NE > 0 ? NE : 1)];
     __shared__ double e_sum[NE > 0 ? NE : 1][FINISH_COLS];
     __shared__ double c_sum[32 > FINISH_COLS ? 32 : FINISH_COLS];
     const int tid = threadIdx.x;
@@ -719,7 +731,7 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
     }
     if (t0 == t1) return;   // nothing of this instance is formed from tiles
     if constexpr (NE > 0) {
-        const int rows = FINISH_THREADS / G, g = tid & (G - 1), sub = tid / G;
+        const int rows = blockDim.x / G, g = tid & (G - 1), sub = tid / G;
         double acc[NE];
 #pragma unroll
         for (int k = 0; k < NE; ++k) acc[k] = 0.0;
@@ -729,11 +741,10 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
 #pragma unroll
                 for (int k = 0; k < NE; ++k) acc[k] += a.epart[((size_t)t * NE + k) * a.R + r0 + g];
         }
+        column_tree<double, NE>(acc, lds, G, rows);
+        if (tid < G)
 #pragma unroll
-        for (int k = 0; k < NE; ++k) {
-            const double v = column_tree<double>(acc[k], lds, G, rows);
-            if (tid < G) e_sum[k][tid] = v;
-        }
+            for (int k = 0; k < NE; ++k) e_sum[k][tid] = acc[k];
         if (tid < G && r0 + tid < a.R) {
             const int r = r0 + tid;
             double U, S;
@@ -759,15 +770,15 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
     if constexpr (COL) {
         __syncthreads();   // the energies have read the old sums
         // 2^-40 fixed point (or state counts): exact in any order
-        const int cols = G * a.q, rows = FINISH_THREADS / cols, c = tid % cols, sub = tid / cols;
+        const int cols = G * a.q, rows = blockDim.x / cols, c = tid % cols, sub = tid / cols;
         const int all = a.R * a.q, at = r0 * a.q + c;
-        long long acc = 0;
+        long long acc[1] = {0};
         if (at < all) {
 #pragma unroll 4
-            for (int t = t0 + sub; t < t1; t += rows) acc += a.cpart[(size_t)t * all + at];
+            for (int t = t0 + sub; t < t1; t += rows) acc[0] += a.cpart[(size_t)t * all + at];
         }
-        const long long v = column_tree<long long>(acc, reinterpret_cast<long long*>(lds), cols, rows);
-        if (tid < cols) c_sum[tid] = (double)v * a.scale;
+        column_tree<long long, 1>(acc, reinterpret_cast<long long*>(lds), cols, rows);
+        if (tid < cols) c_sum[tid] = (double)acc[0] * a.scale;
         __syncthreads();
         if (tid < cols && at < all) {
             const double* C = c_sum + (tid / a.q) * a.q;
@@ -1187,14 +1198,18 @@ hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart,
     return hipGetLastError();
 }
 
-hipError_t launch_finish(const FinishArgs& a, int n_inst, bool energies, bool columns, hipStream_t st)
+hipError_t launch_finish(const FinishArgs& a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
     const int G = columns ? (a.q < FINISH_COLS ? FINISH_COLS / a.q : 1) : FINISH_COLS;
     const unsigned grid = (unsigned)n_inst * (unsigned)((a.R + G - 1) / G);
-    if (columns && energies) finish_kernel<3, true><<<grid, FINISH_THREADS, 0, st>>>(a);
-    else if (columns) finish_kernel<0, true><<<grid, FINISH_THREADS, 0, st>>>(a);
-    else if (energies) finish_kernel<2, false><<<grid, FINISH_THREADS, 0, st>>>(a);
+    // a row of threads per tile of the largest instance, as far as they go
+    int threads = FINISH_THREADS;
+    const int cols = columns ? G * a.q : G;
+    while (threads > 64 && threads / 2 >= pow2ceil(max_tiles) * cols) threads >>= 1;
+    if (columns && energies) finish_kernel<3, true><<<grid, threads, 0, st>>>(a);
+    else if (columns) finish_kernel<0, true><<<grid, threads, 0, st>>>(a);
+    else if (energies) finish_kernel<2, false><<<grid, threads, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -95,7 +95,7 @@ bool resident_choose(const Problem& p, ResData& r);
 // steps: host table of T + 1 entries.
 hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r);
 void resident_free(ResData& r);
-// Enqueues steps [a.t0, a.t1) of every resident instance.
-hipError_t resident_launch(const Problem& p, const ResData& r, bool manip, ResArgs a, hipStream_t st);
+// Enqueues steps [a.t0, a.t1) of the instances of class cls.
+hipError_t resident_launch(const Problem& p, const ResData& r, int cls, bool manip, ResArgs a, hipStream_t st);
 
 }  // namespace fem

@@ -688,9 +688,11 @@ static ResKernel pick(const Problem& p, bool pm1, bool manip, int rpt)
     return pm1 ? maxcut_kernel<false, true, ALDS>(rpt) : maxcut_kernel<false, false, ALDS>(rpt);
 }
 
-hipError_t resident_launch(const Problem& p, const ResData& r, bool manip, ResArgs a, hipStream_t st)
+hipError_t resident_launch(const Problem& p, const ResData& r, int cls, bool manip, ResArgs a, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
+    const ResClass& c = r.classes[(size_t)cls];
+    a.inst = r.inst + c.first;
     a.perm = r.perm;
     a.slice = r.slice;
     a.adj = r.adj;
@@ -699,20 +701,15 @@ hipError_t resident_launch(const Problem& p, const ResData& r, bool manip, ResAr
     a.nrm = p.nrm;
     a.kind = p.kind;
     a.planes = r.planes;
-    for (const ResClass& c : r.classes) {
-        a.inst = r.inst + c.first;
-        ResKernel k = c.adj_lds ? pick<true>(p, r.pm1, manip, c.rpt) : pick<false>(p, r.pm1, manip, c.rpt);
-        if (!k) return hipErrorInvalidValue;
-        if (c.lds > 64 * 1024) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds);
-            if (e != hipSuccess) return e;
-        }
-        k<<<dim3((unsigned)c.n_inst * (unsigned)a.R), dim3(c.threads), c.lds, st>>>(a);
-        hipError_t e = hipGetLastError();
+    ResKernel k = c.adj_lds ? pick<true>(p, r.pm1, manip, c.rpt) : pick<false>(p, r.pm1, manip, c.rpt);
+    if (!k) return hipErrorInvalidValue;
+    if (c.lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds);
         if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    k<<<dim3((unsigned)c.n_inst * (unsigned)a.R), dim3(c.threads), c.lds, st>>>(a);
+    return hipGetLastError();
 }
 
 }  // namespace fem

@@ -1,0 +1,43 @@
+"""The launch shape a solver starts with: every replica count and kind that a
+solver can be created for gets a valid one, and the fields are those of an
+explicit shape."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_09285_amd import fem
+from paper_2412_09285_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+KINDS = {"maxcut": ({}, 8300), "bf16": (dict(marginal_dtype=fem.BF16), 8300),
+         "manip": (dict(gradient=fem.GRAD_MANIPULATED, energy_every=0), 8300), "maxsat": ({}, 4200),
+         "bmincut2": (dict(lam=0.1), 300), "bmincut8": (dict(lam=0.1), 300), "bmincut32": (dict(lam=0.1), 300),
+         "large": ({}, 120000)}
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_default_shape(kind):
+    kw, n = KINDS[kind]
+    q = int(kind[7:]) if kind.startswith("bmincut") else 1
+    if kind == "maxsat":
+        prob = fem.Problem.from_cnf(W.random_ksat(n, 3 * n, 3, seed=1))
+    else:
+        g = W.random_sparse_graph(n, 2 * n, seed=1, weights="one" if q > 1 else "pm1")
+        prob = fem.Problem.maxcut(n, g.u, g.v, g.w) if q == 1 else fem.Problem.bmincut(n, g.u, g.v, g.w, q)
+    for R in (1, 2, 3, 20, 31, 64, 100, 192, 257, 320, 516, 2100, 5000):
+        if n * R * q > 5e7:
+            continue
+        shape = (n, R) if q == 1 else (n, R, q)
+        h0 = torch.randn(shape, device="cuda", generator=torch.Generator("cuda").manual_seed(R)) * 0.3
+        out = []
+        for tile in (None, (q if q > 1 else 1, 2, 3, 0, 0)):
+            s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, **kw), stream=torch.cuda.Stream())
+            if tile is not None:
+                s.set_tile(*tile)
+            torch.cuda.synchronize()
+            s.set_fields(h0)
+            s.run_until(2)
+            out.append(s.fields(torch.empty_like(h0)))
+            s.close()
+        assert torch.equal(*out), R

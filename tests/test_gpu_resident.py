@@ -124,6 +124,12 @@ def test_mixed_batch(kind):
         s.set_fields(h)
         s.run_until(9)
         both.append((s.fields(), s.anytime_best(), s.energies() if kind != "manip" else ()))
+        # the captured range again, with eager steps and getters in between
+        for _ in range(3):
+            s.set_fields(h)
+            s.run_until(9)
+            assert np.array_equal(s.fields(), both[-1][0]) and np.array_equal(s.anytime_best(), both[-1][1])
+            s.step(1)
     hb, bb, eb = both[0]
     for k, (h, b, e) in enumerate(both[1:]):
         assert np.array_equal(h, hb[off[k]:off[k + 1]]) and np.array_equal(b[0], bb[k])
