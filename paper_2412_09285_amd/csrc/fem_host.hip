@@ -440,6 +440,7 @@ struct fem_solver {
     static constexpr int N_SIDE = 2;
     hipStream_t side[N_SIDE] = {nullptr, nullptr};
     hipEvent_t fork = nullptr, join[N_SIDE] = {nullptr, nullptr};
+    char* block = nullptr;   // the allocation behind the small arrays below
     // energies
     int NE = 2;
     double* epart = nullptr;
@@ -466,7 +467,7 @@ struct fem_solver {
     double* best = nullptr;
     // one-logit read-out on bit words (fem_readout.hip), where it applies
     uint32_t* bits = nullptr;    // [n][bit_words(R)]
-    int32_t* count = nullptr;    // [inst][R], behind them
+    int32_t* count = nullptr;    // [inst][R]
     TileSet bs;
     // best replica: double value [inst], int32 replica [inst], uint8 state [n]
     char* pick = nullptr;
@@ -918,7 +919,15 @@ static fem_status do_steps(fem_solver* s, int t_end)
     return FEM_OK;
 }
 
-static fem_status init_marginals(fem_solver* s)
+// Marginal copy (and column sums) of the fields.  src: new fields on the
+// device, to set with cleared moments in the same pass (sets_fields says
+// whether this solver's pass does).
+static bool sets_fields(const fem_solver* s)
+{
+    return !s->res.all && !s->manip && !s->dense_i8;
+}
+
+static fem_status init_marginals(fem_solver* s, const float* src = nullptr)
 {
     if (s->res.all) return FEM_OK;   // resident instances form theirs from the fields
     StepArgs a = base_args(s);
@@ -928,15 +937,13 @@ static fem_status init_marginals(fem_solver* s)
     else if (s->dense_i8)
         HIPCHK(launch_dense_i8_init(*s->prob, a, s->stream));
     else
-        HIPCHK(launch_init_marginals(s->kind, s->dtype, s->geo, s->shape.waves, a, s->vals, s->stream));
+        HIPCHK(launch_init_marginals(s->kind, s->dtype, s->geo, s->shape.waves, a, src, s->stream));
     return finish(s, -1);
 }
 
 static fem_status reset_best(fem_solver* s)
 {
-    std::vector<double> inf((size_t)s->n_inst * s->R, std::numeric_limits<double>::infinity());
-    HIPCHK(hipMemcpyAsync(s->best, inf.data(), inf.size() * sizeof(double), hipMemcpyHostToDevice, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    HIPCHK(launch_fill((size_t)s->n_inst * s->R, std::numeric_limits<double>::infinity(), s->best, s->stream));
     return FEM_OK;
 }
 
@@ -964,18 +971,8 @@ static void destroy_solver(fem_solver* s)
     void* m1v = s->marg[1];
     if (m0) (void)hipFree(m0);
     if (m1v) (void)hipFree(m1v);
-    dfree(s->eout);
     dfree(s->ehist);
-    dfree(s->d_wtot);
-    dfree(s->csum);
-    dfree(s->ctil);
-    dfree(s->sigma);
-    dfree(s->vout);
-    dfree(s->sint);
-    dfree(s->sout);
-    dfree(s->best);
-    dfree(s->bits);
-    dfree(s->pick);
+    dfree(s->block);
     dfree(s->bs.tiles);
     fem_problem* owner = s->owner;
     delete s;
@@ -1442,27 +1439,38 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         }
         if (e != hipSuccess) return bail(fail(FEM_E_HIP, "clearing the marginal copy: %s", hipGetErrorString(e)));
     }
-    ALLOC(s->eout, IR * 3);
     if (P.record_energies && P.energy_every > 0) {
         s->n_records = (P.steps + P.energy_every - 1) / P.energy_every;
         ALLOC(s->ehist, (size_t)s->n_records * IR * 3);
     }
-    ALLOC(s->d_wtot, (size_t)s->n_inst);
-    ALLOC(s->sigma, (size_t)s->n * s->R);
-    ALLOC(s->vout, IR);
-    ALLOC(s->best, IR);
-    if (!evaluation) {
-        ALLOC(s->pick, (size_t)s->n_inst * 12 + (size_t)s->n);
-        if (bit_evaluation(p)) {
-            ALLOC(s->bits, (size_t)s->n * bit_words(s->R) + IR);
-            s->count = reinterpret_cast<int32_t*>(s->bits + (size_t)s->n * bit_words(s->R));
+    {
+        // the small arrays share one allocation
+        size_t off = 0;
+        std::vector<std::pair<void**, size_t>> parts;
+        auto take = [&](auto** ptr, size_t count) {
+            parts.emplace_back(reinterpret_cast<void**>(ptr), off);
+            off += (count * sizeof(**ptr) + 255) & ~(size_t)255;
+        };
+        take(&s->eout, IR * 3);
+        take(&s->d_wtot, (size_t)s->n_inst);
+        take(&s->sigma, (size_t)s->n * s->R);
+        take(&s->vout, IR);
+        take(&s->best, IR);
+        if (!evaluation) {
+            take(&s->pick, (size_t)s->n_inst * 12 + (size_t)s->n);
+            if (bit_evaluation(p)) {
+                take(&s->bits, (size_t)s->n * bit_words(s->R));
+                take(&s->count, IR);
+            }
         }
-    }
-    if (s->kind == KIND_BMINCUT) {
-        ALLOC(s->csum, IR * s->q);
-        ALLOC(s->ctil, IR * s->q);
-        ALLOC(s->sint, IR * s->q);
-        ALLOC(s->sout, IR * s->q);
+        if (s->kind == KIND_BMINCUT) {
+            take(&s->csum, IR * s->q);
+            take(&s->ctil, IR * s->q);
+            take(&s->sint, IR * s->q);
+            take(&s->sout, IR * s->q);
+        }
+        ALLOC(s->block, off);
+        for (auto& q : parts) *q.first = s->block + q.second;
     }
 #undef ALLOC
     e = hipMemcpy(s->d_wtot, p.inst_wtot.data(), sizeof(double) * s->n_inst, hipMemcpyHostToDevice);
@@ -1549,19 +1557,26 @@ fem_status fem_set_fields(fem_solver* s, const float* h, int on_device)
 {
     if (!s || !h) return fail(FEM_E_INVAL, "NULL argument");
     HIPCHK(hipSetDevice(s->prob->device));
-    // the fields, and zero Adam moments, in one pass over the state rows
-    // (host fields are copied first)
+    // the fields, zero Adam moments and, where the kernel does, the marginal
+    // copy in one pass over the state rows (host fields are copied first)
     const int64_t rq = (int64_t)s->R * s->Q;
-    if (on_device) {
-        HIPCHK(launch_rows(s->n, rq, s->h, s->srow, h, rq, s->m1, s->m2, s->stream));
-    } else {
-        HIPCHK(copy_state_rows(s, s->h, true, h, hipMemcpyHostToDevice));
-        HIPCHK(launch_rows(s->n, rq, nullptr, s->srow, nullptr, rq, s->m1, s->m2, s->stream));
-    }
     s->t = 0;
     s->last_energy_step = -1;
-    STCHK(init_marginals(s));
+    // a Potts lane reads its q states as one vector
+    const bool aligned = s->Q == 1 || (reinterpret_cast<uintptr_t>(h) & 15) == 0;
+    if (on_device && sets_fields(s) && aligned) {
+        STCHK(init_marginals(s, h));
+    } else {
+        if (on_device) {
+            HIPCHK(launch_rows(s->n, rq, s->h, s->srow, h, rq, s->m1, s->m2, s->stream));
+        } else {
+            HIPCHK(copy_state_rows(s, s->h, true, h, hipMemcpyHostToDevice));
+            HIPCHK(launch_rows(s->n, rq, nullptr, s->srow, nullptr, rq, s->m1, s->m2, s->stream));
+        }
+        STCHK(init_marginals(s));
+    }
     STCHK(reset_best(s));
+    HIPCHK(hipStreamSynchronize(s->stream));   // the caller's array is read inside the call
     s->fields_set = true;
     return FEM_OK;
 }

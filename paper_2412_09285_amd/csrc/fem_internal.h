@@ -245,10 +245,12 @@ int set_error(int st, const char* msg);
 // host-side kernel launchers (fem_kernels.hip)
 hipError_t launch_step(int kind, int dtype, int vec, bool nt, const LaunchGeom& g, int waves,
                        const StepArgs& a, hipStream_t st);
-// marginal copy of a.h into a.marg_nxt (count = n*R values for one-logit kinds);
-// for bMinCut also the column-sum partials a.cpart
+// marginal copy of a.h into a.marg_nxt; for bMinCut also the column-sum
+// partials a.cpart.  src (dense [n][R] or [n][R][q] on the device, or null): new
+// fields, which a.h is set to, with a.m1 and a.m2 cleared
 hipError_t launch_init_marginals(int kind, int dtype, const LaunchGeom& g, int waves,
-                                 const StepArgs& a, size_t count, hipStream_t st);
+                                 const StepArgs& a, const float* src, hipStream_t st);
+hipError_t launch_fill(size_t count, double x, double* out, hipStream_t st);
 // out[inst][c] = sum over the instance's tiles of part[tile][c] (two fixed-order stages)
 template <typename T>
 hipError_t launch_seg_reduce(const T* part, int cols, const int32_t* chunk_off, int n_chunks,
