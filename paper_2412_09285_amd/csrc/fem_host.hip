@@ -415,6 +415,7 @@ struct fem_solver {
     bool manip = false;   // manipulated gradients on a graph kind: read-out marginal copy
     bool dense = false;   // dense MaxCut problem, explicit gradients: matrix-core step kernel
     bool dense_i8 = false;   // ... with integral weights: int8 digit planes as the marginal copy
+    DenseShape dshape{};      // ... and the block of its workgroups
     int32_t rw = 0;       // MaxCut manipulated: 32-bit words per row of sign bits
     // state: one allocation of 3 vals floats holding h, m1, m2; rows of each
     // are srow floats apart (RQ: three separate arrays; 3RQ: the three rows
@@ -624,8 +625,8 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
         (s->geo.nseg > 1 && count_tiles(s, s->geo.teams_per_block * shape.rows) <= GRID_Y_MAX) ? 1 : 0;
     s->lanes_log2 = 0;
     while ((1 << s->lanes_log2) < s->geo.lanes) ++s->lanes_log2;
-    // the dense step kernel owns fixed row blocks (the padding of W)
-    const int tile_rows = s->dense ? DENSE_ROWS : s->geo.teams_per_block * shape.rows;
+    if (s->dense) s->dshape = dense_shape(p, s->R);
+    const int tile_rows = s->dense ? s->dshape.rows : s->geo.teams_per_block * shape.rows;
     const bool mixed = !s->res.taken.empty();
     STCHK(make_tiles(p, tile_rows, mixed ? s->res.taken.data() : nullptr, s->geo.seg_major != 0, s->ts));
     if (!mixed) s->es = s->ts;
@@ -892,7 +893,7 @@ static fem_status tiled_step(fem_solver* s)
     if (s->manip)
         HIPCHK(launch_manip_step(s->kind, s->shape.vec, s->shape.nt != 0, s->geo, s->shape.waves, a, s->stream));
     else if (s->dense)
-        HIPCHK(launch_dense_step(*s->prob, s->dtype, en, s->shape.nt != 0, s->ts.n_tiles, a, s->stream));
+        HIPCHK(launch_dense_step(*s->prob, s->dshape, s->dtype, en, s->shape.nt != 0, s->ts.n_tiles, a, s->stream));
     else
         HIPCHK(launch_step(s->kind, s->dtype, s->shape.vec, s->shape.nt != 0, s->geo, s->shape.waves, a, s->stream));
     if (e1) HIPCHK(hipEventRecord(e1, s->stream));
@@ -924,7 +925,7 @@ static fem_status do_steps(fem_solver* s, int t_end)
 // whether this solver's pass does).
 static bool sets_fields(const fem_solver* s)
 {
-    return !s->res.all && !s->manip && !s->dense_i8;
+    return !s->res.all && !s->manip;
 }
 
 static fem_status init_marginals(fem_solver* s, const float* src = nullptr)
@@ -935,7 +936,7 @@ static fem_status init_marginals(fem_solver* s, const float* src = nullptr)
     if (s->manip)
         HIPCHK(launch_manip_init(s->kind, s->geo, s->shape.waves, a, s->stream));
     else if (s->dense_i8)
-        HIPCHK(launch_dense_i8_init(*s->prob, a, s->stream));
+        HIPCHK(launch_dense_i8_init(*s->prob, a, src, s->stream));
     else
         HIPCHK(launch_init_marginals(s->kind, s->dtype, s->geo, s->shape.waves, a, src, s->stream));
     return finish(s, -1);
@@ -1044,7 +1045,12 @@ fem_status fem_maxcut_create_dense(int device, int32_t n, const float* W, fem_pr
     if (e == hipSuccess) e = hipMemcpy(p.dense_w, pad.data(), pad.size() * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess && small_int) {
         std::vector<int8_t> w8(pad.size());
-        for (size_t k = 0; k < pad.size(); ++k) w8[k] = (int8_t)pad[k];
+        for (int32_t i = 0; i < n; ++i)
+            for (int32_t j = 0; j < ld; j += 16) {
+                int8_t* at = &w8[dense_i8_at(i, j, ld)];
+                const float* from = &pad[(size_t)i * ld + j];
+                for (int k = 0; k < 16; ++k) at[k] = (int8_t)from[k];
+            }
         e = dalloc(&p.dense_w8, w8.size());
         if (e == hipSuccess) e = hipMemcpy(p.dense_w8, w8.data(), w8.size(), hipMemcpyHostToDevice);
     }

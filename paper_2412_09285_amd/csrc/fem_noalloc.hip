@@ -203,10 +203,10 @@ extern "C" fem_status fem_eval_int_noalloc(const fem_problem* fp, int32_t R, con
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (hipSetDevice(p.device) != hipSuccess) return (fem_status)set_error(FEM_E_HIP, "hipSetDevice failed");
 
-    // the tiling fem_eval_int uses
+    // (tiles of a dense problem hold 64 rows)
     const TileShape shape = eval_shape(p.kind, R);
     const LaunchGeom geo = make_geom(p.kind == KIND_BMINCUT ? 1 : shape.vec, R, shape.waves);
-    const int tile_rows = p.dense_w ? DENSE_ROWS : geo.teams_per_block * shape.rows;
+    const int tile_rows = p.dense_w ? 64 : geo.teams_per_block * shape.rows;
     size_t n_tiles = 0, n_chunks = 0;
     for (int b = 0; b < p.n_inst; ++b) {
         const size_t rows = (size_t)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]);
