@@ -432,12 +432,11 @@ struct fem_solver {
     LaunchGeom geo{};
     LaunchGeom egeo{};   // evaluation kernels: one replica per lane
     int lanes_log2 = 0;
-    TileSet ts;   // the instances of the row-tiled step kernels
-    TileSet es;   // byte evaluation: every instance (ts itself where that is all)
-    // instances whose replicas run on one compute unit each (fem_resident.hip)
+    TileSet ts;
+    // replicas that run on one compute unit each (fem_resident.hip)
     ResData res;
-    // Side streams for what runs beside the solver's stream within a range of
-    // steps: resident classes, where they are not the only part of the range.
+    // Side streams for the resident classes after the first, which run beside
+    // it within a range of steps.
     static constexpr int N_SIDE = 2;
     hipStream_t side[N_SIDE] = {nullptr, nullptr};
     hipEvent_t fork = nullptr, join[N_SIDE] = {nullptr, nullptr};
@@ -529,11 +528,8 @@ static bool valid_shape(const fem_solver* s, const TileShape& t)
 
 static void free_tiling(fem_solver* s)
 {
-    if (s->es.tiles == s->ts.tiles) s->es = TileSet{};
-    for (TileSet* x : {&s->ts, &s->es}) {
-        dfree(x->tiles);
-        *x = TileSet{};
-    }
+    dfree(s->ts.tiles);
+    s->ts = TileSet{};
     dfree(s->epart);
     dfree(s->etmp);
     dfree(s->cpart);
@@ -556,14 +552,13 @@ static void drop_graphs(fem_solver* s)
 // tiles an XCD receives form one contiguous row range; with several segments
 // the grid is segment-major (consecutive blocks = segments of one tile; while
 // the tile count fits grid.y) and the tiles keep their natural order.
-// The tiles of every instance not marked in skip (null: all instances).
-static fem_status make_tiles(const Problem& p, int tile_rows, const uint8_t* skip, bool seg_major, TileSet& ts)
+static fem_status make_tiles(const Problem& p, int tile_rows, bool seg_major, TileSet& ts)
 {
     std::vector<Tile> tiles;
     std::vector<int32_t> chunk_off{0}, inst_chunk_off{0};
     ts = TileSet{};
     for (int b = 0; b < p.n_inst; ++b) {
-        const int32_t r0 = p.inst_off[(size_t)b], r1 = skip && skip[b] ? r0 : p.inst_off[(size_t)b + 1];
+        const int32_t r0 = p.inst_off[(size_t)b], r1 = p.inst_off[(size_t)b + 1];
         const size_t first = tiles.size();
         int in_chunk = 0;
         for (int32_t r = r0; r < r1; r += tile_rows) {
@@ -627,25 +622,22 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
     while ((1 << s->lanes_log2) < s->geo.lanes) ++s->lanes_log2;
     if (s->dense) s->dshape = dense_shape(p, s->R);
     const int tile_rows = s->dense ? s->dshape.rows : s->geo.teams_per_block * shape.rows;
-    const bool mixed = !s->res.taken.empty();
-    STCHK(make_tiles(p, tile_rows, mixed ? s->res.taken.data() : nullptr, s->geo.seg_major != 0, s->ts));
-    if (!mixed) s->es = s->ts;
-    else if (!s->bits) STCHK(make_tiles(p, tile_rows, nullptr, s->geo.seg_major != 0, s->es));
+    STCHK(make_tiles(p, tile_rows, s->geo.seg_major != 0, s->ts));
     s->geo.n_tiles = s->ts.n_tiles;
     s->egeo = make_geom(1, s->R, shape.waves);
-    s->egeo.n_tiles = s->es.n_tiles;
+    s->egeo.n_tiles = s->ts.n_tiles;
     const size_t R = (size_t)s->R;
     HIPCHK(dalloc(&s->epart, (size_t)s->ts.n_tiles * s->NE * R));
     HIPCHK(dalloc(&s->etmp, (size_t)s->ts.n_chunks * s->NE * R));
     if (!s->bits) {
-        HIPCHK(dalloc(&s->vpart, (size_t)s->es.n_tiles * R));
-        HIPCHK(dalloc(&s->vtmp, (size_t)s->es.n_chunks * R));
+        HIPCHK(dalloc(&s->vpart, (size_t)s->ts.n_tiles * R));
+        HIPCHK(dalloc(&s->vtmp, (size_t)s->ts.n_chunks * R));
     }
     if (s->kind == KIND_BMINCUT) {
         HIPCHK(dalloc(&s->cpart, (size_t)s->ts.n_tiles * R * s->q));
         HIPCHK(dalloc(&s->ctmp, (size_t)s->ts.n_chunks * R * s->q));
-        HIPCHK(dalloc(&s->spart, (size_t)s->es.n_tiles * R * s->q));
-        HIPCHK(dalloc(&s->stmp, (size_t)s->es.n_chunks * R * s->q));
+        HIPCHK(dalloc(&s->spart, (size_t)s->ts.n_tiles * R * s->q));
+        HIPCHK(dalloc(&s->stmp, (size_t)s->ts.n_chunks * R * s->q));
     }
     return FEM_OK;
 }
@@ -775,11 +767,11 @@ static fem_status finish(fem_solver* s, int t)
 // integer evaluation of the byte configurations sigma into vout (and sout)
 static fem_status eval_bytes(fem_solver* s, const uint8_t* sigma)
 {
-    HIPCHK(launch_eval(*s->prob, s->egeo, s->shape.waves, s->es.tiles, s->R, sigma, s->vpart, s->spart, s->stream));
-    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->es.chunk_off, s->es.n_chunks, s->es.inst_chunk_off, s->n_inst,
+    HIPCHK(launch_eval(*s->prob, s->egeo, s->shape.waves, s->ts.tiles, s->R, sigma, s->vpart, s->spart, s->stream));
+    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off, s->n_inst,
                                      s->vtmp, s->vout, s->stream));
     if (s->kind == KIND_BMINCUT) {
-        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, s->es.chunk_off, s->es.n_chunks, s->es.inst_chunk_off,
+        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off,
                                       s->n_inst, s->stmp, s->sint, s->stream));
         HIPCHK(launch_sizes_widen((size_t)s->n_inst * s->R * s->q, s->sint, s->sout, s->stream));
     }
@@ -825,13 +817,11 @@ static fem_status profile_begin(fem_solver* s, int n, hipEvent_t* end)
     return FEM_OK;
 }
 
-// Steps [s->t, t_end) of the resident instances, a launch per class.  A class
-// is a few dozen workgroups for tens of microseconds a step, so where there
-// are several parts (classes, row-tiled instances) they run side by side:
-// joined[k] says which side streams the solver's stream has to wait for
-// (join_side).  Side by side, three instances of 1100, 2500 and 6000 nodes at
-// R = 16 take 8.6 us per step, one after the other 13.1; sixteen of 1000 ..
-// 40000 nodes at R = 32 (seven of them row-tiled) 52 and 61.
+// Steps [s->t, t_end) of a resident solver, a launch per class.  A class is a
+// few dozen workgroups for tens of microseconds a step, so several classes run
+// side by side: joined[k] says which side streams the solver's stream has to
+// wait for (join_side).  Side by side, three instances of 1100, 2500 and 6000
+// nodes at R = 16 take 8.6 us per step, one after the other 13.1.
 static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_solver::N_SIDE])
 {
     ResArgs a{};
@@ -849,12 +839,11 @@ static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_so
     a.t1 = t_end;
     a.bf16 = s->dtype == FEM_BF16;
     const int classes = (int)s->res.classes.size();
-    if (s->res.all) STCHK(profile_begin(s, t_end - s->t, &s->res_end));
+    STCHK(profile_begin(s, t_end - s->t, &s->res_end));
     if (s->fork) HIPCHK(hipEventRecord(s->fork, s->stream));
     for (int c = 0; c < classes; ++c) {
-        // the solver's stream takes the first class where it has nothing else
-        const int k = s->fork ? (c + (s->res.all ? fem_solver::N_SIDE : 0)) % (fem_solver::N_SIDE + (s->res.all ? 1 : 0))
-                              : fem_solver::N_SIDE;
+        // the solver's stream takes the first class
+        const int k = s->fork ? (c + fem_solver::N_SIDE) % (fem_solver::N_SIDE + 1) : fem_solver::N_SIDE;
         hipStream_t st = s->stream;
         if (k < fem_solver::N_SIDE) {
             st = s->side[k];
@@ -901,20 +890,19 @@ static fem_status tiled_step(fem_solver* s)
 }
 
 // Enqueues the steps up to t_end: the stretch to the next read-out at a time,
-// the resident instances all of it in one launch, the others step by step.
+// resident instances all of it in one launch, others step by step.
 static fem_status do_steps(fem_solver* s, int t_end)
 {
-    const bool resident = !s->res.taken.empty();
     while (s->t < t_end) {
         int e = t_end;
         if (s->prm.eval_every > 0) e = std::min(e, (s->t / s->prm.eval_every + 1) * s->prm.eval_every);
         bool joined[fem_solver::N_SIDE] = {};
-        if (resident) STCHK(resident_steps(s, e, joined));
+        if (s->res.all) STCHK(resident_steps(s, e, joined));
         for (; s->t < e; ++s->t) {
             if (!s->res.all) STCHK(tiled_step(s));
             if (energy_due(s, s->t)) s->last_energy_step = s->t;
         }
-        if (resident) STCHK(join_side(s, joined));
+        if (s->res.all) STCHK(join_side(s, joined));
         if (eval_due(s, s->t)) STCHK(readout_eval(s, true));
     }
     return FEM_OK;
@@ -1482,12 +1470,11 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     e = hipMemcpy(s->d_wtot, p.inst_wtot.data(), sizeof(double) * s->n_inst, hipMemcpyHostToDevice);
     if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
     if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS && IR <= ((size_t)1 << 30)) {   // a grid of IR blocks
-        if (resident_choose(p, s->res)) {
+        if (resident_choose(p, P.eval_every, s->res)) {
             std::vector<ResStep> steps((size_t)P.steps + 1);   // read one step ahead
             for (int t = 0; t < P.steps; ++t) steps[(size_t)t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
             e = resident_build(p, steps, s->res);
-            // more than one part to run side by side
-            if (e == hipSuccess && s->res.classes.size() + (s->res.all ? 0 : 1) > 1) {
+            if (e == hipSuccess && s->res.classes.size() > 1) {
                 for (int k = 0; k < fem_solver::N_SIDE && e == hipSuccess; ++k) {
                     e = hipStreamCreateWithFlags(&s->side[k], hipStreamNonBlocking);
                     if (e == hipSuccess) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
@@ -1499,12 +1486,8 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
                                  hipGetErrorString(e)));
         }
     }
-    int64_t tiled_rows = 0;   // rows that the row-tiled kernels step
-    for (int b = 0; b < s->n_inst; ++b)
-        if (s->res.taken.empty() || !s->res.taken[(size_t)b])
-            tiled_rows += p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b];
     TileShape sh = evaluation ? eval_shape(s->kind, s->R)
-                              : default_shape(s->kind, s->manip, tiled_rows, s->R, s->q, (int)msz);
+                              : default_shape(s->kind, s->manip, s->n, s->R, s->q, (int)msz);
     if (!valid_shape(s, sh)) sh = eval_shape(s->kind, s->R);
     while (!valid_shape(s, sh) && sh.waves > 1) sh.waves /= 2;
     while (!valid_shape(s, sh) && sh.vec > 1) sh.vec /= 2;
@@ -1512,7 +1495,7 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     fem_status st = setup_tiling(s, sh);
     if (st != FEM_OK) return bail(st);
     if (s->bits) {
-        st = make_tiles(p, bit_tile_rows(s->n, s->R), nullptr, false, s->bs);
+        st = make_tiles(p, bit_tile_rows(s->n, s->R), false, s->bs);
         if (st != FEM_OK) return bail(st);
     }
     st = reset_best(s);
@@ -1961,9 +1944,9 @@ fem_status fem_get_tile(const fem_solver* s, fem_tile* t)
     return FEM_OK;
 }
 
-// The launch shape of the row-tiled kernels; all_tiled: they also take over
-// the resident instances.
-static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool all_tiled)
+// The launch shape of the row-tiled kernels; take_over: they also step resident
+// instances from now on.
+static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool take_over)
 {
     TileShape sh;
     sh.vec = s->kind == KIND_BMINCUT ? 1 : t->vec;
@@ -1977,7 +1960,7 @@ static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool all_tiled)
                     t->rows, t->lanes, s->R);
     HIPCHK(hipSetDevice(s->prob->device));
     HIPCHK(hipStreamSynchronize(s->stream));
-    const bool take_over = all_tiled && !s->res.taken.empty();
+    take_over = take_over && s->res.all;
     if (take_over) resident_free(s->res);
     STCHK(setup_tiling(s, sh));
     // column-sum partials are laid out per tile, and resident instances keep

@@ -157,13 +157,20 @@ inline TileShape eval_shape(int kind, int R)
 //    (`blocks` workgroups for the next doubling): 9000 rows at R = 16 with four
 //    rows 19.7, with one 13.3.
 //  * As many values per lane as still fill the chip: MaxCut 50000 rows, R = 32,
-//    one value 36, two 26; 300000 rows, one 119, four 89.  Max-k-SAT stays at
-//    two (rounds of four incidences): 20000 variables, R = 64, 44 / 34.
+//    one value 36, two 26; 11361 rows, R = 20, 14.5 / 13.5; 300000 rows, one 119,
+//    four 89.  Max-k-SAT stays at
+//    two (rounds of four incidences): 20000 variables, R = 64, 44 / 34; and
+//    where one would take a second segment: 8000, k = 3, R = 76, 31 / 26.  It
+//    also stays at two rows (100000 variables, R = 64: four 198, two 182; 12000,
+//    R = 200: 61 / 55), one row for longer in a single segment of two values
+//    (12000, ratio 8, R = 76: two 49, one 45; in two segments, 5000, R = 200: one
+//    30, two 28).
 //  * MaxCut in float32 at R >= 192: eight replica segments, one per XCD, while
 //    a segment of the marginals fits its 4 MB L2 (30000 rows, R = 256: 81 /
 //    72; R = 512, 7.7 MB: 142 / 149).
 //  * Manipulated gradients (short rows of bits): two waves and one row up to
-//    larger grids, 30000 rows of degree 20, R = 100: 38 / 31.
+//    larger grids, 30000 rows of degree 20, R = 100: 38 / 31; several segments
+//    of single values four waves and two rows (7861 rows, R = 225: 35.0 / 34.0).
 //  * bMinCut: fewer lanes where a full wave leaves too many idle; at q >= 16,
 //    where a lane's states alone are a cache line, down to eight (R = 100, 2400
 //    nodes, q = 16: 86 / 56), else 32 (R = 150, 4720 nodes, q = 8: 67 / 62).
@@ -190,14 +197,17 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
             }
         }
     } else if (kind == KIND_MAXSAT) {
-        t.vec = R % 2 == 0 && R >= 64 && vals >= 1e6 ? 2 : 1;
+        t.vec = R % 2 == 0 && (R > 64 || (R == 64 && vals >= 1e6)) ? 2 : 1;
+        cap = 2;
+        if (t.vec == 2 && R <= 128) blocks = 2048;
     } else if (manip) {
         t.vec = R % 4 == 0 && vals >= 4e5 ? 4 : R % 2 == 0 && vals >= 1e5 ? 2 : 1;
-        t.waves = 2;
-        blocks = 8192;
+        const bool single = t.vec == 1 && R > 64;
+        t.waves = single ? 4 : 2;
+        blocks = single ? 2048 : 8192;
         cap = 2;
     } else {
-        t.vec = R % 4 == 0 && (vals >= 4e6 || R >= 128) ? 4 : R % 2 == 0 && vals >= 4e5 ? 2 : 1;
+        t.vec = R % 4 == 0 && (vals >= 4e6 || R >= 128) ? 4 : R % 2 == 0 && vals >= 2e5 ? 2 : 1;
         if (R >= 192 && marg_bytes == 4 && vals * 4 / 8 <= 4e6) {
             const int l = pow2ceil((R / t.vec + 7) / 8);
             t.lanes = l < 64 ? l : 64;

@@ -50,8 +50,7 @@ struct ResClass {
 
 struct ResData {
     std::vector<ResClass> classes;
-    std::vector<uint8_t> taken;   // [n_inst of the problem]: 1 where resident
-    bool all = false;             // every instance is resident
+    bool all = false;             // the problem's instances are resident
     bool pm1 = false;             // graphs: weights +-1, carried in the entries
     size_t dev_lds = 0;           // LDS a workgroup may use
     int planes = 1;               // values per position that neighbours read
@@ -88,11 +87,10 @@ struct ResArgs {
     int32_t planes;
 };
 
-// Marks the instances to take (the rule and its measurements stand at the
-// definition); false if there are none.
-bool resident_choose(const Problem& p, ResData& r);
-// Builds the device structure for the taken instances;
-// steps: host table of T + 1 entries.
+// Says whether a solver's instances are resident (the rule and its
+// measurements stand at the definition) and starts r.
+bool resident_choose(const Problem& p, int eval_every, ResData& r);
+// Builds the device structure; steps: host table of T + 1 entries.
 hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r);
 void resident_free(ResData& r);
 // Enqueues steps [a.t0, a.t1) of the instances of class cls.

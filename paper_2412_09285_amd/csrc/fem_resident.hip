@@ -483,8 +483,13 @@ void resident_free(ResData& r)
 
 // The rule: an instance is resident if its rows fit the registers of one
 // workgroup (RES_MAX_ROWS) and its entries fit LDS beside the values, or
-// number at most RES_MAX_STREAM and stream from L2.  It looks at the instance
-// alone, so an instance takes the same path by itself and inside a batch.
+// number at most RES_MAX_STREAM and stream from L2.  A batch is resident if
+// each of its instances is: beside row-tiled instances a resident one saves no
+// launch (R = 20, bfloat16, 2000 and 11361 nodes: 457 us for 24 steps, both
+// row-tiled 368; sixty-four of 1000 .. 50000 nodes at R = 32: 4035 and 3869 for
+// 25).  Eight rows per thread take too long to set up again after every
+// read-out if these come within 16 steps (8000 nodes of degree 3, R = 20, every
+// 10 steps: 306 / 252; without read-outs, R = 64: 214 / 275).
 // In LDS it won at every size measured (the table above).  Streaming, at
 // R = 16, resident against the best row-tiled shape: n = 2000 of degree 100
 // (51 k entries of 8 bytes) 11.4 / 12.5 us, n = 2000 of degree 120 (61 k)
@@ -492,7 +497,7 @@ void resident_free(ResData& r)
 // R = 512 24 / 31, 29 / 35 and 29 / 46 us; beyond, one compute unit reads for
 // longer than the whole chip needs.  Eight rows per thread are instantiated
 // only where they fit the registers: +-1 weights, entries in LDS.
-bool resident_choose(const Problem& p, ResData& r)
+bool resident_choose(const Problem& p, int eval_every, ResData& r)
 {
     const bool sat = p.kind == KIND_MAXSAT;
     int dev_lds = 0;
@@ -504,22 +509,21 @@ bool resident_choose(const Problem& p, ResData& r)
     for (size_t k = 0; r.pm1 && r.planes == 1 && k < p.h_adj.size(); ++k)
         if ((uint32_t)p.h_adj[k].y & 0x80000000u) r.planes = 2;
     r.dev_lds = (size_t)dev_lds;
-    r.taken.assign((size_t)p.n_inst, 0);
-    int n = 0;
-    for (int b = 0; b < p.n_inst; ++b)
-        n += r.taken[(size_t)b] = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds).ok ? 1 : 0;
-    r.all = n == p.n_inst;
-    if (!n) r = ResData{};
-    return n > 0;
+    r.all = true;
+    for (int b = 0; b < p.n_inst && r.all; ++b) {
+        const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
+        r.all = plan.ok && !(plan.rpt == 8 && eval_every > 0 && eval_every < 16);
+    }
+    if (!r.all) r = ResData{};
+    return r.all;
 }
 
 hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r)
 {
     hipError_t e = hipSuccess;
     const bool sat = p.kind == KIND_MAXSAT;
-    std::vector<int> ids;
-    for (int b = 0; b < p.n_inst; ++b)
-        if (r.taken[(size_t)b]) ids.push_back(b);
+    std::vector<int> ids((size_t)p.n_inst);
+    std::iota(ids.begin(), ids.end(), 0);
     auto rows_of = [&](int b) { return (int)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]); };
     // larger instances first: the longest workgroups start first
     std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return rows_of(x) > rows_of(y); });
