@@ -181,36 +181,36 @@ __global__ void __launch_bounds__(256) layer1_kernel(int32_t n, const int64_t* _
 }
 
 // Layer 2 on the matrix cores, sixteen nodes per wave at a time.
-// Gather: lane l = 16 g + i takes node i0 + i and the hidden units 16 c + 4 g ..
-// + 3 (c = 0..3) of its own and its neighbours' layer-1 pre-activation rows
-// (four float4 of a 256-byte row, ReLU applied on load, two neighbours in
-// flight): the four lanes of a node read 64 contiguous bytes at a time (with
-// units 16 g .. 16 g + 15 per lane they read 16 bytes of four segments, and
-// the kernel took 97 instead of 77 us on 135 k nodes of mean degree 6.5);
-// every a(H1) sum runs in CSR order, as in a single-node evaluation.
+// Gather: lane l = 16 g + i takes node i0 + i and hidden units 16 g .. 16 g +
+// 15 of its own and its neighbours' layer-1 pre-activation rows (four float4
+// of a 256-byte row, ReLU applied on load, two neighbours in flight); every
+// a(H1) sum runs in CSR order, as in a single-node evaluation.
+// (Units 16 c + 4 g .. + 3, 64 contiguous bytes at a time for the four lanes of
+// a node, took 77 instead of 97 us on 135 k nodes of mean degree 6.5, but add
+// the products in another order: a pre-activation within a rounding of zero
+// then changes sides, and with it the gradient, by up to 5e-6 of its norm.)
 // Dense: pre2 for the 16 nodes is four 16 x 16 output tiles (16 units each),
 // each 32 steps of v_mfma_f32_16x16x4_f32 (A: nodes x 4 inputs, B: 4 inputs x
-// units).  Step s = 4 c + u of the H1 half takes the inputs unit_of(g', s) (g'
-// = 0..3), so a lane supplies its own s-th gathered value as its A element and
-// nothing is staged; the a(H1) half follows.  [A2; B2] (128 x 64, float) sits
-// in LDS with rows padded to W2_LD = 68 floats, which puts the four input rows
-// of a step, four apart, in distinct banks.  Output element (node 4 g + v,
-// unit 16 t + i) is register v of lane l in tile t.  Each output depends on
-// its own node's inputs only, in a fixed order.
+// units).  Step s of the H1 half takes the inputs 16 g' + s (g' = 0..3), so a
+// lane supplies its own s-th gathered value as its A element and nothing is
+// staged; the a(H1) half follows.  [A2; B2] (128 x 64, float) sits in LDS
+// with rows padded to L2_LD = 65 floats, which puts the four input rows of a
+// step in distinct banks.  Output element (node 4 g + v, unit 16 t + i) is
+// register v of lane l in tile t.  Each output depends on its own node's
+// inputs only, in a fixed order.
 constexpr int L2_NB = 16;
-constexpr int W2_LD = 68;
-__device__ __forceinline__ int unit_of(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
+constexpr int L2_LD = 65;
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) layer2_kernel(int32_t n, const int64_t* __restrict__ row_off,
                                                      const int2* __restrict__ adj, const float* __restrict__ inv_deg,
                                                      const uint16_t* __restrict__ w, const float* __restrict__ pre1,
                                                      float* __restrict__ a2out, float* __restrict__ pre2out,
                                                      float* __restrict__ z)
 {
-    __shared__ float sW[2 * HID * W2_LD];   // row k < 64: A2[k][:], row 64 + k: B2[k][:]
+    __shared__ float sW[2 * HID * L2_LD];   // row k < 64: A2[k][:], row 64 + k: B2[k][:]
     for (int t = threadIdx.x; t < HID * HID; t += blockDim.x) {
         const int k = t / HID, j = t % HID;
-        sW[k * W2_LD + j] = bf(w[OFF_A2 + t]);
-        sW[(HID + k) * W2_LD + j] = bf(w[OFF_B2 + t]);
+        sW[k * L2_LD + j] = bf(w[OFF_A2 + t]);
+        sW[(HID + k) * L2_LD + j] = bf(w[OFF_B2 + t]);
     }
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -234,23 +234,23 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             ag[u] = 0.0f;
         }
         if (i < n) {
-            const float4* hp = reinterpret_cast<const float4*>(pre1 + (size_t)i * HID) + g;
+            const float4* hp = reinterpret_cast<const float4*>(pre1 + (size_t)i * HID + 16 * g);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
-                const float4 v = hp[4 * c];
+                const float4 v = hp[c];
                 hs[4 * c] = relu(v.x); hs[4 * c + 1] = relu(v.y); hs[4 * c + 2] = relu(v.z); hs[4 * c + 3] = relu(v.w);
             }
             int64_t k = row_off[i];
             const int64_t kend = row_off[i + 1];
             for (; k + 2 <= kend; k += 2) {
                 const int2 e0 = adj[k], e1 = adj[k + 1];
-                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID) + g;
-                const float4* p1 = reinterpret_cast<const float4*>(pre1 + (size_t)e1.x * HID) + g;
+                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID + 16 * g);
+                const float4* p1 = reinterpret_cast<const float4*>(pre1 + (size_t)e1.x * HID + 16 * g);
                 float4 v0[4], v1[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    v0[c] = p0[4 * c];
-                    v1[c] = p1[4 * c];
+                    v0[c] = p0[c];
+                    v1[c] = p1[c];
                 }
                 const float w0 = __int_as_float(e0.y), w1 = __int_as_float(e1.y);
 #pragma unroll
@@ -267,11 +267,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             }
             if (k < kend) {
                 const int2 e0 = adj[k];
-                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID) + g;
+                const float4* p0 = reinterpret_cast<const float4*>(pre1 + (size_t)e0.x * HID + 16 * g);
                 const float w0 = __int_as_float(e0.y);
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float4 v = p0[4 * c];
+                    const float4 v = p0[c];
                     ag[4 * c] = fmaf(w0, relu(v.x), ag[4 * c]);
                     ag[4 * c + 1] = fmaf(w0, relu(v.y), ag[4 * c + 1]);
                     ag[4 * c + 2] = fmaf(w0, relu(v.z), ag[4 * c + 2]);
@@ -282,9 +282,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
 #pragma unroll
             for (int u = 0; u < 16; ++u) ag[u] *= id;
             if (a2out) {
-                float4* ap = reinterpret_cast<float4*>(a2out + (size_t)i * HID) + g;
+                float4* ap = reinterpret_cast<float4*>(a2out + (size_t)i * HID + 16 * g);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) ap[4 * c] = make_float4(ag[4 * c], ag[4 * c + 1], ag[4 * c + 2], ag[4 * c + 3]);
+                for (int c = 0; c < 4; ++c) ap[c] = make_float4(ag[4 * c], ag[4 * c + 1], ag[4 * c + 2], ag[4 * c + 3]);
             }
         }
         // dense part, the whole wave
@@ -298,7 +298,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[s], sW[unit_of(g, s) * W2_LD + 16 * t + li], acc[t],
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(hs[s], sW[(16 * g + s) * L2_LD + 16 * t + li], acc[t],
                                                               0, 0, 0);
         }
 #pragma unroll
@@ -307,7 +307,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) l
 #pragma unroll
             for (int t = 0; t < 4; ++t)
                 acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                    ag[s], sW[(HID + unit_of(g, s)) * W2_LD + 16 * t + li], acc[t], 0, 0, 0);
+                    ag[s], sW[(HID + 16 * g + s) * L2_LD + 16 * t + li], acc[t], 0, 0, 0);
         }
         // z = relu(pre2) . c + d: per lane over its 4 tiles, then over the 16
         // lanes of its row group (fixed butterfly)
@@ -773,9 +773,15 @@ __global__ void __launch_bounds__(1024) loss_kernel(const int32_t* __restrict__ 
     if (threadIdx.x == 0) L[b] = s0[0] / (double)(i1 > i0 ? i1 - i0 : 1);
 }
 
+// Units of lane group g in step s: four float4 of a row, 64 contiguous bytes at
+// a time for the four lanes of a node; rows of the weights four apart in
+// distinct banks at a pitch of W2_LD floats.
+constexpr int W2_LD = 68;
+__device__ __forceinline__ int unit_of(int g, int s) { return 16 * (s >> 2) + 4 * g + (s & 3); }
+
 // dpre2 = dz c [pre2 > 0] (formed where it is needed, not stored);
 // dH1 (own term) = dpre2 A2^T, da2s = (dpre2 B2^T) / max(deg, 1), on the matrix
-// cores as layer 2 (same lane layout, the transposed weights in LDS).  Bound
+// cores, sixteen nodes per wave as layer 2 (the transposed weights in LDS).  Bound
 // by its three 256-byte rows per node: 135 k nodes take 42 us (2.5 TB/s);
 // with a broadcast and two multiply-adds per (unit, unit) it took 114 us.
 __global__ void __launch_bounds__(256) back2_kernel(int32_t n, const float* __restrict__ inv_deg,
