@@ -240,9 +240,9 @@ fem_status fem_set_adam_state(fem_solver* s, const float* h, const float* m1, co
  * evaluated at h(t). */
 fem_status fem_step(fem_solver* s, int32_t n_steps);
 /* Enqueue the remaining steps up to T as one captured HIP graph (replayed on
- * later calls from the same t).  Small MaxCut and Max-k-SAT instances run
- * whole ranges of steps in one kernel instead, each replica on one compute
- * unit, whatever call enqueues them; a solver of nothing else needs no graph.
+ * later calls from the same t).  MaxCut and Max-k-SAT problems whose instances
+ * are all small run whole ranges of steps in one kernel instead, each replica
+ * on one compute unit, whatever call enqueues them, and need no graph.
  * Their tables (a re-ordered copy of the adjacency and about 100 bytes per
  * step) are device memory of the solver. */
 fem_status fem_run(fem_solver* s);
@@ -330,10 +330,9 @@ fem_status fem_set_state(fem_solver* s, const void* buf, size_t bytes);
  * segments of the same rows, so that each XCD (workgroups are dealt to the
  * eight XCDs round-robin) gathers from its own columns of the marginal copy.
  * fem_get_tile reports the lanes actually used.  All shapes give
- * bit-identical fields.  A solver starts with its small MaxCut and Max-k-SAT
- * instances on kernels that no launch shape applies to (fem_run);
- * fem_set_tile puts every instance on the shaped kernels, with the same
- * fields. */
+ * bit-identical fields.  The solver of a problem of small MaxCut or Max-k-SAT
+ * instances starts on kernels that no launch shape applies to (fem_run);
+ * fem_set_tile puts it on the shaped kernels, with the same fields. */
 typedef struct {
     int32_t vec, waves, rows, nt, lanes;
 } fem_tile;
@@ -341,7 +340,7 @@ fem_status fem_get_tile(const fem_solver* s, fem_tile* t);
 fem_status fem_set_tile(fem_solver* s, const fem_tile* t);
 /* Autotune: time every valid shape twice for trial_steps steps from the same
  * state (restored afterwards), keep the shape with the fastest run (the one
- * it has, untimed, where no instance uses it), and cache it on disk under the key (kind, n,
+ * it has, untimed, where the solver is not on these kernels), and cache it on disk under the key (kind, n,
  * nnz, R, q, dtype, instances, energies on/off, gradient mode) in
  * $FEM_TUNE_CACHE (default ~/.cache/femx/tune.txt).  use_cache = 1 returns a
  * cached choice without timing: the user's cache first, then the shapes
