@@ -1469,8 +1469,8 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
 #undef ALLOC
     e = hipMemcpy(s->d_wtot, p.inst_wtot.data(), sizeof(double) * s->n_inst, hipMemcpyHostToDevice);
     if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
-    if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS && IR <= ((size_t)1 << 30)) {   // a grid of IR blocks
-        if (resident_choose(p, P.eval_every, s->res)) {
+    if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS) {
+        if (resident_choose(p, s->R, P.eval_every, s->res)) {
             std::vector<ResStep> steps((size_t)P.steps + 1);   // read one step ahead
             for (int t = 0; t < P.steps; ++t) steps[(size_t)t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
             e = resident_build(p, steps, s->res);

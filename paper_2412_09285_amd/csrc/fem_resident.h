@@ -89,7 +89,7 @@ struct ResArgs {
 
 // Says whether a solver's instances are resident (the rule and its
 // measurements stand at the definition) and starts r.
-bool resident_choose(const Problem& p, int eval_every, ResData& r);
+bool resident_choose(const Problem& p, int R, int eval_every, ResData& r);
 // Builds the device structure; steps: host table of T + 1 entries.
 hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r);
 void resident_free(ResData& r);

@@ -497,7 +497,9 @@ void resident_free(ResData& r)
 // R = 512 24 / 31, 29 / 35 and 29 / 46 us; beyond, one compute unit reads for
 // longer than the whole chip needs.  Eight rows per thread are instantiated
 // only where they fit the registers: +-1 weights, entries in LDS.
-bool resident_choose(const Problem& p, int eval_every, ResData& r)
+// A launch has a workgroup per (instance, replica), and HIP takes fewer than
+// 2^32 threads.
+bool resident_choose(const Problem& p, int R, int eval_every, ResData& r)
 {
     const bool sat = p.kind == KIND_MAXSAT;
     int dev_lds = 0;
@@ -510,9 +512,11 @@ bool resident_choose(const Problem& p, int eval_every, ResData& r)
         if ((uint32_t)p.h_adj[k].y & 0x80000000u) r.planes = 2;
     r.dev_lds = (size_t)dev_lds;
     r.all = true;
+    uint64_t threads = 0;
     for (int b = 0; b < p.n_inst && r.all; ++b) {
         const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
-        r.all = plan.ok && !(plan.rpt == 8 && eval_every > 0 && eval_every < 16);
+        threads += (uint64_t)plan.threads * (uint64_t)R;
+        r.all = plan.ok && !(plan.rpt == 8 && eval_every > 0 && eval_every < 16) && threads <= UINT32_MAX;
     }
     if (!r.all) r = ResData{};
     return r.all;

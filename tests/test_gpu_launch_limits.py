@@ -1,0 +1,31 @@
+"""Calls whose natural grid would pass a limit of a launch (2^32 threads, 65535
+blocks along y): they run, and give what small grids give."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_09285_amd import fem
+
+pytestmark = pytest.mark.gpu
+
+
+def pair():
+    return fem.Problem.maxcut(2, [0], [1], [1.0])
+
+
+def test_one_workgroup_per_replica_of_many():
+    """17 instances of two nodes with 4,194,240 replicas: a workgroup of 64
+    threads for each (instance, replica) would be 2^32 threads and more."""
+    batch = fem.Problem.batch([pair() for _ in range(17)])
+    R = 65535 * 64
+    h0 = torch.randn(batch.n, R, device="cuda", generator=torch.Generator("cuda").manual_seed(1)) * 0.5
+    out = []
+    for problem, h in ((batch, h0), (pair(), h0[:2, :64].contiguous())):
+        s = fem.Solver(problem, fem.default_params(replicas=h.shape[1], steps=10, energy_every=0))
+        s.set_fields(h)
+        s.step(3)
+        out.append(s.fields(torch.empty_like(h)))
+        s.sync()
+        s.close()
+    assert torch.equal(out[0][:2, :64], out[1])
+    assert torch.isfinite(out[0]).all() and not torch.equal(out[0][32:], h0[32:])
