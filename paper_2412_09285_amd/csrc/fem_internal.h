@@ -280,12 +280,13 @@ struct FinishArgs {
     double lam, beta;
     double scale;                 // 2^-40 for fixed-point marginal sums, 1 for state counts
     int32_t kind, R, q;
+    uint32_t first;               // first workgroup of this launch (of every instance's replica groups)
 };
 // epart and cpart (cols 0: absent) summed per chunk of tiles
 hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart, int ccols, const int32_t* chunk_off,
                          int n_chunks, double* esum, long long* csum, hipStream_t st);
 // max_tiles: most tiles (or chunks) of one instance
-hipError_t launch_finish(const FinishArgs& a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st);
+hipError_t launch_finish(FinishArgs a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st);
 // manipulated gradients (fem_manip.hip): the step kernel, and the read-out copy
 // of a.h (sign bits or argmax states, with per-tile state counts for bMinCut)
 hipError_t launch_manip_step(int kind, int vec, bool nt, const LaunchGeom& g, int waves, const StepArgs& a,

@@ -752,7 +752,8 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
     const int tid = threadIdx.x;
     const int G = COL ? (a.q < FINISH_COLS ? FINISH_COLS / a.q : 1) : FINISH_COLS;   // replicas
     const int groups = (a.R + G - 1) / G;
-    const int inst = blockIdx.x / groups, r0 = (blockIdx.x % groups) * G;
+    const uint32_t block = a.first + blockIdx.x;
+    const int inst = block / groups, r0 = (block % groups) * G;
     int t0 = a.inst_chunk_off[inst], t1 = a.inst_chunk_off[inst + 1];
     if (a.chunk_off) {   // tiles, not chunk sums
         t0 = a.chunk_off[t0];
@@ -1252,18 +1253,24 @@ hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart,
     return hipGetLastError();
 }
 
-hipError_t launch_finish(const FinishArgs& a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st)
+hipError_t launch_finish(FinishArgs a, int n_inst, int max_tiles, bool energies, bool columns, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
     const int G = columns ? (a.q < FINISH_COLS ? FINISH_COLS / a.q : 1) : FINISH_COLS;
-    const unsigned grid = (unsigned)n_inst * (unsigned)((a.R + G - 1) / G);
+    const uint64_t blocks = (uint64_t)n_inst * ((a.R + G - 1) / G);
     // a row of threads per tile of the largest instance, as far as they go
     int threads = FINISH_THREADS;
     const int cols = columns ? G * a.q : G;
     while (threads > 64 && threads / 2 >= pow2ceil(max_tiles) * cols) threads >>= 1;
-    if (columns && energies) finish_kernel<3, true><<<grid, threads, 0, st>>>(a);
-    else if (columns) finish_kernel<0, true><<<grid, threads, 0, st>>>(a);
-    else if (energies) finish_kernel<2, false><<<grid, threads, 0, st>>>(a);
+    // HIP takes fewer than 2^32 threads a launch
+    const unsigned most = UINT32_MAX / (unsigned)threads;
+    for (uint64_t first = 0; first < blocks; first += most) {
+        const unsigned grid = (unsigned)(blocks - first < most ? blocks - first : most);
+        a.first = (uint32_t)first;
+        if (columns && energies) finish_kernel<3, true><<<grid, threads, 0, st>>>(a);
+        else if (columns) finish_kernel<0, true><<<grid, threads, 0, st>>>(a);
+        else if (energies) finish_kernel<2, false><<<grid, threads, 0, st>>>(a);
+    }
     return hipGetLastError();
 }
 

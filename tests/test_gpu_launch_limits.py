@@ -29,3 +29,25 @@ def test_one_workgroup_per_replica_of_many():
         s.close()
     assert torch.equal(out[0][:2, :64], out[1])
     assert torch.isfinite(out[0]).all() and not torch.equal(out[0][32:], h0[32:])
+
+
+def test_energies_of_many_instances_beside_a_large_one():
+    """4,196,352 instances of two nodes and one of 140,000 (more than 128 tiles):
+    a workgroup of 1024 threads per instance would be 2^32 threads and more."""
+    many = fem.Problem.batch([pair()] * 2048)
+    m = 140000
+    path = fem.Problem.maxcut(m, np.arange(m - 1), np.arange(1, m), np.ones(m - 1, np.float32))
+    batch = fem.Problem.batch([many] * 2049 + [path])
+    h0 = torch.full((batch.n, 1), 0.25, device="cuda")
+    out = []
+    for problem, h in ((batch, h0), (pair(), h0[:2].contiguous()), (path, h0[:m].contiguous())):
+        s = fem.Solver(problem, fem.default_params(replicas=1, steps=10))
+        s.set_tile(1, 4, 4)
+        s.set_fields(h)
+        s.step(2)
+        out.append(s.energies())
+        s.close()
+    for all_, one, last in zip(*out):
+        # sums of two terms, and of some 10^5: float32 terms of one sign
+        assert np.abs(all_[:-1] - one[0]).max() <= 4 * 2.0 ** -24 * np.abs(one[0]).max()
+        assert np.abs(all_[-1] - last[0]).max() <= 8 * 2.0 ** -24 * np.abs(last[0]).max()
