@@ -747,30 +747,32 @@ inf_layer2_kernel(int32_t n, int32_t R, const int64_t* __restrict__ row_off, con
 // ------------------------------------------------------------ training ----
 __device__ __forceinline__ float softplusf(float x) { return fmaxf(x, 0.0f) + log1pf(expf(-fabsf(x))); }
 
-// per instance (one workgroup): L = mean softplus(z) - y z, and
+// per instance (one workgroup at a time): L = mean softplus(z) - y z, and
 // dz_i = (sigmoid(z_i) - y_i) / (N_b B)
 __global__ void __launch_bounds__(1024) loss_kernel(const int32_t* __restrict__ inst_off, int32_t B,
                                                     const float* __restrict__ z, const int32_t* __restrict__ y,
                                                     float* __restrict__ dz, double* __restrict__ L)
 {
     __shared__ double s0[1024];
-    const int b = blockIdx.x;
-    const int i0 = inst_off[b], i1 = inst_off[b + 1];
-    const float nb = (float)(i1 - i0);
-    double a0 = 0.0;
-    for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
-        const float zi = z[i], yi = (float)y[i];
-        a0 += (double)(softplusf(zi) - yi * zi);
-        const float sg = 1.0f / (1.0f + expf(-zi));
-        dz[i] = (sg - yi) / (nb * (float)B);
-    }
-    s0[threadIdx.x] = a0;
-    __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) s0[threadIdx.x] += s0[threadIdx.x + s];
+    for (int b = blockIdx.x; b < B; b += gridDim.x) {
+        const int i0 = inst_off[b], i1 = inst_off[b + 1];
+        const float nb = (float)(i1 - i0);
+        double a0 = 0.0;
+        for (int i = i0 + threadIdx.x; i < i1; i += blockDim.x) {
+            const float zi = z[i], yi = (float)y[i];
+            a0 += (double)(softplusf(zi) - yi * zi);
+            const float sg = 1.0f / (1.0f + expf(-zi));
+            dz[i] = (sg - yi) / (nb * (float)B);
+        }
+        s0[threadIdx.x] = a0;
         __syncthreads();
+        for (int s = 512; s > 0; s >>= 1) {
+            if ((int)threadIdx.x < s) s0[threadIdx.x] += s0[threadIdx.x + s];
+            __syncthreads();
+        }
+        if (threadIdx.x == 0) L[b] = s0[0] / (double)(i1 > i0 ? i1 - i0 : 1);
+        __syncthreads();   // s0 is the next instance's
     }
-    if (threadIdx.x == 0) L[b] = s0[0] / (double)(i1 > i0 ? i1 - i0 : 1);
 }
 
 // Units of lane group g in step s: four float4 of a row, 64 contiguous bytes at
@@ -1267,7 +1269,7 @@ fem_status fem_mpnn_train_step(fem_mpnn* m, const fem_problem* fp, const float* 
     s = forward(m, p, m->state, 1, seed, draw0, true, nullptr);
     if (s != FEM_OK) return s;
     (void)hipGetLastError();
-    loss_kernel<<<B, 1024>>>(p.inst_off_d, B, m->z, m->y, m->dz, m->L);
+    loss_kernel<<<std::min(B, 1 << 16), 1024>>>(p.inst_off_d, B, m->z, m->y, m->dz, m->L);
     back2_kernel<<<grid_rows((n + L2_NB - 1) / L2_NB, 4), 256>>>(n, m->inv_deg, m->wbf, m->dz, m->pre2, m->dh1s,
                                                                 m->da2s);
     back1_kernel<<<grid_rows((n + 3) / 4, 4), 256>>>(n, p.row_off, p.adj, m->pre1, m->dh1s, m->da2s, m->dpre1);

@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from paper_2412_09285_amd import fem
+from paper_2412_09285_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -51,3 +52,21 @@ def test_energies_of_many_instances_beside_a_large_one():
         # sums of two terms, and of some 10^5: float32 terms of one sign
         assert np.abs(all_[:-1] - one[0]).max() <= 4 * 2.0 ** -24 * np.abs(one[0]).max()
         assert np.abs(all_[-1] - last[0]).max() <= 8 * 2.0 ** -24 * np.abs(last[0]).max()
+
+
+def test_training_on_millions_of_instances():
+    """4,196,352 instances of one node: a workgroup of 1024 threads each would be
+    2^32 threads and more.  Without neighbours the loss is a function of the
+    logits alone, which the forward pass gives."""
+    one = fem.Problem.maxcut(1, [], [])
+    batch = fem.Problem.batch([fem.Problem.batch([one] * 2048)] * 2049)
+    rng = np.random.default_rng(1)
+    state = rng.standard_normal(batch.n).astype(np.float32)
+    y = rng.integers(0, 2, batch.n).astype(np.int32)
+    net = fem.MPNN(W.mpnn_init_weights(3))
+    z = net.forward(batch, state, seed=5, draw=1).astype(np.float64)
+    loss, g = net.train_step(batch, state, y, seed=5, draw0=1, lr=1e-3, want_grad=True)
+    assert abs(loss - np.mean(np.logaddexp(0.0, z) - y * z)) <= 1e-5 * loss
+    # d: the sum of dz over all nodes, float32 partial sums of some 2000 rows
+    dz = (1.0 / (1.0 + np.exp(-z)) - y) / batch.n
+    assert abs(g[-1] - dz.sum()) <= 2000 * 2.0 ** -24 * np.abs(dz).sum()
