@@ -1224,7 +1224,7 @@ __global__ void __launch_bounds__(256) chunk_kernel(const double* __restrict__ e
                                                     long long* __restrict__ csum)
 {
     __shared__ double lds[256];
-    const int eblocks = (ecols + 31) / 32;
+    const int eblocks = (ecols + 31) / 32, blocks = eblocks + (ccols + 31) / 32;
     const int t0 = chunk_off[blockIdx.x], t1 = chunk_off[blockIdx.x + 1], sub = threadIdx.x >> 5;
     auto sum = [&](const auto* part, int cols, int c, auto* out, auto* l) {
         typename std::remove_pointer<decltype(out)>::type acc = 0;
@@ -1240,15 +1240,21 @@ __global__ void __launch_bounds__(256) chunk_kernel(const double* __restrict__ e
         }
     };
     const int c = (int)(threadIdx.x & 31);
-    if ((int)blockIdx.y < eblocks) sum(epart, ecols, (int)blockIdx.y * 32 + c, esum, lds);
-    else sum(cpart, ccols, ((int)blockIdx.y - eblocks) * 32 + c, csum, reinterpret_cast<long long*>(lds));
+    for (int k = blockIdx.y; k < blocks; k += gridDim.y) {
+        if (k < eblocks) sum(epart, ecols, k * 32 + c, esum, lds);
+        else sum(cpart, ccols, (k - eblocks) * 32 + c, csum, reinterpret_cast<long long*>(lds));
+        __syncthreads();   // lds is the next columns'
+    }
 }
 
 hipError_t launch_chunks(const double* epart, int ecols, const long long* cpart, int ccols, const int32_t* chunk_off,
                          int n_chunks, double* esum, long long* csum, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
-    const dim3 g(n_chunks, (ecols + 31) / 32 + (ccols + 31) / 32);
+    // a grid has at most 65535 blocks along y; both arrays of R replicas take
+    // (3 + q) R / 32
+    const int blocks = (ecols + 31) / 32 + (ccols + 31) / 32;
+    const dim3 g(n_chunks, blocks < 4096 ? blocks : 4096);
     chunk_kernel<<<g, 256, 0, st>>>(epart, ecols, cpart, ccols, chunk_off, esum, csum);
     return hipGetLastError();
 }

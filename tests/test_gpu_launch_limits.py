@@ -70,3 +70,23 @@ def test_training_on_millions_of_instances():
     # d: the sum of dz over all nodes, float32 partial sums of some 2000 rows
     dz = (1.0 / (1.0 + np.exp(-z)) - y) / batch.n
     assert abs(g[-1] - dz.sum()) <= 2000 * 2.0 ** -24 * np.abs(dz).sum()
+
+
+def test_column_blocks_of_the_chunk_sums():
+    """1030 tiles, so that chunks are summed first, and 27000 replicas: more
+    column blocks of energies and column sums than the launch has workgroups along y."""
+    n, R, q = 1030, 27000, 2
+    prob = fem.Problem.bmincut(n, np.arange(n - 1), np.arange(1, n), np.ones(n - 1, np.float32), q)
+    h0 = torch.randn(n, R, q, device="cuda", generator=torch.Generator("cuda").manual_seed(2)) * 0.3
+    out = []
+    for r0, r1 in ((0, R), (R - 64, R)):
+        h = h0[:, r0:r1].contiguous()
+        s = fem.Solver(prob, fem.default_params(replicas=r1 - r0, steps=10, lam=0.01))
+        s.set_tile(q, 1, 1)
+        s.set_fields(h)
+        s.step(3)
+        out.append((s.fields(torch.empty_like(h)).cpu().numpy(), s.energies()))
+        s.close()
+    assert np.array_equal(out[0][0][:, -64:], out[1][0])
+    for all_, some in zip(out[0][1], out[1][1]):
+        assert np.allclose(all_[:, -64:], some, rtol=1e-12, atol=0)   # double sums of the same double terms
