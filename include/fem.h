@@ -242,7 +242,9 @@ fem_status fem_step(fem_solver* s, int32_t n_steps);
 /* Enqueue the remaining steps up to T as one captured HIP graph (replayed on
  * later calls from the same t).  MaxCut and Max-k-SAT problems whose instances
  * are all small run whole ranges of steps in one kernel instead, each replica
- * on one compute unit, whatever call enqueues them, and need no graph.
+ * on one compute unit, whatever call enqueues them, and need no graph; ranges
+ * (or stretches between read-outs) of a few steps take the shaped kernels
+ * there too, with the same fields.
  * Their tables (a re-ordered copy of the adjacency and about 100 bytes per
  * step) are device memory of the solver. */
 fem_status fem_run(fem_solver* s);

@@ -435,6 +435,8 @@ struct fem_solver {
     TileSet ts;
     // replicas that run on one compute unit each (fem_resident.hip)
     ResData res;
+    bool marg_ok = false;     // the marginal copy is that of the fields: resident steps leave it behind
+    bool always_res = false;  // its steps are part of a caller's graph, which moves the fields unseen
     // Side streams for the resident classes after the first, which run beside
     // it within a range of steps.
     static constexpr int N_SIDE = 2;
@@ -839,6 +841,7 @@ static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_so
     a.t1 = t_end;
     a.bf16 = s->dtype == FEM_BF16;
     const int classes = (int)s->res.classes.size();
+    s->marg_ok = false;
     STCHK(profile_begin(s, t_end - s->t, &s->res_end));
     if (s->fork) HIPCHK(hipEventRecord(s->fork, s->stream));
     for (int c = 0; c < classes; ++c) {
@@ -867,6 +870,21 @@ static fem_status join_side(fem_solver* s, const bool (&joined)[fem_solver::N_SI
     return FEM_OK;
 }
 
+// Whether the steps up to t_end are resident: ranges, or stretches between
+// read-outs, that are long enough (resident_choose).  Steps that a caller
+// captures are always: their replays find no marginal copy to rely on.
+static bool takes_resident(fem_solver* s, int t_end)
+{
+    if (!s->res.all) return false;
+    int steps = t_end - s->t;
+    if (s->prm.eval_every > 0) steps = std::min(steps, s->prm.eval_every);
+    if (steps >= s->res.min_steps || s->always_res) return true;
+    if (!s->stream || s->capturing) return false;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive) s->always_res = true;
+    return s->always_res;
+}
+
 // One step of the row-tiled kernels.
 static fem_status tiled_step(fem_solver* s)
 {
@@ -889,20 +907,24 @@ static fem_status tiled_step(fem_solver* s)
     return finish(s, en ? t : -1);
 }
 
+static fem_status init_marginals(fem_solver* s, const float* src = nullptr);
+
 // Enqueues the steps up to t_end: the stretch to the next read-out at a time,
 // resident instances all of it in one launch, others step by step.
 static fem_status do_steps(fem_solver* s, int t_end)
 {
+    const bool resident = takes_resident(s, t_end);
+    if (!resident && !s->marg_ok) STCHK(init_marginals(s));
     while (s->t < t_end) {
         int e = t_end;
         if (s->prm.eval_every > 0) e = std::min(e, (s->t / s->prm.eval_every + 1) * s->prm.eval_every);
         bool joined[fem_solver::N_SIDE] = {};
-        if (s->res.all) STCHK(resident_steps(s, e, joined));
+        if (resident) STCHK(resident_steps(s, e, joined));
         for (; s->t < e; ++s->t) {
-            if (!s->res.all) STCHK(tiled_step(s));
+            if (!resident) STCHK(tiled_step(s));
             if (energy_due(s, s->t)) s->last_energy_step = s->t;
         }
-        if (s->res.all) STCHK(join_side(s, joined));
+        if (resident) STCHK(join_side(s, joined));
         if (eval_due(s, s->t)) STCHK(readout_eval(s, true));
     }
     return FEM_OK;
@@ -916,9 +938,8 @@ static bool sets_fields(const fem_solver* s)
     return !s->res.all && !s->manip;
 }
 
-static fem_status init_marginals(fem_solver* s, const float* src = nullptr)
+static fem_status init_marginals(fem_solver* s, const float* src)
 {
-    if (s->res.all) return FEM_OK;   // resident instances form theirs from the fields
     StepArgs a = base_args(s);
     a.marg_nxt = s->marg[s->t & 1];
     if (s->manip)
@@ -927,7 +948,17 @@ static fem_status init_marginals(fem_solver* s, const float* src = nullptr)
         HIPCHK(launch_dense_i8_init(*s->prob, a, src, s->stream));
     else
         HIPCHK(launch_init_marginals(s->kind, s->dtype, s->geo, s->shape.waves, a, src, s->stream));
-    return finish(s, -1);
+    STCHK(finish(s, -1));
+    s->marg_ok = true;
+    return FEM_OK;
+}
+
+// After new fields: resident steps form their marginals from them, and
+// row-tiled ones of such a solver form the copy when they come.
+static fem_status new_fields(fem_solver* s)
+{
+    s->marg_ok = false;
+    return s->res.all ? FEM_OK : init_marginals(s);
 }
 
 static fem_status reset_best(fem_solver* s)
@@ -1470,7 +1501,7 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     e = hipMemcpy(s->d_wtot, p.inst_wtot.data(), sizeof(double) * s->n_inst, hipMemcpyHostToDevice);
     if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
     if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS) {
-        if (resident_choose(p, s->R, P.eval_every, s->res)) {
+        if (resident_choose(p, s->R, s->manip, P.eval_every, s->res)) {
             std::vector<ResStep> steps((size_t)P.steps + 1);   // read one step ahead
             for (int t = 0; t < P.steps; ++t) steps[(size_t)t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
             e = resident_build(p, steps, s->res);
@@ -1562,7 +1593,7 @@ fem_status fem_set_fields(fem_solver* s, const float* h, int on_device)
             HIPCHK(copy_state_rows(s, s->h, true, h, hipMemcpyHostToDevice));
             HIPCHK(launch_rows(s->n, rq, nullptr, s->srow, nullptr, rq, s->m1, s->m2, s->stream));
         }
-        STCHK(init_marginals(s));
+        STCHK(new_fields(s));
     }
     STCHK(reset_best(s));
     HIPCHK(hipStreamSynchronize(s->stream));   // the caller's array is read inside the call
@@ -1582,7 +1613,7 @@ fem_status fem_set_adam_state(fem_solver* s, const float* h, const float* m1, co
     HIPCHK(copy_state_rows(s, s->m2, true, m2, kd));
     s->t = t;
     s->last_energy_step = -1;
-    STCHK(init_marginals(s));
+    STCHK(new_fields(s));
     HIPCHK(hipStreamSynchronize(s->stream));
     s->fields_set = true;
     return FEM_OK;
@@ -1599,7 +1630,35 @@ fem_status fem_step(fem_solver* s, int32_t n_steps)
     return do_steps(s, s->t + n_steps);
 }
 
-fem_status fem_capture(fem_solver* s, int32_t t_end);
+// The graph of the row-tiled steps [t, t_end), if there is none yet.
+static fem_status capture_range(fem_solver* s, int t_end)
+{
+    if (s->graphs.count(std::make_pair((int)s->t, t_end))) return FEM_OK;
+    const int t0 = s->t;
+    const int last = s->last_energy_step;
+    const bool marg_ok = s->marg_ok;
+    HIPCHK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
+    s->capturing = true;
+    s->marg_ok = true;   // formed ahead of every launch of the graph
+    fem_status st = do_steps(s, t_end);
+    s->marg_ok = marg_ok;
+    s->capturing = false;
+    s->t = t0;
+    s->last_energy_step = last;
+    hipGraph_t g = nullptr;
+    hipError_t e = hipStreamEndCapture(s->stream, &g);
+    if (st != FEM_OK) {
+        if (g) (void)hipGraphDestroy(g);
+        return st;
+    }
+    if (e != hipSuccess) return fail(FEM_E_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+    hipGraphExec_t ge = nullptr;
+    e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
+    (void)hipGraphDestroy(g);
+    if (e != hipSuccess) return fail(FEM_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
+    s->graphs.emplace(std::make_pair(t0, t_end), ge);
+    return FEM_OK;
+}
 
 fem_status fem_run_until(fem_solver* s, int32_t t_end)
 {
@@ -1612,8 +1671,9 @@ fem_status fem_run_until(fem_solver* s, int32_t t_end)
     const int t0 = s->t;
     // graph capture needs a non-null stream: run eagerly on the null stream;
     // resident steps are a launch or two per range and need no graph
-    if (!s->stream || s->res.all) return do_steps(s, t_end);
-    STCHK(fem_capture(s, t_end));
+    if (!s->stream || takes_resident(s, t_end)) return do_steps(s, t_end);
+    if (!s->marg_ok) STCHK(init_marginals(s));
+    STCHK(capture_range(s, t_end));
     auto it = s->graphs.find(std::make_pair(t0, (int)t_end));
     HIPCHK(hipGraphLaunch(it->second, s->stream));
     s->t = t_end;
@@ -1634,29 +1694,9 @@ fem_status fem_capture(fem_solver* s, int32_t t_end)
     if (t_end < s->t || t_end > s->prm.steps)
         return fail(FEM_E_STATE, "t_end %d outside [%d, %d]", t_end, s->t, s->prm.steps);
     if (!s->stream) return fail(FEM_E_STATE, "graph capture needs a non-null stream");
-    if (t_end == s->t || s->res.all || s->graphs.count(std::make_pair((int)s->t, (int)t_end))) return FEM_OK;
+    if (t_end == s->t) return FEM_OK;
     HIPCHK(hipSetDevice(s->prob->device));
-    const int t0 = s->t;
-    const int last = s->last_energy_step;
-    HIPCHK(hipStreamBeginCapture(s->stream, hipStreamCaptureModeThreadLocal));
-    s->capturing = true;
-    fem_status st = do_steps(s, t_end);
-    s->capturing = false;
-    s->t = t0;
-    s->last_energy_step = last;
-    hipGraph_t g = nullptr;
-    hipError_t e = hipStreamEndCapture(s->stream, &g);
-    if (st != FEM_OK) {
-        if (g) (void)hipGraphDestroy(g);
-        return st;
-    }
-    if (e != hipSuccess) return fail(FEM_E_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-    hipGraphExec_t ge = nullptr;
-    e = hipGraphInstantiate(&ge, g, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(g);
-    if (e != hipSuccess) return fail(FEM_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    s->graphs.emplace(std::make_pair(t0, (int)t_end), ge);
-    return FEM_OK;
+    return takes_resident(s, t_end) ? FEM_OK : capture_range(s, t_end);
 }
 
 fem_status fem_run(fem_solver* s)
@@ -1926,7 +1966,7 @@ fem_status fem_set_state(fem_solver* s, const void* buf, size_t bytes)
     HIPCHK(hipMemcpyAsync(s->best, p + 3 * s->vals * 4, (size_t)s->n_inst * s->R * 8, hipMemcpyHostToDevice, s->stream));
     s->t = hd.t;
     s->last_energy_step = -1;
-    STCHK(init_marginals(s));
+    STCHK(new_fields(s));
     HIPCHK(hipStreamSynchronize(s->stream));
     s->fields_set = true;
     return FEM_OK;
@@ -1963,9 +2003,9 @@ static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool take_over)
     take_over = take_over && s->res.all;
     if (take_over) resident_free(s->res);
     STCHK(setup_tiling(s, sh));
-    // column-sum partials are laid out per tile, and resident instances keep
-    // no marginal copy: rebuild them
-    if (s->fields_set && (s->kind == KIND_BMINCUT || take_over)) STCHK(init_marginals(s));
+    // column-sum partials are laid out per tile, and resident instances may
+    // have left the marginal copy behind: rebuild them
+    if (s->fields_set && (s->kind == KIND_BMINCUT || (take_over && !s->marg_ok))) STCHK(init_marginals(s));
     return FEM_OK;
 }
 
@@ -2063,7 +2103,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
         if (!save) {
             s->t = t_save;
             s->last_energy_step = -1;
-            STCHK(init_marginals(s));
+            STCHK(new_fields(s));
         }
         HIPCHK(hipStreamSynchronize(s->stream));
         return FEM_OK;

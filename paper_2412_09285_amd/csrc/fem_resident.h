@@ -54,6 +54,7 @@ struct ResData {
     bool pm1 = false;             // graphs: weights +-1, carried in the entries
     size_t dev_lds = 0;           // LDS a workgroup may use
     int planes = 1;               // values per position that neighbours read
+    int min_steps = 1;            // shorter ranges are faster on the row-tiled kernels
     void* block = nullptr;        // device: the one allocation behind the tables
     ResInst* inst = nullptr;
     int32_t* perm = nullptr;      // position -> global row, -1 for padding
@@ -89,7 +90,7 @@ struct ResArgs {
 
 // Says whether a solver's instances are resident (the rule and its
 // measurements stand at the definition) and starts r.
-bool resident_choose(const Problem& p, int R, int eval_every, ResData& r);
+bool resident_choose(const Problem& p, int R, bool manip, int eval_every, ResData& r);
 // Builds the device structure; steps: host table of T + 1 entries.
 hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r);
 void resident_free(ResData& r);

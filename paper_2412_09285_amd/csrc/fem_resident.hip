@@ -32,6 +32,7 @@
 #include <numeric>
 
 #include "fem_device.h"
+#include "fem_readout.h"
 
 namespace fem {
 
@@ -487,9 +488,7 @@ void resident_free(ResData& r)
 // each of its instances is: beside row-tiled instances a resident one saves no
 // launch (R = 20, bfloat16, 2000 and 11361 nodes: 457 us for 24 steps, both
 // row-tiled 368; sixty-four of 1000 .. 50000 nodes at R = 32: 4035 and 3869 for
-// 25).  Eight rows per thread take too long to set up again after every
-// read-out if these come within 16 steps (8000 nodes of degree 3, R = 20, every
-// 10 steps: 306 / 252; without read-outs, R = 64: 214 / 275).
+// 25).
 // In LDS it won at every size measured (the table above).  Streaming, at
 // R = 16, resident against the best row-tiled shape: n = 2000 of degree 100
 // (51 k entries of 8 bytes) 11.4 / 12.5 us, n = 2000 of degree 120 (61 k)
@@ -499,7 +498,28 @@ void resident_free(ResData& r)
 // only where they fit the registers: +-1 weights, entries in LDS.
 // A launch has a workgroup per (instance, replica), and HIP takes fewer than
 // 2^32 threads.
-bool resident_choose(const Problem& p, int R, int eval_every, ResData& r)
+//
+// Every launch loads the state (a cache line for each float of it) and the
+// entries again, so short ranges, of the caller or between read-outs, stay
+// row-tiled.  us a step of ranges of 1, 2, 4, 8 and 16 steps, resident, and
+// row-tiled at any of them:
+//   n =  200, degree 20, R =  64:   5.8   3.8   2.6   1.9   1.7    8.3
+//   n =  800, degree 48, R = 512:  24.2  15.1  10.5   8.4   7.3   14.8
+//   n = 2000, degree 20, R =  16:  16.0   9.9   6.8   5.1   4.3    9.0
+//   n = 2000, degree 20, R = 512:  41.3  24.1  15.4  11.2   9.1   16.3
+//   n = 4000, degree  6, R =  16:  25.6  14.9   9.4   6.7   5.3    9.5
+//   n = 4000, 16800 clauses, 16:   29.6  19.3  14.3  11.5  10.1   10.8
+//   n = 8000, degree  3, R =  16:  46.6  26.9  16.6  11.7   9.1   10.5
+//   n = 8000, degree  3, R = 256:  69.6  38.3  22.7  14.8  11.0   22.6
+// so one step where the workgroup is not the largest, else one for each row of
+// a thread, and two where the replicas do not fill the chip or are more than it
+// holds (n = 4000, degree 6, R = 64: 27.7 15.7 10.2 7.0 5.4, row-tiled 12.6); twice
+// as many with manipulated gradients, whose row-tiled kernels gather bits (n =
+// 2000, R = 16: 16.6 9.7 6.4 4.7 3.9, row-tiled 5.7).  Several classes cost a fork and a join besides (20 instances of 40 .. 5000 nodes, R =
+// 50: 54.8 34 23 18.5 16.9, row-tiled 16), and a read-out by bytes is five
+// launches that a graph replays faster (67 nodes, real weights, R = 1, every
+// step: 19.4 / 13).
+bool resident_choose(const Problem& p, int R, bool manip, int eval_every, ResData& r)
 {
     const bool sat = p.kind == KIND_MAXSAT;
     int dev_lds = 0;
@@ -512,12 +532,22 @@ bool resident_choose(const Problem& p, int R, int eval_every, ResData& r)
         if ((uint32_t)p.h_adj[k].y & 0x80000000u) r.planes = 2;
     r.dev_lds = (size_t)dev_lds;
     r.all = true;
+    r.min_steps = eval_every > 0 && !bit_evaluation(p) ? 4 : 1;
     uint64_t threads = 0;
+    ResPlan first;
     for (int b = 0; b < p.n_inst && r.all; ++b) {
         const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
+        if (b == 0) first = plan;
         threads += (uint64_t)plan.threads * (uint64_t)R;
-        r.all = plan.ok && !(plan.rpt == 8 && eval_every > 0 && eval_every < 16) && threads <= UINT32_MAX;
+        if (plan.threads == 1024) {
+            const bool fits = R <= 256 && (R >= (manip ? 128 : 64) || (plan.rpt == 1 && !manip));
+            r.min_steps = std::max(r.min_steps, (fits ? 1 : 2) * (manip ? 2 : 1) * plan.rpt);
+        }
+        if (plan.threads != first.threads || plan.rpt != first.rpt || plan.adj_lds != first.adj_lds)
+            r.min_steps = std::max(r.min_steps, 8);   // more than one class
+        r.all = plan.ok && threads <= UINT32_MAX;
     }
+    if (eval_every > 0 && eval_every < r.min_steps) r.all = false;
     if (!r.all) r = ResData{};
     return r.all;
 }

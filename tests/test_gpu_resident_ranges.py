@@ -1,0 +1,147 @@
+"""Solvers of small instances whose step ranges change length: long ones run on
+one compute unit per replica, short ones on the row-tiled kernels, and the two
+alternate on the same state; batches of several workgroup sizes, which run on
+side streams; ranges inside a caller's graph.  Everything is compared with a
+solver that an explicit launch shape keeps on the row-tiled kernels: fields,
+moments, read-outs and anytime bests bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2412_09285_amd import fem
+from paper_2412_09285_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+TILE = (1, 4, 2, 0, 0)
+
+
+def graph(n, deg, weights="pm1", seed=1):
+    m = min(n * deg // 2, n * (n - 1) // 2)
+    g = W.er_graph_m(n, m, seed=seed, weights="one" if weights == "real" else weights)
+    w = W.rng_for(seed + 1).standard_normal(m).astype(np.float32) if weights == "real" else g.w
+    return fem.Problem.maxcut(n, g.u, g.v, w)
+
+
+def formula(n, m, k=3, seed=1):
+    return fem.Problem.from_cnf(W.random_ksat(n, m, k, seed=seed))
+
+
+def problem(kind):
+    if kind == "batch":
+        return fem.Problem.batch([graph(n, 6, seed=n) for n in (90, 300, 700, 1500, 3000)])
+    if kind == "sat batch":
+        return fem.Problem.batch([formula(n, 4 * n, seed=n) for n in (90, 300, 700, 1500, 3000)])
+    return {"rows 1": lambda: graph(900, 20), "rows 2": lambda: graph(2000, 20), "rows 4": lambda: graph(3500, 8, "real"),
+            "rows 8": lambda: graph(5000, 4), "sat": lambda: formula(1500, 6300),
+            "manip": lambda: graph(2000, 20, "one"), "manip batch": lambda: problem("batch"),
+            "real": lambda: graph(300, 12, "real")}[kind]()
+
+
+def solver(prob, R, kind, tiled, **kw):
+    if kind.startswith("manip"):
+        kw.update(gradient=fem.GRAD_MANIPULATED, energy_every=0)
+    s = fem.Solver(prob, fem.default_params(replicas=R, steps=400, keep_grad=1, **kw), stream=torch.cuda.Stream())
+    if tiled:
+        s.set_tile(*TILE)
+    return s
+
+
+@pytest.mark.parametrize("kind", ["rows 1", "rows 2", "rows 4", "rows 8", "sat", "manip", "real", "batch", "manip batch",
+                                  "sat batch"])
+@pytest.mark.parametrize("eval_every,dtype", [(0, fem.F32), (3, fem.BF16), (20, fem.F32)])
+def test_ranges_of_changing_length(kind, eval_every, dtype):
+    prob = problem(kind)
+    R = 11
+    h0 = W.initial_fields(prob.n, R, seed=3, std=0.4)
+    h1 = W.initial_fields(prob.n, R, seed=4, std=0.4)
+    a, b = (solver(prob, R, kind, tiled, eval_every=eval_every, marginal_dtype=dtype) for tiled in (False, True))
+    for s in (a, b):
+        s.set_fields(torch.from_numpy(h0).cuda())
+    blob = None
+    plan = [1, 1, 40, 2, 33, 3, 1, "graph", 50, "graph", "save", 1, 35, "load", 1, "set", 1, 2, 40, "graph", 5, 17, 34,
+            "load", 36]
+    for op in plan:
+        for s in (a, b):
+            if op == "graph":          # short ranges twice, the second time from a replayed graph
+                t = s.t
+                st = s.get_state()
+                s.capture(t + 2)
+                s.run_until(t + 2)
+                s.step(35)
+                s.set_state(st)
+                s.run_until(t + 2)
+            elif op == "save":
+                blob = b.get_state()
+            elif op == "load":
+                s.set_state(blob)
+            elif op == "set":
+                s.set_fields(h1)
+            else:
+                s.step(op)
+        assert a.t == b.t and a.get_state() == b.get_state(), op
+        if op not in ("save", "load", "set"):
+            assert np.array_equal(a.last_grad(), b.last_grad()), op
+        if eval_every:
+            assert np.array_equal(a.anytime_best(), b.anytime_best()), op
+    assert np.array_equal(a.round(), b.round())
+    assert all(np.array_equal(x, y) for x, y in zip(a.best(), b.best()))
+
+
+@pytest.mark.parametrize("kind", ["rows 2", "rows 4", "rows 8", "sat", "batch"])
+def test_short_ranges_take_the_row_tiled_kernels(kind):
+    """The energies of a short range are those of the shaped kernels to the bit:
+    the sums of a workgroup that holds all rows round differently."""
+    prob = problem(kind)
+    R = 32
+    h0 = W.initial_fields(prob.n, R, seed=5, std=1.0)
+    out = []
+    for tiled in (False, True):
+        s = solver(prob, R, kind, False)
+        if tiled:
+            s.set_tile(*s.tile())
+        s.set_fields(h0)
+        s.step(1)
+        e = [s.energies()]
+        s.run_until(s.t + 1)
+        e.append(s.energies())
+        out.append(np.array(e))
+    assert np.array_equal(*out)
+
+
+def test_no_marginal_copy_is_relied_on_after_a_callers_graph():
+    """A caller's graph of steps moves the fields without the solver's
+    knowledge; a short range after its replay starts from the moved fields."""
+    prob = problem("rows 2")
+    R = 8
+    h0 = W.initial_fields(prob.n, R, seed=6, std=0.4)
+    s = solver(prob, R, "rows 2", False)
+    s.set_fields(h0)
+    s.step(1)                          # a short range: row-tiled
+    s.set_fields(h0)
+    stream = torch.cuda.Stream()
+    s2 = fem.Solver(prob, fem.default_params(replicas=R, steps=400), stream=stream)
+    s2.set_fields(h0)
+    s2.step(1)
+    s2.set_fields(h0)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        s2.step(2)
+    for k in (2, 30):
+        ref = fem.Solver(prob, fem.default_params(replicas=R, steps=400))
+        ref.set_tile(*TILE)
+        ref.set_fields(h0)
+        ref.step(2)
+        h, m1, m2 = (np.frombuffer(ref.get_state()[-(3 * h0.nbytes + 8 * R):][i * h0.nbytes:(i + 1) * h0.nbytes],
+                                   np.float32).reshape(h0.shape) for i in range(3))
+        assert np.array_equal(h, ref.fields())
+        s2.set_fields(h0)
+        s2.step(1)                     # leaves a marginal copy of other fields behind
+        s2.set_fields(h0)
+        g.replay()
+        stream.synchronize()
+        assert np.array_equal(s2.fields(), h)
+        s2.step(k)                     # from t = 0 as far as the solver knows
+        ref.set_adam_state(h, m1, m2, 0)
+        ref.step(k)
+        assert np.array_equal(s2.fields(), ref.fields())
