@@ -333,20 +333,21 @@ fem_status fem_set_state(fem_solver* s, const void* buf, size_t bytes);
  * eight XCDs round-robin) gathers from its own columns of the marginal copy.
  * fem_get_tile reports the lanes actually used.  All shapes give
  * bit-identical fields.  The solver of a problem of small MaxCut or Max-k-SAT
- * instances starts on kernels that no launch shape applies to (fem_run);
- * fem_set_tile puts it on the shaped kernels, with the same fields. */
+ * instances takes its long ranges on kernels that no launch shape applies to
+ * (fem_run), also after fem_tune, whose shape its short ranges take;
+ * fem_set_tile puts all of them on the shaped kernels, with the same fields. */
 typedef struct {
     int32_t vec, waves, rows, nt, lanes;
 } fem_tile;
 fem_status fem_get_tile(const fem_solver* s, fem_tile* t);
 fem_status fem_set_tile(fem_solver* s, const fem_tile* t);
 /* Autotune: time every valid shape twice for trial_steps steps from the same
- * state (restored afterwards), keep the shape with the fastest run (the one
- * it has, untimed, where the solver is not on these kernels), and cache it on disk under the key (kind, n,
- * nnz, R, q, dtype, instances, energies on/off, gradient mode) in
- * $FEM_TUNE_CACHE (default ~/.cache/femx/tune.txt).  use_cache = 1 returns a
- * cached choice without timing: the user's cache first, then the shapes
- * tuned on an MI355X that ship beside the library (data/tune_mi355x.txt). */
+ * state (restored afterwards), keep the shape with the fastest run, and cache
+ * it on disk under the key (kind, n, nnz, R, q, dtype, instances, energies
+ * on/off, gradient mode) in $FEM_TUNE_CACHE (default ~/.cache/femx/tune.txt).
+ * use_cache = 1 returns a cached choice without timing: the user's cache
+ * first, then the shapes tuned on an MI355X that ship beside the library
+ * (data/tune_mi355x.txt). */
 fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_tile* chosen);
 
 /* Average duration in milliseconds of one step in the step kernel over the last

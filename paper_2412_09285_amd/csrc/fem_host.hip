@@ -437,6 +437,7 @@ struct fem_solver {
     ResData res;
     bool marg_ok = false;     // the marginal copy is that of the fields: resident steps leave it behind
     bool always_res = false;  // its steps are part of a caller's graph, which moves the fields unseen
+    bool tuning = false;      // the tuner times the row-tiled kernels
     // Side streams for the resident classes after the first, which run beside
     // it within a range of steps.
     static constexpr int N_SIDE = 2;
@@ -875,7 +876,7 @@ static fem_status join_side(fem_solver* s, const bool (&joined)[fem_solver::N_SI
 // captures are always: their replays find no marginal copy to rely on.
 static bool takes_resident(fem_solver* s, int t_end)
 {
-    if (!s->res.all) return false;
+    if (!s->res.all || s->tuning) return false;
     int steps = t_end - s->t;
     if (s->prm.eval_every > 0) steps = std::min(steps, s->prm.eval_every);
     if (steps >= s->res.min_steps || s->always_res) return true;
@@ -2116,19 +2117,18 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
         }
     }
     std::vector<TileShape> cands;
-    if (s->res.all) cands.push_back(s->shape);   // no row-tiled steps: nothing to choose
     const int vecs[4] = {1, 2, 4, 8};
     const int wavess[4] = {2, 4, 8, 16};
     const int rowss[4] = {1, 2, 4, 8};
     const int laness[4] = {0, 32, 16, 8};
     // the dense step kernel has a fixed shape: only the non-temporal flag is
     // tried (the rest of the shape serves the read-out)
-    for (int ntf = 0; !s->res.all && s->dense && ntf < 2; ++ntf) {
+    for (int ntf = 0; s->dense && ntf < 2; ++ntf) {
         TileShape sh = s->shape;
         sh.nt = ntf;
         cands.push_back(sh);
     }
-    for (int vi = 0; !s->res.all && !s->dense && vi < (s->kind == KIND_BMINCUT ? 1 : 4); ++vi)
+    for (int vi = 0; !s->dense && vi < (s->kind == KIND_BMINCUT ? 1 : 4); ++vi)
         for (int ln : laness) {
             // a lane cap only matters where it splits the replicas
             const int per_lane = s->kind == KIND_BMINCUT ? 1 : vecs[vi];
@@ -2152,6 +2152,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
     float best_ms = std::numeric_limits<float>::infinity();
     const bool prof = s->profile;
     s->profile = false;
+    s->tuning = true;
     fem_status st = FEM_OK;
     for (const TileShape& sh : cands) {
         fem_tile t{sh.vec, sh.waves, sh.rows, sh.nt, sh.lanes};
@@ -2183,6 +2184,7 @@ fem_status fem_tune(fem_solver* s, int32_t trial_steps, int32_t use_cache, fem_t
         }
     }
     s->profile = prof;
+    s->tuning = false;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     fem_tile bt{best_sh.vec, best_sh.waves, best_sh.rows, best_sh.nt, best_sh.lanes};

@@ -145,3 +145,36 @@ def test_no_marginal_copy_is_relied_on_after_a_callers_graph():
         ref.set_adam_state(h, m1, m2, 0)
         ref.step(k)
         assert np.array_equal(s2.fields(), ref.fields())
+
+
+@pytest.mark.parametrize("kind", ["rows 2", "batch"])
+def test_the_tuner_times_the_row_tiled_kernels(kind, tmp_path, monkeypatch):
+    """A shape that is no candidate of the tuner, three rows per team, is taken
+    from the cache, but not kept or written again by a tuning run; the solver's
+    steps go on as if untuned, and long ones stay on one compute unit."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("FEM_TUNE_CACHE", str(cache))
+    prob = problem(kind)
+    R = 8
+    h0 = W.initial_fields(prob.n, R, seed=7, std=0.4)
+    s = solver(prob, R, kind, False)
+    s.set_fields(h0)
+    s.tune(trial_steps=1, use_cache=False)
+    key = cache.read_text().split()[0]
+    cache.write_text(f"{key} 1 4 3 0 8\n")
+    assert s.tune(trial_steps=1, use_cache=True) == (1, 4, 3, 0, 8) == s.tile()
+    s.step(5)
+    tile = s.tune(trial_steps=2, use_cache=False)
+    assert tile[2] != 3 and tile == s.tile()
+    assert cache.read_text().splitlines()[-1].split() == [key] + [str(v) for v in tile]
+    s.step(30)
+    e = s.energies()
+    out = []
+    for tiled in (False, True):
+        r = solver(prob, R, kind, tiled)
+        r.set_fields(h0)
+        r.step(5)
+        r.step(30)
+        out.append(r.energies())
+        assert np.array_equal(r.fields(), s.fields())
+    assert np.array_equal(e, out[0]) and not np.array_equal(e, out[1])
