@@ -245,8 +245,9 @@ fem_status fem_step(fem_solver* s, int32_t n_steps);
  * on one compute unit, whatever call enqueues them, and need no graph; ranges
  * (or stretches between read-outs) of a few steps take the shaped kernels
  * there too, with the same fields.
- * Their tables (a re-ordered copy of the adjacency and about 100 bytes per
- * step) are device memory of the solver. */
+ * The re-ordered copy of the adjacency that they read is device memory of the
+ * problem, made by the first such solver and shared by the others; 104 bytes per
+ * step of the schedule are the solver's. */
 fem_status fem_run(fem_solver* s);
 /* Enqueue steps [t, t_end) as one captured HIP graph. */
 fem_status fem_run_until(fem_solver* s, int32_t t_end);

@@ -15,6 +15,7 @@
 #include <cstring>
 #include <limits>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <sys/stat.h>
@@ -86,7 +87,12 @@ static void free_problem_device(Problem& p);
 static void problem_unref(fem_problem* fp)
 {
     if (!fp) return;
-    if (--fp->refs <= 0 && fp->released) {
+    bool gone;
+    {
+        std::lock_guard<std::mutex> lock(fp->lock);
+        gone = --fp->refs <= 0 && fp->released;
+    }
+    if (gone) {
         (void)hipSetDevice(fp->p.device);
         free_problem_device(fp->p);
         delete fp;
@@ -474,8 +480,9 @@ struct fem_solver {
     TileSet bs;
     // best replica: double value [inst], int32 replica [inst], uint8 state [n]
     char* pick = nullptr;
-    // schedules
+    // schedules, and the step counts from which b1^n and b2^n are below 2^-60
     std::vector<double> beta, lam;
+    double b_gone[2];
     // graphs keyed by (t0, t1)
     std::map<std::pair<int, int>, hipGraphExec_t> graphs;
     // profiling of the step kernel
@@ -665,8 +672,11 @@ static StepScalars step_scalars(const fem_solver* s, int t)
     sc.gamma_d = p.gradient == FEM_GRAD_MANIPULATED ? p.gamma_grad : 1.0;
     sc.inv_beta = (float)sc.inv_beta_d;
     sc.lam = (float)sc.lam_d;
-    const double bc2_sqrt = std::sqrt(1.0 - std::pow(p.adam_b2, nstep));
-    sc.step_size = (float)(p.lr / (1.0 - std::pow(p.adam_b1, nstep)));
+    // (powers below half an ulp of 1 are not formed: a step table has one of
+    // each for every step of the schedule)
+    const double bc1 = nstep < s->b_gone[0] ? 1.0 - std::pow(p.adam_b1, nstep) : 1.0;
+    const double bc2_sqrt = std::sqrt(nstep < s->b_gone[1] ? 1.0 - std::pow(p.adam_b2, nstep) : 1.0);
+    sc.step_size = (float)(p.lr / bc1);
     sc.bc2_sqrt = (float)bc2_sqrt;
     sc.inv_bc2_sqrt = (float)(1.0 / bc2_sqrt);
     sc.b1 = (float)p.adam_b1;
@@ -800,6 +810,38 @@ static fem_status readout_eval(fem_solver* s, bool update_best)
     return FEM_OK;
 }
 
+// Side streams are handed on from solver to solver: creating one takes 80 to
+// 125 us, more than the rest of a small solver.  A stream is returned once the
+// work queued on it is waited for by its solver's stream, and at most 16 are
+// kept per device.
+static std::mutex side_lock;
+static std::map<int, std::vector<hipStream_t>> side_free;
+static hipError_t side_stream(int device, hipStream_t* st)
+{
+    {
+        std::lock_guard<std::mutex> lock(side_lock);
+        std::vector<hipStream_t>& v = side_free[device];
+        if (!v.empty()) {
+            *st = v.back();
+            v.pop_back();
+            return hipSuccess;
+        }
+    }
+    return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
+}
+static void return_side_stream(int device, hipStream_t st)
+{
+    {
+        std::lock_guard<std::mutex> lock(side_lock);
+        std::vector<hipStream_t>& v = side_free[device];
+        if (v.size() < 16) {
+            v.push_back(st);
+            return;
+        }
+    }
+    (void)hipStreamDestroy(st);
+}
+
 // An interval of the profile on the solver's stream, covering n steps: the
 // start is recorded here, *end is what the caller records after its launch
 // (null when not profiling).
@@ -841,7 +883,7 @@ static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_so
     a.t0 = s->t;
     a.t1 = t_end;
     a.bf16 = s->dtype == FEM_BF16;
-    const int classes = (int)s->res.classes.size();
+    const int classes = (int)s->res.t->classes.size();
     s->marg_ok = false;
     STCHK(profile_begin(s, t_end - s->t, &s->res_end));
     if (s->fork) HIPCHK(hipEventRecord(s->fork, s->stream));
@@ -976,7 +1018,7 @@ static void destroy_solver(fem_solver* s)
     drop_graphs(s);
     // the solver's stream waits for the side streams, so they are idle too
     for (int k = 0; k < fem_solver::N_SIDE; ++k) {
-        if (s->side[k]) (void)hipStreamDestroy(s->side[k]);
+        if (s->side[k]) return_side_stream(s->prob->device, s->side[k]);
         if (s->join[k]) (void)hipEventDestroy(s->join[k]);
     }
     if (s->fork) (void)hipEventDestroy(s->fork);
@@ -985,7 +1027,6 @@ static void destroy_solver(fem_solver* s)
         (void)hipEventDestroy(ev.second);
     }
     free_tiling(s);
-    resident_free(s->res);
     dfree(s->state);
     dfree(s->grad);
     void* m0 = s->marg[0];
@@ -1310,8 +1351,13 @@ fem_status fem_graph_order(int32_t n, int64_t n_edges, const int32_t* u, const i
 void fem_problem_destroy(fem_problem* fp)
 {
     if (!fp) return;
-    fp->released = true;
-    if (fp->refs <= 0) {
+    bool gone;
+    {
+        std::lock_guard<std::mutex> lock(fp->lock);
+        fp->released = true;
+        gone = fp->refs <= 0;
+    }
+    if (gone) {
         (void)hipSetDevice(fp->p.device);
         free_problem_device(fp->p);
         delete fp;
@@ -1386,7 +1432,10 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     auto* s = new (std::nothrow) fem_solver;
     if (!s) return fail(FEM_E_NOMEM, "host allocation failed");
     s->owner = const_cast<fem_problem*>(fp);
-    s->owner->refs++;
+    {
+        std::lock_guard<std::mutex> lock(s->owner->lock);
+        s->owner->refs++;
+    }
     s->prob = &p;
     s->prm = P;
     s->stream = static_cast<hipStream_t>(hip_stream);
@@ -1408,6 +1457,10 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     for (int t = 0; t < P.steps; ++t) {
         s->beta[(size_t)t] = sched_beta(P, P.steps, t);
         s->lam[(size_t)t] = P.lambda_ramp ? (P.steps > 1 ? P.lambda * t / (double)(P.steps - 1) : P.lambda) : P.lambda;
+    }
+    for (int k = 0; k < 2; ++k) {
+        const double b = k ? P.adam_b2 : P.adam_b1;
+        s->b_gone[k] = b > 0.0 && b < 1.0 ? std::ceil(-42.0 / std::log(b)) : std::numeric_limits<double>::infinity();
     }
     auto bail = [&](fem_status st) {
         std::string keep = g_err;
@@ -1469,6 +1522,20 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         s->n_records = (P.steps + P.energy_every - 1) / P.energy_every;
         ALLOC(s->ehist, (size_t)s->n_records * IR * 3);
     }
+    if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS) {
+        e = resident_choose(*s->owner, s->R, s->manip, P.eval_every, s->res);
+        if (e == hipSuccess && s->res.all && s->res.t->classes.size() > 1) {
+            for (int k = 0; k < fem_solver::N_SIDE && e == hipSuccess; ++k) {
+                e = side_stream(p.device, &s->side[k]);
+                if (e == hipSuccess) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
+            }
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
+        }
+        if (e != hipSuccess)
+            return bail(fail(e == hipErrorOutOfMemory ? FEM_E_NOMEM : FEM_E_HIP, "resident instances: %s",
+                             hipGetErrorString(e)));
+    }
+    const size_t n_steps = s->res.all ? (size_t)P.steps + 1 : 0;   // resident kernels read one step ahead
     {
         // the small arrays share one allocation
         size_t off = 0;
@@ -1477,8 +1544,9 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
             parts.emplace_back(reinterpret_cast<void**>(ptr), off);
             off += (count * sizeof(**ptr) + 255) & ~(size_t)255;
         };
-        take(&s->eout, IR * 3);
         take(&s->d_wtot, (size_t)s->n_inst);
+        take(&s->res.steps, n_steps);
+        take(&s->eout, IR * 3);
         take(&s->sigma, (size_t)s->n * s->R);
         take(&s->vout, IR);
         take(&s->best, IR);
@@ -1499,24 +1567,15 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         for (auto& q : parts) *q.first = s->block + q.second;
     }
 #undef ALLOC
-    e = hipMemcpy(s->d_wtot, p.inst_wtot.data(), sizeof(double) * s->n_inst, hipMemcpyHostToDevice);
-    if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
-    if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS) {
-        if (resident_choose(p, s->R, s->manip, P.eval_every, s->res)) {
-            std::vector<ResStep> steps((size_t)P.steps + 1);   // read one step ahead
-            for (int t = 0; t < P.steps; ++t) steps[(size_t)t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
-            e = resident_build(p, steps, s->res);
-            if (e == hipSuccess && s->res.classes.size() > 1) {
-                for (int k = 0; k < fem_solver::N_SIDE && e == hipSuccess; ++k) {
-                    e = hipStreamCreateWithFlags(&s->side[k], hipStreamNonBlocking);
-                    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
-                }
-                if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
-            }
-            if (e != hipSuccess)
-                return bail(fail(e == hipErrorOutOfMemory ? FEM_E_NOMEM : FEM_E_HIP, "resident instances: %s",
-                                 hipGetErrorString(e)));
-        }
+    {
+        // instance weights and step scalars, in one transfer
+        const size_t at = n_steps ? (size_t)((char*)s->res.steps - (char*)s->d_wtot) : (size_t)s->n_inst * 8;
+        std::vector<char> host(at + n_steps * sizeof(ResStep));
+        std::memcpy(host.data(), p.inst_wtot.data(), (size_t)s->n_inst * 8);
+        ResStep* steps = reinterpret_cast<ResStep*>(host.data() + at);
+        for (int t = 0; n_steps && t < P.steps; ++t) steps[t] = ResStep{step_scalars(s, t), s->beta[(size_t)t]};
+        e = hipMemcpy(s->d_wtot, host.data(), host.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
     }
     TileShape sh = evaluation ? eval_shape(s->kind, s->R)
                               : default_shape(s->kind, s->manip, s->n, s->R, s->q, (int)msz);
@@ -2002,7 +2061,7 @@ static fem_status apply_tile(fem_solver* s, const fem_tile* t, bool take_over)
     HIPCHK(hipSetDevice(s->prob->device));
     HIPCHK(hipStreamSynchronize(s->stream));
     take_over = take_over && s->res.all;
-    if (take_over) resident_free(s->res);
+    if (take_over) s->res = ResData{};   // (its table of steps stays in the solver's block)
     STCHK(setup_tiling(s, sh));
     // column-sum partials are laid out per tile, and resident instances may
     // have left the marginal copy behind: rebuild them

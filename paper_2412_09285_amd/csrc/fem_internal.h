@@ -4,10 +4,14 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
 namespace fem {
+
+struct ResTables;   // fem_resident.h
+void resident_release(ResTables* t);
 
 enum Kind { KIND_MAXCUT = 0, KIND_BMINCUT = 1, KIND_MAXSAT = 2 };
 
@@ -315,6 +319,9 @@ hipError_t launch_best_update(int kind, int R, int n_inst, int q, double lam, co
 // problem released by its owner stays alive until its last solver is gone.
 struct fem_problem {
     fem::Problem p;
+    std::mutex lock;   // of what follows: solvers may be made and destroyed by several threads
     int refs = 0;
     bool released = false;
+    fem::ResTables* res = nullptr;
+    ~fem_problem() { fem::resident_release(res); }
 };

@@ -28,7 +28,6 @@
 
 #include <algorithm>
 #include <cstring>
-#include <functional>
 #include <numeric>
 
 #include "fem_device.h"
@@ -452,7 +451,13 @@ struct ResPlan {
     bool ok = false;
 };
 
-static ResPlan res_plan(const Problem& p, int b, int planes, bool unit, size_t dev_lds)
+// per: incidences or adjacency entries in 8 bytes
+static int res_per(const Problem& p) { return p.kind != KIND_MAXSAT ? 4 : p.sat_width == 2 ? 2 : 1; }
+
+// The plan of instance b; its rows by falling degree (ties by index) are
+// appended to perm, padded to the positions.
+static ResPlan res_plan(const Problem& p, int b, int planes, bool unit, size_t dev_lds, std::vector<int32_t>& count,
+                        std::vector<int32_t>& perm)
 {
     ResPlan r;
     const bool sat = p.kind == KIND_MAXSAT;
@@ -462,11 +467,22 @@ static ResPlan res_plan(const Problem& p, int b, int planes, bool unit, size_t d
     while (r.threads < n && r.threads < 1024) r.threads <<= 1;
     while ((int64_t)r.rpt * r.threads < n) r.rpt <<= 1;
     const int64_t* ro = p.h_row_off.data() + row0;
-    std::vector<int32_t> deg((size_t)n);
-    for (int64_t i = 0; i < n; ++i) deg[(size_t)i] = (int32_t)std::min<int64_t>(ro[i + 1] - ro[i], 1 << 20);
-    std::sort(deg.begin(), deg.end(), std::greater<int32_t>());
-    const int per = !sat ? 4 : p.sat_width == 2 ? 2 : 1;
-    for (int64_t s = 0; s < n; s += 64) r.n_adj += (deg[(size_t)s] + per - 1) / per * 64;
+    const int per = res_per(p);
+    if (ro[n] - ro[0] > RES_MAX_STREAM * per) return r;   // no arrangement of so many is accepted
+    // by counting: degrees are few, and the rows keep their order
+    int64_t most = 0;
+    for (int64_t i = 0; i < n; ++i) most = std::max(most, ro[i + 1] - ro[i]);
+    count.assign((size_t)most + 2, 0);
+    for (int64_t i = 0; i < n; ++i) ++count[(size_t)(most - (ro[i + 1] - ro[i]) + 1)];
+    for (int64_t d = 0; d <= most; ++d) count[(size_t)d + 1] += count[(size_t)d];
+    const size_t base = perm.size();
+    perm.resize(base + (size_t)r.threads * r.rpt, -1);
+    for (int64_t i = 0; i < n; ++i)
+        perm[base + (size_t)count[(size_t)(most - (ro[i + 1] - ro[i]))]++] = row0 + (int32_t)i;
+    for (int64_t s = 0; s < n; s += 64) {
+        const int64_t i = perm[base + (size_t)s] - row0;
+        r.n_adj += (ro[i + 1] - ro[i] + per - 1) / per * 64;
+    }
     r.lds = RES_PART_BYTES + (size_t)res_buffers(r.rpt) * planes * res_values(r.threads * r.rpt) * 4;
     const size_t with = r.lds + (size_t)r.n_adj * (unit ? 8 : 24);
     r.adj_lds = with <= dev_lds;
@@ -476,10 +492,172 @@ static ResPlan res_plan(const Problem& p, int b, int planes, bool unit, size_t d
     return r;
 }
 
-void resident_free(ResData& r)
+// The plan of all instances, larger ones first: the longest workgroups start
+// first.
+static void res_plan_all(const Problem& p, ResTables& t)
 {
-    if (r.block) (void)hipFree(r.block);
-    r = ResData{};
+    t.planned = true;
+    const bool sat = p.kind == KIND_MAXSAT;
+    int dev_lds = 0;
+    if (p.kind == KIND_BMINCUT || p.dense_w ||
+        hipDeviceGetAttribute(&dev_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device) != hipSuccess)
+        return;
+    auto rows_of = [&](int b) { return (int)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]); };
+    std::vector<int> ids((size_t)p.n_inst);
+    std::iota(ids.begin(), ids.end(), 0);
+    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return rows_of(x) > rows_of(y); });
+    if (rows_of(ids[0]) > (sat ? RES_MAX_ROWS_SAT : RES_MAX_ROWS)) return;
+    t.pm1 = !sat && p.adj_pm1 != nullptr;
+    t.planes = sat ? 2 : 1;
+    for (size_t k = 0; t.pm1 && t.planes == 1 && k < p.h_adj.size(); ++k)
+        if ((uint32_t)p.h_adj[k].y & 0x80000000u) t.planes = 2;
+    std::vector<int32_t> count;
+    int64_t adj0 = 0;
+    int32_t slice0 = 0;
+    t.fits = true;
+    for (int b : ids) {
+        ResInst in{};
+        in.pos0 = (int32_t)t.h_perm.size();
+        const ResPlan plan = res_plan(p, b, t.planes, t.pm1 || sat, (size_t)dev_lds, count, t.h_perm);
+        if (!plan.ok) {
+            t = ResTables{};
+            t.planned = true;
+            return;
+        }
+        if (t.classes.empty() || t.classes.back().threads != plan.threads || t.classes.back().rpt != plan.rpt ||
+            t.classes.back().adj_lds != plan.adj_lds) {
+            ResClass c;
+            c.threads = plan.threads;
+            c.rpt = plan.rpt;
+            c.first = (int)t.h_inst.size();
+            c.adj_lds = plan.adj_lds;
+            t.classes.push_back(c);
+        }
+        t.classes.back().n_inst++;
+        t.classes.back().lds = std::max(t.classes.back().lds, plan.lds);
+        t.threads += (uint64_t)plan.threads;
+        in.inst = b;
+        in.n = rows_of(b);
+        in.npos = plan.threads * plan.rpt;
+        in.slice0 = slice0;
+        in.n_adj = (int32_t)plan.n_adj;
+        in.adj0 = adj0;
+        slice0 += in.npos / 64;
+        adj0 += plan.n_adj;
+        t.h_inst.push_back(in);
+    }
+}
+
+void resident_release(ResTables* t)
+{
+    if (t && t->block) (void)hipFree(t->block);
+    delete t;
+}
+
+// The tables of a plan: per row its entries, as the kernels read them.
+static hipError_t res_build(const Problem& p, ResTables& t)
+{
+    const bool sat = p.kind == KIND_MAXSAT, unit = sat || t.pm1;
+    const int per = res_per(p);
+    const ResInst& end = t.h_inst.back();
+    const size_t n_slice = (size_t)end.slice0 + end.npos / 64;
+    // entries are read two rounds ahead
+    const size_t n_adj = (size_t)end.adj0 + end.n_adj + 4 * 64;
+    size_t bytes = 0;
+    auto take = [&](size_t b) {
+        const size_t at = bytes;
+        bytes = (bytes + b + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t o_inst = take(t.h_inst.size() * sizeof(ResInst)), o_perm = take(t.h_perm.size() * 4),
+                 o_slice = take(n_slice * sizeof(int2)), o_adj = take(n_adj * sizeof(uint2)),
+                 o_wgt = take(unit ? 0 : n_adj * sizeof(float4));
+    std::vector<char> host(bytes);
+    std::memcpy(host.data() + o_inst, t.h_inst.data(), t.h_inst.size() * sizeof(ResInst));
+    std::memcpy(host.data() + o_perm, t.h_perm.data(), t.h_perm.size() * 4);
+    int2* slice = reinterpret_cast<int2*>(host.data() + o_slice);
+    uint2* adj = reinterpret_cast<uint2*>(host.data() + o_adj);
+    float4* wgt = unit ? nullptr : reinterpret_cast<float4*>(host.data() + o_wgt);
+    std::vector<uint32_t> pos;   // byte offset of a row's value
+    for (const ResInst& in : t.h_inst) {
+        const int32_t row0 = p.inst_off[(size_t)in.inst];
+        const int32_t* perm = t.h_perm.data() + in.pos0;
+        const int64_t* ro = p.h_row_off.data();
+        pos.resize((size_t)in.n);
+        for (int k = 0; k < in.n; ++k) pos[(size_t)(perm[k] - row0)] = (uint32_t)k << 2;
+        auto at = [&](uint32_t row) { return pos[(size_t)row - (size_t)row0]; };
+        const uint32_t zero = (uint32_t)res_zero_slot(in.npos) << 2, one = zero + 4;
+        const uint32_t plane = (uint32_t)res_values(in.npos) << 2;
+        auto lit = [&](uint32_t l) {   // a literal slot of an incidence record
+            const uint32_t var = l & SAT_VAR_MASK;
+            if (var == SAT_NONE) return one;
+            return at(var) + ((l & SAT_POS) ? plane : 0u);
+        };
+        auto sat_word = [&](uint32_t s0, uint32_t s1, bool own_pos, bool owner) {
+            return lit(s0) | (lit(s1) << 16) | (owner ? 0x8000u : 0u) | (own_pos ? 0x80000000u : 0u);
+        };
+        // entry g of the row [q, q1), 8 bytes
+        auto pack = [&](int64_t q, int64_t q1, float* wf) {
+            if (!sat) {
+                uint32_t w[4];
+                for (int u = 0; u < 4; ++u, ++q) {
+                    w[u] = zero;
+                    if (q < q1) {
+                        const int2 ad = p.h_adj[(size_t)q];
+                        w[u] = at((uint32_t)ad.x) + (t.pm1 && ad.y < 0 ? plane : 0u);
+                        if (wf) std::memcpy(&wf[u], &ad.y, 4);
+                    }
+                }
+                return make_uint2(w[0] | w[1] << 16, w[2] | w[3] << 16);
+            }
+            if (p.sat_width == 2) {
+                uint32_t w[2];
+                for (int u = 0; u < 2; ++u, ++q) {
+                    w[u] = zero | (one << 16);
+                    if (q < q1) {
+                        const uint32_t x = (uint32_t)p.h_inc2[(size_t)q].x, y = (uint32_t)p.h_inc2[(size_t)q].y;
+                        w[u] = sat_word(x & ~SAT_FLAG, y & ~SAT_FLAG, x & SAT_FLAG, y & SAT_FLAG);
+                    }
+                }
+                return make_uint2(w[0], w[1]);
+            }
+            if (q >= q1) return make_uint2(zero | (one << 16), one);
+            const int4 rec = p.h_inc4[(size_t)q];
+            return make_uint2(sat_word((uint32_t)rec.x, (uint32_t)rec.y, rec.w & 1, rec.w & 2), lit((uint32_t)rec.z));
+        };
+        int first = 0;   // round of the instance
+        for (int s = 0; s < in.npos / 64; ++s) {
+            const int64_t i = perm[s * 64];   // the slice's longest row
+            const int rounds = i < 0 ? 0 : (int)((ro[i + 1] - ro[i] + per - 1) / per);
+            slice[in.slice0 + s] = make_int2(first, rounds);
+            uint2* a = adj + in.adj0 + (size_t)first * 64;
+            for (int l = 0; l < 64 && rounds > 0; ++l) {
+                const int32_t row = perm[s * 64 + l];
+                const int64_t q0 = row < 0 ? 0 : ro[row], q1 = row < 0 ? 0 : ro[row + 1];
+                for (int g = 0; g < rounds; ++g) {
+                    const size_t e = (size_t)g * 64 + l;
+                    a[e] = pack(q0 + (int64_t)g * per, q1, wgt ? &wgt[in.adj0 + first * 64 + (int64_t)e].x : nullptr);
+                }
+            }
+            first += rounds;
+        }
+    }
+    char* d = nullptr;
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&d), bytes);
+    if (e != hipSuccess) return e;
+    if ((e = hipMemcpy(d, host.data(), bytes, hipMemcpyHostToDevice)) != hipSuccess) {
+        (void)hipFree(d);
+        return e;
+    }
+    t.block = d;
+    t.inst = reinterpret_cast<ResInst*>(d + o_inst);
+    t.perm = reinterpret_cast<int32_t*>(d + o_perm);
+    t.slice = reinterpret_cast<int2*>(d + o_slice);
+    t.adj = reinterpret_cast<uint2*>(d + o_adj);
+    t.wgt = reinterpret_cast<float4*>(d + o_wgt);
+    std::vector<ResInst>().swap(t.h_inst);
+    std::vector<int32_t>().swap(t.h_perm);
+    return hipSuccess;
 }
 
 // The rule: an instance is resident if its rows fit the registers of one
@@ -519,175 +697,29 @@ void resident_free(ResData& r)
 // 50: 54.8 34 23 18.5 16.9, row-tiled 16), and a read-out by bytes is five
 // launches that a graph replays faster (67 nodes, real weights, R = 1, every
 // step: 19.4 / 13).
-bool resident_choose(const Problem& p, int R, bool manip, int eval_every, ResData& r)
+hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, ResData& r)
 {
-    const bool sat = p.kind == KIND_MAXSAT;
-    int dev_lds = 0;
-    if (p.kind == KIND_BMINCUT ||
-        hipDeviceGetAttribute(&dev_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device) != hipSuccess)
-        return false;
-    r.pm1 = !sat && p.adj_pm1 != nullptr;
-    r.planes = sat ? 2 : 1;
-    for (size_t k = 0; r.pm1 && r.planes == 1 && k < p.h_adj.size(); ++k)
-        if ((uint32_t)p.h_adj[k].y & 0x80000000u) r.planes = 2;
-    r.dev_lds = (size_t)dev_lds;
+    const Problem& p = fp.p;
+    std::lock_guard<std::mutex> lock(fp.lock);
+    if (!fp.res) fp.res = new ResTables;
+    ResTables& t = *fp.res;
+    if (!t.planned) res_plan_all(p, t);
+    if (!t.fits || t.threads * (uint64_t)R > UINT32_MAX) return hipSuccess;
+    int steps = eval_every > 0 && !bit_evaluation(p) ? 4 : 1;
+    if (t.classes.size() > 1) steps = std::max(steps, 8);
+    for (const ResClass& c : t.classes)
+        if (c.threads == 1024) {
+            const bool filled = R <= 256 && (R >= (manip ? 128 : 64) || (c.rpt == 1 && !manip));
+            steps = std::max(steps, (filled ? 1 : 2) * (manip ? 2 : 1) * c.rpt);
+        }
+    if (eval_every > 0 && eval_every < steps) return hipSuccess;
+    if (!t.block) {
+        const hipError_t e = res_build(p, t);
+        if (e != hipSuccess) return e;
+    }
+    r.t = &t;
+    r.min_steps = steps;
     r.all = true;
-    r.min_steps = eval_every > 0 && !bit_evaluation(p) ? 4 : 1;
-    uint64_t threads = 0;
-    ResPlan first;
-    for (int b = 0; b < p.n_inst && r.all; ++b) {
-        const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
-        if (b == 0) first = plan;
-        threads += (uint64_t)plan.threads * (uint64_t)R;
-        if (plan.threads == 1024) {
-            const bool fits = R <= 256 && (R >= (manip ? 128 : 64) || (plan.rpt == 1 && !manip));
-            r.min_steps = std::max(r.min_steps, (fits ? 1 : 2) * (manip ? 2 : 1) * plan.rpt);
-        }
-        if (plan.threads != first.threads || plan.rpt != first.rpt || plan.adj_lds != first.adj_lds)
-            r.min_steps = std::max(r.min_steps, 8);   // more than one class
-        r.all = plan.ok && threads <= UINT32_MAX;
-    }
-    if (eval_every > 0 && eval_every < r.min_steps) r.all = false;
-    if (!r.all) r = ResData{};
-    return r.all;
-}
-
-hipError_t resident_build(const Problem& p, const std::vector<ResStep>& steps, ResData& r)
-{
-    hipError_t e = hipSuccess;
-    const bool sat = p.kind == KIND_MAXSAT;
-    std::vector<int> ids((size_t)p.n_inst);
-    std::iota(ids.begin(), ids.end(), 0);
-    auto rows_of = [&](int b) { return (int)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]); };
-    // larger instances first: the longest workgroups start first
-    std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return rows_of(x) > rows_of(y); });
-    std::vector<ResInst> inst;
-    std::vector<int32_t> perm;
-    std::vector<int2> slice;
-    std::vector<uint2> adj;
-    std::vector<float4> wgt;
-    // entries per 8 bytes
-    const int per = !sat ? 4 : p.sat_width == 2 ? 2 : 1;
-    std::vector<int32_t> order, pos;
-    for (int b : ids) {
-        const int n = rows_of(b), row0 = p.inst_off[(size_t)b];
-        const ResPlan plan = res_plan(p, b, r.planes, r.pm1 || sat, r.dev_lds);
-        const int threads = plan.threads, rpt = plan.rpt;
-        if (r.classes.empty() || r.classes.back().threads != threads || r.classes.back().rpt != rpt ||
-            r.classes.back().adj_lds != plan.adj_lds) {
-            ResClass c;
-            c.threads = threads;
-            c.rpt = rpt;
-            c.first = (int)inst.size();
-            c.adj_lds = plan.adj_lds;
-            r.classes.push_back(c);
-        }
-        r.classes.back().n_inst++;
-        r.classes.back().lds = std::max(r.classes.back().lds, plan.lds);
-        ResInst in{};
-        in.inst = b;
-        in.row0 = row0;
-        in.n = n;
-        in.npos = threads * rpt;
-        in.pos0 = (int32_t)perm.size();
-        in.slice0 = (int32_t)slice.size();
-        in.adj0 = (int64_t)adj.size();
-        const int64_t* ro = p.h_row_off.data() + row0;
-        order.resize((size_t)n);
-        std::iota(order.begin(), order.end(), 0);
-        std::stable_sort(order.begin(), order.end(),
-                         [&](int32_t x, int32_t y) { return ro[x + 1] - ro[x] > ro[y + 1] - ro[y]; });
-        pos.resize((size_t)n);
-        for (int k = 0; k < n; ++k) pos[(size_t)order[(size_t)k]] = k;
-        for (int k = 0; k < in.npos; ++k) perm.push_back(k < n ? row0 + order[(size_t)k] : -1);
-        const uint32_t zero = (uint32_t)res_zero_slot(in.npos) << 2, one = zero + 4;
-        const uint32_t plane = (uint32_t)res_values(in.npos) << 2;
-        auto lit = [&](uint32_t l) {   // a literal slot of an incidence record
-            const uint32_t var = l & SAT_VAR_MASK;
-            if (var == SAT_NONE) return one;
-            return ((uint32_t)pos[(size_t)var - (size_t)row0] << 2) + ((l & SAT_POS) ? plane : 0u);
-        };
-        auto sat_word = [&](uint32_t s0, uint32_t s1, bool own_pos, bool owner) {
-            return lit(s0) | (lit(s1) << 16) | (owner ? 0x8000u : 0u) | (own_pos ? 0x80000000u : 0u);
-        };
-        for (int s = 0; s < in.npos / 64; ++s) {
-            int64_t deg = 0;
-            for (int l = 0; l < 64; ++l) {
-                const int k = s * 64 + l;
-                if (k < n) deg = std::max(deg, ro[order[(size_t)k] + 1] - ro[order[(size_t)k]]);
-            }
-            const int rounds = (int)((deg + per - 1) / per);
-            const size_t at = adj.size();
-            slice.push_back(make_int2((int)((at - (size_t)in.adj0) / 64), rounds));
-            adj.resize(at + (size_t)rounds * 64);
-            if (!sat && !r.pm1) wgt.resize(at + (size_t)rounds * 64, make_float4(0, 0, 0, 0));
-            for (int l = 0; l < 64; ++l) {
-                const int k = s * 64 + l;
-                const int64_t k0 = k < n ? ro[order[(size_t)k]] : 0, k1 = k < n ? ro[order[(size_t)k] + 1] : 0;
-                for (int g = 0; g < rounds; ++g) {
-                    uint32_t w[2] = {0, 0};
-                    float wf[4] = {0, 0, 0, 0};
-                    for (int u = 0; u < per; ++u) {
-                        const int64_t q = k0 + (int64_t)g * per + u;
-                        if (!sat) {
-                            uint32_t ent = zero;
-                            if (q < k1) {
-                                const int2 ad = p.h_adj[(size_t)q];
-                                float we;
-                                std::memcpy(&we, &ad.y, 4);
-                                ent = ((uint32_t)pos[(size_t)(ad.x - row0)] << 2) + (r.pm1 && we < 0.0f ? plane : 0u);
-                                wf[u] = we;
-                            }
-                            w[u / 2] |= ent << (16 * (u & 1));
-                        } else if (p.sat_width == 2) {
-                            w[u] = zero | (one << 16);
-                            if (q < k1) {
-                                const uint32_t x = (uint32_t)p.h_inc2[(size_t)q].x, y = (uint32_t)p.h_inc2[(size_t)q].y;
-                                w[u] = sat_word(x & ~SAT_FLAG, y & ~SAT_FLAG, x & SAT_FLAG, y & SAT_FLAG);
-                            }
-                        } else {
-                            w[0] = zero | (one << 16);
-                            w[1] = one;
-                            if (q < k1) {
-                                const int4 rec = p.h_inc4[(size_t)q];
-                                w[0] = sat_word((uint32_t)rec.x, (uint32_t)rec.y, rec.w & 1, rec.w & 2);
-                                w[1] = lit((uint32_t)rec.z);
-                            }
-                        }
-                    }
-                    adj[at + (size_t)g * 64 + l] = make_uint2(w[0], w[1]);
-                    if (!sat && !r.pm1) wgt[at + (size_t)g * 64 + l] = make_float4(wf[0], wf[1], wf[2], wf[3]);
-                }
-            }
-        }
-        in.n_adj = (int32_t)(adj.size() - (size_t)in.adj0);
-        inst.push_back(in);
-    }
-    // entries are read two rounds ahead
-    adj.resize(adj.size() + 4 * 64);
-    if (!wgt.empty()) wgt.resize(wgt.size() + 4 * 64);
-    // one allocation and one transfer for all tables
-    std::vector<char> host;
-    auto put = [&](const auto& v) {
-        const size_t at = (host.size() + 255) & ~(size_t)255, bytes = v.size() * sizeof(v[0]);
-        host.resize(at + bytes);
-        if (bytes) std::memcpy(host.data() + at, v.data(), bytes);
-        return at;
-    };
-    const size_t o_inst = put(inst), o_perm = put(perm), o_slice = put(slice), o_adj = put(adj), o_wgt = put(wgt),
-                 o_steps = put(steps);
-    if ((e = hipMalloc(&r.block, host.size())) != hipSuccess) {
-        r.block = nullptr;
-        return e;
-    }
-    if ((e = hipMemcpy(r.block, host.data(), host.size(), hipMemcpyHostToDevice)) != hipSuccess) return e;
-    char* d = static_cast<char*>(r.block);
-    r.inst = reinterpret_cast<ResInst*>(d + o_inst);
-    r.perm = reinterpret_cast<int32_t*>(d + o_perm);
-    r.slice = reinterpret_cast<int2*>(d + o_slice);
-    r.adj = reinterpret_cast<uint2*>(d + o_adj);
-    r.wgt = reinterpret_cast<float4*>(d + o_wgt);
-    r.steps = reinterpret_cast<ResStep*>(d + o_steps);
     return hipSuccess;
 }
 
@@ -729,17 +761,18 @@ static ResKernel pick(const Problem& p, bool pm1, bool manip, int rpt)
 hipError_t resident_launch(const Problem& p, const ResData& r, int cls, bool manip, ResArgs a, hipStream_t st)
 {
     (void)hipGetLastError();   // drop stale errors of earlier calls
-    const ResClass& c = r.classes[(size_t)cls];
-    a.inst = r.inst + c.first;
-    a.perm = r.perm;
-    a.slice = r.slice;
-    a.adj = r.adj;
-    a.wgt = r.wgt;
+    const ResTables& t = *r.t;
+    const ResClass& c = t.classes[(size_t)cls];
+    a.inst = t.inst + c.first;
+    a.perm = t.perm;
+    a.slice = t.slice;
+    a.adj = t.adj;
+    a.wgt = t.wgt;
     a.steps = r.steps;
     a.nrm = p.nrm;
     a.kind = p.kind;
-    a.planes = r.planes;
-    ResKernel k = c.adj_lds ? pick<true>(p, r.pm1, manip, c.rpt) : pick<false>(p, r.pm1, manip, c.rpt);
+    a.planes = t.planes;
+    ResKernel k = c.adj_lds ? pick<true>(p, t.pm1, manip, c.rpt) : pick<false>(p, t.pm1, manip, c.rpt);
     if (!k) return hipErrorInvalidValue;
     if (c.lds > 64 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),

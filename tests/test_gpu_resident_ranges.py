@@ -4,6 +4,8 @@ alternate on the same state; batches of several workgroup sizes, which run on
 side streams; ranges inside a caller's graph.  Everything is compared with a
 solver that an explicit launch shape keeps on the row-tiled kernels: fields,
 moments, read-outs and anytime bests bit for bit."""
+from concurrent.futures import ThreadPoolExecutor
+
 import numpy as np
 import pytest
 import torch
@@ -178,3 +180,38 @@ def test_the_tuner_times_the_row_tiled_kernels(kind, tmp_path, monkeypatch):
         out.append(r.energies())
         assert np.array_equal(r.fields(), s.fields())
     assert np.array_equal(e, out[0]) and not np.array_equal(e, out[1])
+
+
+@pytest.mark.parametrize("kind", ["rows 2", "batch", "sat batch", "manip"])
+def test_solvers_of_one_problem_share_its_tables(kind):
+    """Solvers made by several threads at once, with other replica counts and
+    schedules, stepping side by side after the problem and the solver that built
+    the tables are gone."""
+    prob = problem(kind)
+    counts = [3, 8, 17, 32, 5, 64]
+    h0 = [W.initial_fields(prob.n, R, seed=R, std=0.4) for R in counts]
+
+    def run(k, tiled=False):
+        s = solver(prob, counts[k], kind, tiled)
+        s.set_fields(h0[k])
+        return s
+
+    with ThreadPoolExecutor(len(counts)) as pool:
+        made = list(pool.map(run, range(len(counts))))
+        ref = [run(k, tiled=True) for k in range(len(counts))]
+        prob.close()
+        for k in (0, 2):
+            made[k].close()
+        torch.cuda.synchronize()
+
+        def go(k):
+            out = []
+            for n in (40, 33):
+                made[k].step(n)
+                out.append(made[k].fields())
+            return out
+
+        for k, got in zip((1, 3, 4, 5), pool.map(go, (1, 3, 4, 5))):
+            for n, h in zip((40, 33), got):
+                ref[k].step(n)
+                assert np.array_equal(ref[k].fields(), h), k
