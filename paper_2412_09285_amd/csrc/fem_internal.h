@@ -169,9 +169,12 @@ inline TileShape eval_shape(int kind, int R)
 //    R = 200: 61 / 55), one row for longer in a single segment of two values
 //    (12000, ratio 8, R = 76: two 49, one 45; in two segments, 5000, R = 200: one
 //    30, two 28).
-//  * MaxCut in float32 at R >= 192: eight replica segments, one per XCD, while
-//    a segment of the marginals fits its 4 MB L2 (30000 rows, R = 256: 81 /
-//    72; R = 512, 7.7 MB: 142 / 149).
+//  * MaxCut in float32 at R >= 256: up to eight replica segments, one per XCD,
+//    while a segment of the marginals fits its 4 MB L2 (30000 rows, R = 256: 81
+//    / 72; R = 512, 7.7 MB: 142 / 149) and segments are whole cache lines
+//    (24000 rows, degree 40, R = 256: 142 / 106, 288: 202 / 173, but 200: 114 /
+//    203, 300: 224 / 244).  Six and seven segments do not pin theirs to an
+//    XCD (R = 192: 102 / 91, of degree 6 39 / 41; 224: 121 / 136, 45 / 50).
 //  * Manipulated gradients (short rows of bits): two waves and one row up to
 //    larger grids, 30000 rows of degree 20, R = 100: 38 / 31; several segments
 //    of single values four waves and two rows (7861 rows, R = 225: 35.0 / 34.0).
@@ -212,7 +215,7 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
         cap = 2;
     } else {
         t.vec = R % 4 == 0 && (vals >= 4e6 || R >= 128) ? 4 : R % 2 == 0 && vals >= 2e5 ? 2 : 1;
-        if (R >= 192 && marg_bytes == 4 && vals * 4 / 8 <= 4e6) {
+        if (R >= 256 && R % 32 == 0 && marg_bytes == 4 && vals * 4 / 8 <= 4e6) {
             const int l = pow2ceil((R / t.vec + 7) / 8);
             t.lanes = l < 64 ? l : 64;
         }

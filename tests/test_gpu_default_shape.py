@@ -41,3 +41,27 @@ def test_default_shape(kind):
             out.append(s.fields(torch.empty_like(h0)))
             s.close()
         assert torch.equal(*out), R
+
+
+@pytest.mark.parametrize("R", [192, 200, 224, 256, 264, 288, 300, 384, 500, 512])
+@pytest.mark.parametrize("layout", [fem.STATE_SEPARATE, fem.STATE_INTERLEAVED])
+def test_replica_segments_are_whole_cache_lines(R, layout):
+    """MaxCut in float32: where a team covers less of a row than its 64 lanes
+    could, rows and segments are multiples of 128 bytes; and the shape gives the
+    fields of another."""
+    n = 9000
+    g = W.random_sparse_graph(n, 3 * n, seed=1, weights="pm1")
+    prob = fem.Problem.maxcut(g.n, g.u, g.v, g.w)
+    h0 = W.initial_fields(n, R, seed=1, std=0.3)
+    out = []
+    for tile in (None, (1, 4, 2, 0, 0)):
+        s = fem.Solver(prob, fem.default_params(replicas=R, steps=20, state_layout=layout))
+        vec, _, _, _, lanes = s.tile()
+        if tile:
+            s.set_tile(*tile)
+        elif lanes < 64 and lanes * vec < R:
+            assert R % 32 == 0 and lanes * vec % 32 == 0
+        s.set_fields(h0)
+        s.step(3)
+        out.append(s.fields())
+    assert np.array_equal(*out)
