@@ -183,13 +183,17 @@ inline TileShape eval_shape(int kind, int R)
 //    nodes, q = 16: 86 / 56), else 32 (R = 150, 4720 nodes, q = 8: 67 / 62).
 //  * State past the Infinity Cache is not found there again: non-temporal
 //    from 256 MB of state and marginals on (bMinCut 200000 nodes, q = 8, R = 16:
-//    404 / 334; at exactly 256 MB, MaxCut 50000 rows, R = 256: 111 / 111).
+//    404 / 334; at exactly 256 MB, MaxCut 50000 rows, R = 256: 111 / 111).  With
+//    manipulated gradients the copy is the read-out, a bit or a byte per (node,
+//    replica): MaxCut 60000 rows, cached and non-temporal, R = 332 (244 MB) 146 /
+//    172, R = 364 (267 MB) 176 / 175, R = 416 193 / 175.
 inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, int marg_bytes)
 {
     TileShape t;
     const double vals = (double)n * R * (kind == KIND_BMINCUT ? q : 1);
     t.waves = 4;
-    t.nt = vals * (12 + 2 * marg_bytes) > 256e6 && !(kind == KIND_BMINCUT && q >= 16) ? 1 : 0;
+    const double copy_bytes = !manip ? marg_bytes : kind == KIND_BMINCUT ? 1.0 / q : 0.125;   // per value
+    t.nt = vals * (12 + 2 * copy_bytes) > 256e6 && !(kind == KIND_BMINCUT && q >= 16) ? 1 : 0;
     int cap = 4;
     double blocks = 1024;
     if (kind == KIND_BMINCUT) {

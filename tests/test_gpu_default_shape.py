@@ -65,3 +65,15 @@ def test_replica_segments_are_whole_cache_lines(R, layout):
         s.step(3)
         out.append(s.fields())
     assert np.array_equal(*out)
+
+
+@pytest.mark.parametrize("kind,q,R,nt", [("maxcut", 1, 332, 0), ("maxcut", 1, 364, 1), ("bmincut", 4, 84, 0),
+                                         ("bmincut", 4, 92, 1)])
+def test_non_temporal_state_of_manipulated_gradients(kind, q, R, nt):
+    """State and read-outs past 256 MB are taken as non-temporal: 60000 rows of
+    12 bytes a value and two read-outs of a bit or a byte per replica."""
+    n = 60000
+    g = W.random_sparse_graph(n, 2 * n, seed=1, weights="one")
+    prob = fem.Problem.maxcut(n, g.u, g.v, g.w) if q == 1 else fem.Problem.bmincut(n, g.u, g.v, g.w, q)
+    s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, gradient=fem.GRAD_MANIPULATED, energy_every=0))
+    assert s.tile()[3] == nt
