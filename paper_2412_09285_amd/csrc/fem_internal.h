@@ -178,9 +178,19 @@ inline TileShape eval_shape(int kind, int R)
 //  * Manipulated gradients (short rows of bits): two waves and one row up to
 //    larger grids, 30000 rows of degree 20, R = 100: 38 / 31; several segments
 //    of single values four waves and two rows (7861 rows, R = 225: 35.0 / 34.0).
-//  * bMinCut: fewer lanes where a full wave leaves too many idle; at q >= 16,
-//    where a lane's states alone are a cache line, down to eight (R = 100, 2400
-//    nodes, q = 16: 86 / 56), else 32 (R = 150, 4720 nodes, q = 8: 67 / 62).
+//  * bMinCut: 32 lanes where that leaves a quarter fewer idle (R = 66, 8000
+//    nodes, q = 16: 160 / 120), at q < 16 also where it leaves some fewer and 32
+//    replicas of the marginals fit an XCD's L2 (R = 130, 2500 nodes, q = 4: 55 / 43;
+//    but 30000 nodes, q = 2, 7.7 MB: 116 / 130, and R = 200, seven segments, 8000
+//    nodes, q = 4: 135 / 162).  At q >= 16 a lane's states alone are a cache
+//    line: up to 6500 nodes down to eight lanes (R = 100, 2400 nodes, q = 16: 86 / 56;
+//    R = 66, 2500, q = 32: 404 / 263; 5000, q = 32, R = 66: 501 / 301); at 8000
+//    and more the gathers of so many segments cost more than the idle lanes
+//    (q = 32, R = 50: 338 / 399; q = 16, R = 33: 68 / 88), but for q = 32 from
+//    20000 nodes on (30000, R = 24: 672 / 603); and not for q = 16 at about two
+//    waves (3500 nodes, R = 150: 217 / 258; R = 200: 316 / 281).  Rows of q = 32
+//    are long: larger tiles from fewer blocks on (8000 nodes, R = 20, two rows
+//    176, four 163).
 //  * State past the Infinity Cache is not found there again: non-temporal
 //    from 256 MB of state and marginals on (bMinCut 200000 nodes, q = 8, R = 16:
 //    404 / 334; at exactly 256 MB, MaxCut 50000 rows, R = 256: 111 / 111).  With
@@ -197,15 +207,19 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
     int cap = 4;
     double blocks = 1024;
     if (kind == KIND_BMINCUT) {
-        blocks = 448;
-        double best = 0.0;
-        for (int l = 64; l >= (q >= 16 ? 8 : 32); l >>= 1) {
+        const auto used = [&](int l) {   // share of the lanes of R's segments that hold a replica
             const LaunchGeom g = make_geom(1, R, t.waves, l);
-            const double used = (double)R / ((double)g.nseg * g.lanes);
-            if (used > best * 1.05) {
-                best = used;
-                t.lanes = l;
-            }
+            return (double)R / ((double)g.nseg * g.lanes);
+        };
+        const bool two_waves = q == 16 && n >= 2000 && R > 128 && R < 192;
+        blocks = q == 32 && n > 6500 ? 200 : 448;
+        t.lanes = 64;
+        if (q >= 16 && ((n <= 6500 && !two_waves) || (q == 32 && n > 20000))) {
+            for (int l = 32; l >= 8; l >>= 1)
+                if (used(l) > 1.05 * used(t.lanes)) t.lanes = l;
+        } else if (used(32) >= 1.3 * used(64) ||
+                   (q < 16 && used(32) >= 1.15 * used(64) && (double)n * 32 * q * copy_bytes <= 2.6e6)) {
+            t.lanes = 32;
         }
     } else if (kind == KIND_MAXSAT) {
         t.vec = R % 2 == 0 && (R > 64 || (R == 64 && vals >= 1e6)) ? 2 : 1;

@@ -77,3 +77,26 @@ def test_non_temporal_state_of_manipulated_gradients(kind, q, R, nt):
     prob = fem.Problem.maxcut(n, g.u, g.v, g.w) if q == 1 else fem.Problem.bmincut(n, g.u, g.v, g.w, q)
     s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, gradient=fem.GRAD_MANIPULATED, energy_every=0))
     assert s.tile()[3] == nt
+
+
+@pytest.mark.parametrize("n,q,R,lanes", [(6500, 32, 50, 8), (6501, 32, 50, 64), (20001, 32, 24, 8), (3500, 16, 150, 64),
+                                         (3500, 16, 128, 64), (3500, 16, 192, 64), (3500, 16, 200, 16),
+                                         (8000, 16, 66, 32), (8000, 16, 33, 64), (2500, 4, 130, 32), (30000, 2, 130, 64),
+                                         (8000, 4, 200, 64)])
+def test_lanes_of_a_potts_team(n, q, R, lanes):
+    """Both sides of the rule's lines, and the fields of another shape."""
+    g = W.random_sparse_graph(n, 2 * n, seed=1, weights="one")
+    prob = fem.Problem.bmincut(n, g.u, g.v, g.w, q)
+    h0 = torch.randn((n, R, q), device="cuda", generator=torch.Generator("cuda").manual_seed(R)) * 0.3
+    out = []
+    for tile in (None, (q, 2, 3, 0, 0)):
+        s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, lam=0.1))
+        if tile:
+            s.set_tile(*tile)
+        else:
+            assert s.tile()[4] == lanes
+        s.set_fields(h0)
+        s.step(2)
+        out.append(s.fields(torch.empty_like(h0)))
+        s.close()
+    assert torch.equal(*out)
