@@ -465,6 +465,7 @@ struct fem_solver {
     double* csum = nullptr;
     double* ctil = nullptr;
     // evaluation
+    TileSet es;                // its tiles, where it does not take those of the steps
     uint8_t* sigma = nullptr;
     double* vpart = nullptr;
     double* vtmp = nullptr;
@@ -539,7 +540,9 @@ static bool valid_shape(const fem_solver* s, const TileShape& t)
 static void free_tiling(fem_solver* s)
 {
     dfree(s->ts.tiles);
+    dfree(s->es.tiles);
     s->ts = TileSet{};
+    s->es = TileSet{};
     dfree(s->epart);
     dfree(s->etmp);
     dfree(s->cpart);
@@ -634,20 +637,32 @@ static fem_status setup_tiling(fem_solver* s, const TileShape& shape)
     const int tile_rows = s->dense ? s->dshape.rows : s->geo.teams_per_block * shape.rows;
     STCHK(make_tiles(p, tile_rows, s->geo.seg_major != 0, s->ts));
     s->geo.n_tiles = s->ts.n_tiles;
+    // The evaluation by bytes holds one replica per lane, so that tiles made
+    // for short teams are long for it (a team then walks eight rows and more,
+    // on fewer workgroups): it takes at most the rows of eval_shape (8000 nodes of
+    // degree 40, q = 32, R = 50: 446 us a fem_best with 64 rows a tile, 384 with
+    // 16).
+    if (!s->bits) {
+        const TileShape ev = eval_shape(s->kind, s->R);
+        const LaunchGeom g = make_geom(s->kind == KIND_BMINCUT ? 1 : ev.vec, s->R, ev.waves);
+        const int rows = g.teams_per_block * ev.rows;
+        if (tile_rows > rows) STCHK(make_tiles(p, rows, false, s->es));
+    }
+    const TileSet& ets = s->es.tiles ? s->es : s->ts;
     s->egeo = make_geom(1, s->R, shape.waves);
-    s->egeo.n_tiles = s->ts.n_tiles;
+    s->egeo.n_tiles = ets.n_tiles;
     const size_t R = (size_t)s->R;
     HIPCHK(dalloc(&s->epart, (size_t)s->ts.n_tiles * s->NE * R));
     HIPCHK(dalloc(&s->etmp, (size_t)s->ts.n_chunks * s->NE * R));
     if (!s->bits) {
-        HIPCHK(dalloc(&s->vpart, (size_t)s->ts.n_tiles * R));
-        HIPCHK(dalloc(&s->vtmp, (size_t)s->ts.n_chunks * R));
+        HIPCHK(dalloc(&s->vpart, (size_t)ets.n_tiles * R));
+        HIPCHK(dalloc(&s->vtmp, (size_t)ets.n_chunks * R));
     }
     if (s->kind == KIND_BMINCUT) {
         HIPCHK(dalloc(&s->cpart, (size_t)s->ts.n_tiles * R * s->q));
         HIPCHK(dalloc(&s->ctmp, (size_t)s->ts.n_chunks * R * s->q));
-        HIPCHK(dalloc(&s->spart, (size_t)s->ts.n_tiles * R * s->q));
-        HIPCHK(dalloc(&s->stmp, (size_t)s->ts.n_chunks * R * s->q));
+        HIPCHK(dalloc(&s->spart, (size_t)ets.n_tiles * R * s->q));
+        HIPCHK(dalloc(&s->stmp, (size_t)ets.n_chunks * R * s->q));
     }
     return FEM_OK;
 }
@@ -780,11 +795,12 @@ static fem_status finish(fem_solver* s, int t)
 // integer evaluation of the byte configurations sigma into vout (and sout)
 static fem_status eval_bytes(fem_solver* s, const uint8_t* sigma)
 {
-    HIPCHK(launch_eval(*s->prob, s->egeo, s->shape.waves, s->ts.tiles, s->R, sigma, s->vpart, s->spart, s->stream));
-    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off, s->n_inst,
+    const TileSet& t = s->es.tiles ? s->es : s->ts;
+    HIPCHK(launch_eval(*s->prob, s->egeo, s->shape.waves, t.tiles, s->R, sigma, s->vpart, s->spart, s->stream));
+    HIPCHK(launch_seg_reduce<double>(s->vpart, s->R, t.chunk_off, t.n_chunks, t.inst_chunk_off, s->n_inst,
                                      s->vtmp, s->vout, s->stream));
     if (s->kind == KIND_BMINCUT) {
-        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, s->ts.chunk_off, s->ts.n_chunks, s->ts.inst_chunk_off,
+        HIPCHK(launch_seg_reduce<int>(s->spart, s->R * s->q, t.chunk_off, t.n_chunks, t.inst_chunk_off,
                                       s->n_inst, s->stmp, s->sint, s->stream));
         HIPCHK(launch_sizes_widen((size_t)s->n_inst * s->R * s->q, s->sint, s->sout, s->stream));
     }

@@ -100,3 +100,28 @@ def test_lanes_of_a_potts_team(n, q, R, lanes):
         out.append(s.fields(torch.empty_like(h0)))
         s.close()
     assert torch.equal(*out)
+
+
+@pytest.mark.parametrize("q,R,tile", [(16, 100, None), (32, 50, None), (32, 20, (32, 4, 64, 0, 8)), (4, 7, (4, 16, 64, 0, 0)),
+                                      (1, 20, (4, 8, 16, 0, 0)), (1, 6, (2, 1, 64, 0, 2))])
+def test_evaluation_of_large_tiles(q, R, tile):
+    """Read-outs by bytes under step tiles of many rows: the best replica and the
+    values seen on the way are those of the evaluation entry point."""
+    n = 2500
+    g = W.random_sparse_graph(n, 3 * n, seed=2, weights="one")
+    w = np.arange(1, g.u.size + 1, dtype=np.float32) % 7 + 2     # integral, not +-1
+    prob = fem.Problem.maxcut(n, g.u, g.v, w) if q == 1 else fem.Problem.bmincut(n, g.u, g.v, w, q)
+    s = fem.Solver(prob, fem.default_params(replicas=R, steps=20, lam=0.5, eval_every=2))
+    if tile:
+        s.set_tile(*tile)
+    s.set_fields(W.initial_fields(n, R, seed=3, std=0.3, q=q) if q > 1 else W.initial_fields(n, R, seed=3, std=0.3))
+    best = None
+    for _ in range(3):
+        s.step(2)
+        sig = s.round()
+        value, sizes = prob.eval_int(sig)
+        score = -value[0].astype(float) if q == 1 else 2.0 * value[0] + 0.5 * (sizes[0] * (sizes[0] - 1)).sum(axis=1)
+        best = score if best is None else np.minimum(best, score)
+    rep, val, cfg = s.best()
+    assert rep[0] == score.argmin() and val[0] == value[0][rep[0]] and np.array_equal(cfg, sig[rep[0]])
+    assert np.array_equal(s.anytime_best()[0], -best if q == 1 else best)
