@@ -184,13 +184,15 @@ inline TileShape eval_shape(int kind, int R)
 //    but 30000 nodes, q = 2, 7.7 MB: 116 / 130, and R = 200, seven segments, 8000
 //    nodes, q = 4: 135 / 162).  At q >= 16 a lane's states alone are a cache
 //    line: up to 6500 nodes down to eight lanes (R = 100, 2400 nodes, q = 16: 86 / 56;
-//    R = 66, 2500, q = 32: 404 / 263; 5000, q = 32, R = 66: 501 / 301); at 8000
-//    and more the gathers of so many segments cost more than the idle lanes
-//    (q = 32, R = 50: 338 / 399; q = 16, R = 33: 68 / 88), but for q = 32 from
-//    20000 nodes on (30000, R = 24: 672 / 603); and not for q = 16 at about two
-//    waves (3500 nodes, R = 150: 217 / 258; R = 200: 316 / 281).  Rows of q = 32
-//    are long: larger tiles from fewer blocks on (8000 nodes, R = 20, two rows
-//    176, four 163).
+//    5000, q = 32, R = 66: 501 / 301), but not for q = 16 at about two waves (3500
+//    nodes, R = 150: 217 / 258; R = 200: 316 / 281); from there to 10000 the gathers
+//    of so many segments cost more than the idle lanes (8000, q = 32, R = 50:
+//    338 / 399; q = 16, R = 33: 68 / 88); above, more than a wave of replicas takes
+//    down to sixteen where each halving leaves some fewer idle (30000, q = 16, R =
+//    100: 694 / 628, R = 66 with 32 451, with 16 432), and for q = 32 from 20000 on
+//    less than a wave down to eight (30000, R = 24: 672 / 603; but 12000, R = 50:
+//    507 / 580).  Rows of q = 32 are long: larger tiles from fewer blocks on (8000
+//    nodes, R = 20, two rows 176, four 163).
 //  * State past the Infinity Cache is not found there again: non-temporal
 //    from 256 MB of state and marginals on (bMinCut 200000 nodes, q = 8, R = 16:
 //    404 / 334; at exactly 256 MB, MaxCut 50000 rows, R = 256: 111 / 111).  With
@@ -211,12 +213,15 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
             const LaunchGeom g = make_geom(1, R, t.waves, l);
             return (double)R / ((double)g.nseg * g.lanes);
         };
-        const bool two_waves = q == 16 && n >= 2000 && R > 128 && R < 192;
-        blocks = q == 32 && n > 6500 ? 200 : 448;
+        blocks = q == 32 && n > 6500 ? 180 : 448;
         t.lanes = 64;
-        if (q >= 16 && ((n <= 6500 && !two_waves) || (q == 32 && n > 20000))) {
+        const bool two_waves = q == 16 && n >= 2000 && R > 128 && R < 192;
+        if (q >= 16 && (n <= 6500 ? !two_waves : n > 20000 && q == 32 && R <= 64)) {
             for (int l = 32; l >= 8; l >>= 1)
                 if (used(l) > 1.05 * used(t.lanes)) t.lanes = l;
+        } else if (q >= 16 && n > 10000 && R > 64 && !manip) {
+            for (int l = 32; l >= 16; l >>= 1)
+                if (used(l) >= 1.12 * used(t.lanes)) t.lanes = l;
         } else if (used(32) >= 1.3 * used(64) ||
                    (q < 16 && used(32) >= 1.15 * used(64) && (double)n * 32 * q * copy_bytes <= 2.6e6)) {
             t.lanes = 32;

@@ -79,9 +79,9 @@ def test_non_temporal_state_of_manipulated_gradients(kind, q, R, nt):
     assert s.tile()[3] == nt
 
 
-@pytest.mark.parametrize("n,q,R,lanes", [(6500, 32, 50, 8), (6501, 32, 50, 64), (20001, 32, 24, 8), (3500, 16, 150, 64),
+@pytest.mark.parametrize("n,q,R,lanes", [(6500, 32, 50, 8), (6501, 32, 50, 64), (20000, 32, 24, 32), (20001, 32, 24, 8), (3500, 16, 150, 64),
                                          (3500, 16, 128, 64), (3500, 16, 192, 64), (3500, 16, 200, 16),
-                                         (8000, 16, 66, 32), (8000, 16, 33, 64), (2500, 4, 130, 32), (30000, 2, 130, 64),
+                                         (8000, 16, 66, 32), (10001, 16, 66, 16), (10001, 16, 150, 32), (8000, 16, 33, 64), (2500, 4, 130, 32), (30000, 2, 130, 64),
                                          (8000, 4, 200, 64)])
 def test_lanes_of_a_potts_team(n, q, R, lanes):
     """Both sides of the rule's lines, and the fields of another shape."""
