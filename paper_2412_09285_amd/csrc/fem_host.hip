@@ -1602,7 +1602,7 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     fem_status st = setup_tiling(s, sh);
     if (st != FEM_OK) return bail(st);
     if (s->bits) {
-        st = make_tiles(p, bit_tile_rows(s->n, s->R), false, s->bs);
+        st = make_tiles(p, bit_tile_rows(p, s->R), false, s->bs);
         if (st != FEM_OK) return bail(st);
     }
     st = reset_best(s);

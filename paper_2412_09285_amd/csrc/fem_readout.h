@@ -8,9 +8,11 @@ namespace fem {
 
 // 32-bit words per row of read-out bits: replica r is bit r % 32 of word r / 32
 inline int bit_words(int R) { return (R + 31) / 32; }
-// lanes that share a row in the evaluation, and rows per workgroup
+// words of a row that the lanes of a workgroup take, parts of its entries, each
+// with lanes of its own, and rows per workgroup
 inline int bit_lanes(int R) { return pow2ceil(bit_words(R) < 64 ? bit_words(R) : 64); }
-int bit_tile_rows(int64_t n, int R);
+int bit_parts(const Problem& p, int R);
+int bit_tile_rows(const Problem& p, int R);
 // whether the problem is evaluated on bit words
 bool bit_evaluation(const Problem& p);
 

@@ -114,7 +114,7 @@ struct BitArgs {
     const Tile* tiles;
     const uint32_t* bits;
     int32_t* count;
-    int32_t R, rw, lanes_log2;
+    int32_t R, rw, lanes_log2, parts_log2;
 };
 
 // KIND 0: ordered cut of +-1 weights.  A weight -1 contributes -d = (1 - d) - 1:
@@ -126,8 +126,10 @@ __global__ void __launch_bounds__(256) eval_bits_kernel(BitArgs a)
 {
     extern __shared__ int sums[];   // [words of this segment][32]
     const Tile tile = a.tiles[blockIdx.x];
-    const int L = 1 << a.lanes_log2, tl = threadIdx.x & (L - 1), team = threadIdx.x >> a.lanes_log2;
-    const int teams = 256 >> a.lanes_log2, w0 = blockIdx.y * L, w = w0 + tl;
+    const int L = 1 << a.lanes_log2, tl = threadIdx.x & (L - 1);
+    const int parts = 1 << a.parts_log2, part = (threadIdx.x >> a.lanes_log2) & (parts - 1);
+    const int team = threadIdx.x >> (a.lanes_log2 + a.parts_log2), teams = 256 >> (a.lanes_log2 + a.parts_log2);
+    const int w0 = blockIdx.y * L, w = w0 + tl;
     const int words = min(L, a.rw - w0);
     for (int k = threadIdx.x; k < words * 32; k += 256) sums[k] = 0;
     __syncthreads();
@@ -145,9 +147,8 @@ __global__ void __launch_bounds__(256) eval_bits_kernel(BitArgs a)
         };
         for (int i = tile.row_begin + team; i < tile.row_end; i += teams) {
             const uint32_t own = bits[(size_t)i * rw];
-            int64_t k = a.row_off[i];
             const int64_t kend = a.row_off[i + 1];
-            for (; k < kend; k += 4) {
+            for (int64_t k = a.row_off[i] + 4 * part; k < kend; k += 4 * parts) {
                 room();
                 uint32_t x[4];
                 if constexpr (KIND == 0) {
@@ -310,13 +311,25 @@ bool bit_evaluation(const Problem& p)
     return p.nnz <= INT32_MAX && (p.kind == KIND_MAXSAT || (p.kind == KIND_MAXCUT && p.adj_pm1 != nullptr));
 }
 
+// Long rows of few words are shared by several lanes while a lane keeps 32
+// entries and more and the chip has lanes to spare: alone, a lane of a complete
+// graph walks its row through as many dependent rounds as it has entries / 4
+// (a read-out of n = 2500, R = 8: 705 us, by bytes 549, in 64 parts 27).
+int bit_parts(const Problem& p, int R)
+{
+    int parts = 1;
+    while (bit_lanes(R) * parts < 64 && p.nnz / p.n >= 64 * parts && (int64_t)p.n * bit_lanes(R) * parts < 1 << 18)
+        parts <<= 1;
+    return parts;
+}
+
 // A lane's 32 counters are flushed at the end of its rows (some 700
 // instructions): up to eight rows a lane, fewer while that would leave less
 // than 512 workgroups.
-int bit_tile_rows(int64_t n, int R)
+int bit_tile_rows(const Problem& p, int R)
 {
-    const int teams = 256 / bit_lanes(R);
-    const int64_t rows = n / ((int64_t)teams * 512);
+    const int teams = 256 / (bit_lanes(R) * bit_parts(p, R));
+    const int64_t rows = p.n / ((int64_t)teams * 512);
     return teams * (int)(rows < 1 ? 1 : rows > 8 ? 8 : rows);
 }
 
@@ -348,6 +361,7 @@ hipError_t launch_eval_bits(const Problem& p, int32_t R, const Tile* tiles, int 
     a.rw = bit_words(R);
     const int L = bit_lanes(R);
     while ((1 << a.lanes_log2) < L) ++a.lanes_log2;
+    while ((1 << a.parts_log2) < bit_parts(p, R)) ++a.parts_log2;
     const dim3 g(n_tiles, (a.rw + L - 1) / L);
     const size_t lds = (size_t)L * 32 * sizeof(int);
     if (p.kind == KIND_MAXCUT) eval_bits_kernel<0><<<g, 256, lds, st>>>(a);

@@ -72,3 +72,16 @@ def test_bmincut_and_real_weights(q, R):
     check(fem.Problem.bmincut(g.n, g.u, g.v, g.w, q), R)
     w = np.round(W.rng_for(3).standard_normal(g.u.size) * 5).astype(np.float32)   # integral, not +-1
     check(fem.Problem.maxcut(g.n, g.u, g.v, w), R)
+
+
+@pytest.mark.parametrize("n,edges,R", [(129, 129 * 64, 1), (129, 128 * 64, 32), (700, 700 * 699 // 2, 33), (1500, 300000, 64),
+                                       (2100, 2100 * 2099 // 2, 1), (2100, 2100 * 2099 // 2, 100), (2100, 2000000, 257)])
+def test_rows_shared_by_several_lanes(n, edges, R):
+    """Mean degrees around 64 and far above, where the lanes of a row split its entries."""
+    g = W.er_graph_m(n, edges, seed=n, weights="pm1")
+    check(fem.Problem.maxcut(g.n, g.u, g.v, g.w), R)
+
+
+@pytest.mark.parametrize("k", [3, 4])
+def test_clauses_shared_by_several_lanes(k):
+    check(fem.Problem.from_cnf(W.random_ksat(60, 9000, k, seed=k)), 40)
