@@ -11,7 +11,8 @@ namespace fem {
 // values; Max-k-SAT four per thread and 15 bits.
 constexpr int RES_MAX_ROWS = 8 * 1024 - 2;
 constexpr int RES_MAX_ROWS_SAT = 4 * 1024 - 8;
-// Entries (of 8 bytes) that may be streamed from L2 instead of lying in LDS.
+// Entries (of 8 bytes, and 16 of weights where they are not +-1) that may be
+// streamed from L2 instead of lying in LDS, at most.
 constexpr int64_t RES_MAX_STREAM = 1 << 16;
 // LDS for the energy terms of the waves, in front of the values
 constexpr int RES_PART_BYTES = 2 * 16 * 2 * 8;
@@ -45,6 +46,7 @@ struct ResClass {
     int n_inst = 0;
     int first = 0;         // offset into ResTables::inst
     bool adj_lds = false;  // every instance's entries fit in LDS beside the marginals
+    int64_t stream = 0;    // else the most entries of one instance
     size_t lds = 0;        // dynamic LDS of the launch
 };
 

@@ -535,6 +535,7 @@ static void res_plan_all(const Problem& p, ResTables& t)
         }
         t.classes.back().n_inst++;
         t.classes.back().lds = std::max(t.classes.back().lds, plan.lds);
+        if (!plan.adj_lds) t.classes.back().stream = std::max(t.classes.back().stream, plan.n_adj);
         t.threads += (uint64_t)plan.threads;
         in.inst = b;
         in.n = rows_of(b);
@@ -667,13 +668,27 @@ static hipError_t res_build(const Problem& p, ResTables& t)
 // launch (R = 20, bfloat16, 2000 and 11361 nodes: 457 us for 24 steps, both
 // row-tiled 368; sixty-four of 1000 .. 50000 nodes at R = 32: 4035 and 3869 for
 // 25).
-// In LDS it won at every size measured (the table above).  Streaming, at
-// R = 16, resident against the best row-tiled shape: n = 2000 of degree 100
-// (51 k entries of 8 bytes) 11.4 / 12.5 us, n = 2000 of degree 120 (61 k)
-// 13.5 / 13.2 us, n = 1000 of degree 250 (63 k) 13.3 / 15.5 us, and at
-// R = 512 24 / 31, 29 / 35 and 29 / 46 us; beyond, one compute unit reads for
-// longer than the whole chip needs.  Eight rows per thread are instantiated
-// only where they fit the registers: +-1 weights, entries in LDS.
+// In LDS it won at every size measured (the table above).  Streaming, one
+// compute unit reads all entries while the row-tiled kernels read them from the
+// whole chip, which pays as long as few replicas leave most of it idle: the more
+// rows, the fewer entries.  us a step, resident / row-tiled, R = 16 and R = 64:
+//                                     explicit            manipulated
+//   n = 1000, +-1,    62 k entries   12.3/14.6 12.4/15.1  11.8/18.7 12.0/19.7
+//   n = 2000, +-1,    50 k           11.0/10.9 11.1/13.7  10.4/10.4 10.7/13.2
+//   n = 4000, +-1,    32 k            8.5/9.3   8.7/15.6   7.8/6.5   8.0/8.2
+//   n = 4000, +-1,    48 k           11.4/9.8  11.6/17.4  10.7/7.5  11.0/9.5
+//   n = 1000, others, 62 k           16.9/15.0 17.0/15.5  16.4/18.9 16.6/19.7
+//   n = 2000, others, 30 k            8.8/9.8   8.9/12.6   8.4/7.9   8.6/9.7
+//   n = 2000, others, 50 k           13.5/11.3 13.7/14.6  13.2/10.6 13.6/13.2
+//   n = 4000, others, 24 k            7.9/9.1   8.2/14.0   7.2/5.7   7.5/7.1
+//   n = 4000, others, 48 k           13.7/9.8  13.8/17.1  13.0/7.6  13.4/9.4
+//   n = 4000, 3-SAT,  45 k           13.4/11.5 13.7/17.4
+// (R = 128, n = 4000, 48 k: 12.1/20.7 and 11.3/12.1).  So RES_MAX_STREAM entries of
+// one row per thread, three quarters of two, half of four (a quarter with
+// manipulated gradients, three quarters for Max-k-SAT), times three quarters for
+// other weights, twice as many from R = 64 on, four times from 128 on.  Eight rows
+// per thread are instantiated only where they fit the registers: +-1 weights,
+// entries in LDS.
 // A launch has a workgroup per (instance, replica), and HIP takes fewer than
 // 2^32 threads.
 //
@@ -713,6 +728,11 @@ hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, R
             steps = std::max(steps, (filled ? 1 : 2) * (manip ? 2 : 1) * c.rpt);
         }
     if (eval_every > 0 && eval_every < steps) return hipSuccess;
+    for (const ResClass& c : t.classes) {
+        const double rows = c.rpt == 1 ? 1.0 : c.rpt == 2 || p.kind == KIND_MAXSAT ? 0.75 : manip ? 0.25 : 0.5;
+        const double limit = rows * (t.pm1 || p.kind == KIND_MAXSAT ? 1.0 : 0.75) * (R < 64 ? 1 : R < 128 ? 2 : 4);
+        if ((double)c.stream > limit * (double)RES_MAX_STREAM) return hipSuccess;
+    }
     if (!t.block) {
         const hipError_t e = res_build(p, t);
         if (e != hipSuccess) return e;

@@ -215,3 +215,30 @@ def test_solvers_of_one_problem_share_its_tables(kind):
             for n, h in zip((40, 33), got):
                 ref[k].step(n)
                 assert np.array_equal(ref[k].fields(), h), k
+
+
+@pytest.mark.parametrize("n,deg,weights,R,manip,resident", [
+    (1000, 250, "pm1", 16, False, True), (1000, 250, "real", 16, False, False), (1000, 180, "real", 16, False, True),
+    (2000, 100, "one", 16, False, False), (2000, 90, "one", 16, False, True), (2000, 100, "real", 64, False, True),
+    (4000, 48, "pm1", 16, False, False), (4000, 48, "pm1", 64, False, True), (4000, 24, "pm1", 16, True, False),
+    (4000, 24, "pm1", 64, True, True), (4000, 20, "real", 63, True, False), (4000, 20, "real", 64, True, True)])
+def test_entries_that_stream(n, deg, weights, R, manip, resident):
+    """Long ranges with entries beyond LDS, on both sides of the rule: resident
+    energies round otherwise than the shaped kernels' where a thread holds several
+    rows; the fields are the same."""
+    prob = graph(n, deg, weights)
+    kw = {} if not manip else dict(gradient=fem.GRAD_MANIPULATED, energy_every=0)
+    h0 = W.initial_fields(n, R, seed=8, std=1.0)
+    out = []
+    for tiled in (False, True):
+        s = fem.Solver(prob, fem.default_params(replicas=R, steps=80, **kw), stream=torch.cuda.Stream())
+        if tiled:
+            s.set_tile(*s.tile())
+        s.set_fields(h0)
+        s.run_until(40)
+        s.step(40)
+        out.append((s.fields(), None if manip else np.array(s.energies())))
+        s.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    if not manip and (n > 1024 or not resident):
+        assert np.array_equal(out[0][1], out[1][1]) != resident
