@@ -59,6 +59,7 @@ struct ResTables {
     uint64_t threads = 0;         // of one replica of every instance
     bool pm1 = false;             // graphs: weights +-1, carried in the entries
     int planes = 1;               // values per position that neighbours read
+    int dev_lds = 0;              // LDS a workgroup may use
     std::vector<ResInst> h_inst;  // the plan, until the tables are on the device
     std::vector<int32_t> h_perm;
     void* block = nullptr;        // device: the one allocation behind the tables

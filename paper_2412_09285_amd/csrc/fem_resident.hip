@@ -498,9 +498,8 @@ static void res_plan_all(const Problem& p, ResTables& t)
 {
     t.planned = true;
     const bool sat = p.kind == KIND_MAXSAT;
-    int dev_lds = 0;
     if (p.kind == KIND_BMINCUT || p.dense_w ||
-        hipDeviceGetAttribute(&dev_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device) != hipSuccess)
+        hipDeviceGetAttribute(&t.dev_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, p.device) != hipSuccess)
         return;
     auto rows_of = [&](int b) { return (int)(p.inst_off[(size_t)b + 1] - p.inst_off[(size_t)b]); };
     std::vector<int> ids((size_t)p.n_inst);
@@ -518,7 +517,7 @@ static void res_plan_all(const Problem& p, ResTables& t)
     for (int b : ids) {
         ResInst in{};
         in.pos0 = (int32_t)t.h_perm.size();
-        const ResPlan plan = res_plan(p, b, t.planes, t.pm1 || sat, (size_t)dev_lds, count, t.h_perm);
+        const ResPlan plan = res_plan(p, b, t.planes, t.pm1 || sat, (size_t)t.dev_lds, count, t.h_perm);
         if (!plan.ok) {
             t = ResTables{};
             t.planned = true;
@@ -795,8 +794,10 @@ hipError_t resident_launch(const Problem& p, const ResData& r, int cls, bool man
     ResKernel k = c.adj_lds ? pick<true>(p, t.pm1, manip, c.rpt) : pick<false>(p, t.pm1, manip, c.rpt);
     if (!k) return hipErrorInvalidValue;
     if (c.lds > 64 * 1024) {
+        // the attribute is the kernel's, for all threads: one value, so that
+        // another solver does not lower it between this call and the launch
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)c.lds);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, t.dev_lds);
         if (e != hipSuccess) return e;
     }
     k<<<dim3((unsigned)c.n_inst * (unsigned)a.R), dim3(c.threads), c.lds, st>>>(a);

@@ -242,3 +242,27 @@ def test_entries_that_stream(n, deg, weights, R, manip, resident):
     assert np.array_equal(out[0][0], out[1][0])
     if not manip and (n > 1024 or not resident):
         assert np.array_equal(out[0][1], out[1][1]) != resident
+
+
+def test_threads_that_need_different_amounts_of_lds():
+    """Two problems run by the same kernel with 80 and 112 KB of LDS, stepped by
+    two threads at once."""
+    made = []
+    for k, deg in enumerate((12, 20)):
+        prob = graph(2000, deg)
+        h0 = W.initial_fields(2000, 4, seed=9 + k, std=0.4)
+        ref = solver(prob, 4, "maxcut", True)
+        s = solver(prob, 4, "maxcut", False)
+        for x in (s, ref):
+            x.set_fields(h0)
+        ref.step(400)
+        made.append((s, ref.fields()))
+
+    def go(k):
+        for _ in range(50):
+            made[k][0].step(8)
+        return made[k][0].fields()
+
+    with ThreadPoolExecutor(2) as pool:
+        for (_, want), got in zip(made, pool.map(go, (0, 1))):
+            assert np.array_equal(got, want)
