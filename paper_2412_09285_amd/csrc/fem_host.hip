@@ -398,8 +398,8 @@ static fem_status build_sat(int device, int32_t n_vars, int64_t n_clauses, const
 }
 
 // ------------------------------------------------------------------ solver --
-// The tiles of a set of instances and the chunks that their partial sums are
-// reduced by (an instance outside the set has no chunks).
+// The tiles of a problem's instances and the chunks that their partial sums are
+// reduced by.
 struct TileSet {
     Tile* tiles = nullptr;
     int32_t* chunk_off = nullptr;
@@ -491,7 +491,6 @@ struct fem_solver {
     std::vector<std::pair<hipEvent_t, hipEvent_t>> prof_events;
     size_t prof_used = 0;
     int64_t prof_steps = 0;   // steps that the recorded intervals cover
-    hipEvent_t res_end = nullptr;   // end of the interval around resident steps, while it is open
     bool capturing = false;
 };
 
@@ -880,10 +879,10 @@ static fem_status profile_begin(fem_solver* s, int n, hipEvent_t* end)
 
 // Steps [s->t, t_end) of a resident solver, a launch per class.  A class is a
 // few dozen workgroups for tens of microseconds a step, so several classes run
-// side by side: joined[k] says which side streams the solver's stream has to
-// wait for (join_side).  Side by side, three instances of 1100, 2500 and 6000
-// nodes at R = 16 take 8.6 us per step, one after the other 13.1.
-static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_solver::N_SIDE])
+// side by side, the first on the solver's stream and the others on its side
+// streams.  Side by side, three instances of 1100, 2500 and 6000 nodes at R = 16
+// take 8.6 us per step, one after the other 13.1.
+static fem_status resident_steps(fem_solver* s, int t_end)
 {
     ResArgs a{};
     a.wtot = s->d_wtot;
@@ -901,31 +900,20 @@ static fem_status resident_steps(fem_solver* s, int t_end, bool (&joined)[fem_so
     a.bf16 = s->dtype == FEM_BF16;
     const int classes = (int)s->res.t->classes.size();
     s->marg_ok = false;
-    STCHK(profile_begin(s, t_end - s->t, &s->res_end));
-    if (s->fork) HIPCHK(hipEventRecord(s->fork, s->stream));
+    hipEvent_t end = nullptr;
+    STCHK(profile_begin(s, t_end - s->t, &end));
+    const int side = s->fork ? std::min(classes - 1, fem_solver::N_SIDE) : 0;   // side streams in use
+    if (side) HIPCHK(hipEventRecord(s->fork, s->stream));
+    for (int k = 0; k < side; ++k) HIPCHK(hipStreamWaitEvent(s->side[k], s->fork, 0));
     for (int c = 0; c < classes; ++c) {
-        // the solver's stream takes the first class
-        const int k = s->fork ? (c + fem_solver::N_SIDE) % (fem_solver::N_SIDE + 1) : fem_solver::N_SIDE;
-        hipStream_t st = s->stream;
-        if (k < fem_solver::N_SIDE) {
-            st = s->side[k];
-            if (!joined[k]) HIPCHK(hipStreamWaitEvent(st, s->fork, 0));
-            joined[k] = true;
-        }
-        HIPCHK(resident_launch(*s->prob, s->res, c, s->manip, a, st));
+        const int k = c % (side + 1);
+        HIPCHK(resident_launch(*s->prob, s->res, c, s->manip, a, k ? s->side[k - 1] : s->stream));
     }
-    return FEM_OK;
-}
-
-static fem_status join_side(fem_solver* s, const bool (&joined)[fem_solver::N_SIDE])
-{
-    for (int k = 0; k < fem_solver::N_SIDE; ++k)
-        if (joined[k]) {
-            HIPCHK(hipEventRecord(s->join[k], s->side[k]));
-            HIPCHK(hipStreamWaitEvent(s->stream, s->join[k], 0));
-        }
-    if (s->res_end) HIPCHK(hipEventRecord(s->res_end, s->stream));
-    s->res_end = nullptr;
+    for (int k = 0; k < side; ++k) {
+        HIPCHK(hipEventRecord(s->join[k], s->side[k]));
+        HIPCHK(hipStreamWaitEvent(s->stream, s->join[k], 0));
+    }
+    if (end) HIPCHK(hipEventRecord(end, s->stream));
     return FEM_OK;
 }
 
@@ -977,13 +965,11 @@ static fem_status do_steps(fem_solver* s, int t_end)
     while (s->t < t_end) {
         int e = t_end;
         if (s->prm.eval_every > 0) e = std::min(e, (s->t / s->prm.eval_every + 1) * s->prm.eval_every);
-        bool joined[fem_solver::N_SIDE] = {};
-        if (resident) STCHK(resident_steps(s, e, joined));
+        if (resident) STCHK(resident_steps(s, e));
         for (; s->t < e; ++s->t) {
             if (!resident) STCHK(tiled_step(s));
             if (energy_due(s, s->t)) s->last_energy_step = s->t;
         }
-        if (resident) STCHK(join_side(s, joined));
         if (eval_due(s, s->t)) STCHK(readout_eval(s, true));
     }
     return FEM_OK;

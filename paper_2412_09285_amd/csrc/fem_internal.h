@@ -297,7 +297,7 @@ hipError_t launch_seg_reduce(const T* part, int cols, const int32_t* chunk_off, 
                              const int32_t* inst_chunk_off, int n_inst, T* tmp, T* out,
                              hipStream_t st);
 // What follows a step (energies, bMinCut column sums), from the per-tile
-// partials of every instance that has tiles.
+// partials of every instance.
 struct FinishArgs {
     const double* epart;          // [tile or chunk][NE][R]
     const long long* cpart;       // [tile or chunk][R][q]

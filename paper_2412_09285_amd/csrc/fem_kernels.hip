@@ -759,7 +759,6 @@ __global__ void __launch_bounds__(FINISH_THREADS) finish_kernel(FinishArgs a)
         t0 = a.chunk_off[t0];
         t1 = a.chunk_off[t1];
     }
-    if (t0 == t1) return;   // nothing of this instance is formed from tiles
     if constexpr (NE > 0) {
         const int rows = blockDim.x / G, g = tid & (G - 1), sub = tid / G;
         double acc[NE];

@@ -3,6 +3,9 @@ against the row-tiled kernels, which an explicit launch shape selects: fields,
 gradients and anytime bests bit for bit, energies up to the rounding of their
 float32 per-lane terms; ranges split anywhere; batches in which some
 instances are resident and others are not."""
+# (A batch is resident as a whole or row-tiled as a whole: test_mixed_batch holds
+# batches that are row-tiled against their instances alone, some of which are
+# resident; test_gpu_resident_ranges.py has batches that are resident.)
 import numpy as np
 import pytest
 import torch
