@@ -1398,8 +1398,8 @@ void fem_params_default(fem_params* p)
 
 // evaluation: a solver that only evaluates configurations (it takes no steps,
 // so no instance is made resident)
-static fem_status create_solver(const fem_problem* fp, const fem_params* prm, void* hip_stream, bool evaluation,
-                                fem_solver** out)
+static fem_status create_solver_or_throw(const fem_problem* fp, const fem_params* prm, void* hip_stream, bool evaluation,
+                                         fem_solver** out)
 {
     if (!out) return fail(FEM_E_INVAL, "out is NULL");
     *out = nullptr;
@@ -1433,6 +1433,10 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
         return fail(FEM_E_NOMEM, "state of %lld values does not fit", (long long)p.n * P.replicas);
     auto* s = new (std::nothrow) fem_solver;
     if (!s) return fail(FEM_E_NOMEM, "host allocation failed");
+    struct Unwind {   // of an exception: what is made so far goes
+        fem_solver* s;
+        ~Unwind() { destroy_solver(s); }
+    } unwind{s};
     s->owner = const_cast<fem_problem*>(fp);
     {
         std::lock_guard<std::mutex> lock(s->owner->lock);
@@ -1467,6 +1471,7 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     auto bail = [&](fem_status st) {
         std::string keep = g_err;
         destroy_solver(s);
+        unwind.s = nullptr;
         g_err = keep;
         return st;
     };
@@ -1594,7 +1599,20 @@ static fem_status create_solver(const fem_problem* fp, const fem_params* prm, vo
     st = reset_best(s);
     if (st != FEM_OK) return bail(st);
     *out = s;
+    unwind.s = nullptr;
     return FEM_OK;
+}
+
+// Host memory may run out: a resident schedule of 2^20 steps has a table of 109 MB,
+// and a batch of many instances its re-ordered entries.
+static fem_status create_solver(const fem_problem* fp, const fem_params* prm, void* hip_stream, bool evaluation,
+                                fem_solver** out)
+{
+    try {
+        return create_solver_or_throw(fp, prm, hip_stream, evaluation, out);
+    } catch (const std::bad_alloc&) {
+        return fail(FEM_E_NOMEM, "host allocation failed");
+    }
 }
 
 fem_status fem_solver_create(const fem_problem* fp, const fem_params* prm, void* hip_stream, fem_solver** out)
