@@ -110,10 +110,11 @@ __device__ __forceinline__ double row16_sum(double x) { return add_ror<1>(add_ro
 // The wave's sums of the two energy terms, in double and in a fixed order, to
 // its slots of part: the lower half-wave sums the first term, the upper the
 // second.
-__device__ __forceinline__ void res_partial(const ResCtx& c, int t, float e0, float e1)
+template <typename T>
+__device__ __forceinline__ void res_partial(const ResCtx& c, int t, T e0, T e1)
 {
     const bool up = c.lane >= 32;
-    const float other = __shfl_xor(up ? e0 : e1, 32, 64);
+    const T other = __shfl_xor(up ? e0 : e1, 32, 64);
     double x = row16_sum((double)(up ? e1 : e0) + (double)other);
     x += __shfl_xor(x, 16, 64);
     if ((c.lane & 31) == 0) c.part[((t & 1) * 16 + c.wave) * 2 + (up ? 1 : 0)] = x;
@@ -313,13 +314,23 @@ __global__ void __launch_bounds__(1024) res_maxcut_kernel(ResArgs a)
             q1 = n1;
             if constexpr (TWO) update(k, acc[k]);
         }
-        if constexpr (!TWO) {
+        if constexpr (TWO) {
+            if (en) res_partial(c, t, e0, e1);
+        } else {
             __syncthreads();   // every gather has read the old values
+            // at most four float32 terms to a sum, as on the row-tiled kernels
+            double f0 = 0.0, f1 = 0.0;
 #pragma unroll
-            for (int k = 0; k < RPT; ++k)
+            for (int k = 0; k < RPT; ++k) {
                 if ((k * c.nwaves + c.wave) * 64 < c.in.n) update(k, acc[k]);
+                if (k % 4 == 3) {
+                    f0 += (double)e0;
+                    f1 += (double)e1;
+                    e0 = e1 = 0.0f;
+                }
+            }
+            if (en) res_partial(c, t, f0, f1);
         }
-        if (en) res_partial(c, t, e0, e1);
         sc = uniform_at(a.steps, t + 1).sc;   // the table has an entry beyond the last step
         __syncthreads();
         if (en && c.wave == c.nwaves - 1) res_energy(a, c, t);

@@ -266,3 +266,25 @@ def test_threads_that_need_different_amounts_of_lds():
     with ThreadPoolExecutor(2) as pool:
         for (_, want), got in zip(made, pool.map(go, (0, 1))):
             assert np.array_equal(got, want)
+
+
+def test_energy_sums_of_eight_rows_per_thread():
+    """Equal fields in every row, one per replica: entropies that are sums of
+    equal float32 terms.  Where a term's last two mantissa bits are zero, sums of
+    up to four are exact in float32 (of five to eight they are not), and so is
+    the entropy in double."""
+    n, R = 8190, 256
+    h = np.linspace(0.05, 2.5, R, dtype=np.float32)
+    prob = fem.Problem.maxcut(n, [0], [1], [1.0])
+    one = fem.Problem.maxcut(1, [], [])
+    S = []
+    for p, rows in ((prob, n), (one, 1)):
+        s = fem.Solver(p, fem.default_params(replicas=R, steps=100, energy_every=100), stream=torch.cuda.Stream())
+        s.set_fields(np.tile(h, (rows, 1)))
+        s.step(40)
+        S.append(s.energies()[1][0])
+    term = S[1].astype(np.float32)
+    assert np.array_equal(term.astype(np.float64), S[1])
+    exact = (term.view(np.uint32) & 3) == 0
+    assert exact.sum() > 30
+    assert np.array_equal(S[0][exact], n * S[1][exact])
