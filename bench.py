@@ -31,7 +31,9 @@ roofline.traffic is the HBM traffic of one launch measured with the
 FETCH_SIZE and WRITE_SIZE counters (scaled by a plain copy of known size),
 read from the committed counter summary of the workload; it is null when the
 kernel sources, launch shape or marginal type differ from the ones the
-counters were taken with.
+counters were taken with.  er800 runs all its steps in one launch that keeps a
+replica on one compute unit: its roofline is the LDS read rate of the units
+in use.
 """
 import argparse
 import hashlib
@@ -46,6 +48,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
+LDS_PEAK_GBS_PER_CU = 307.2   # 128 B a clock at 2.4 GHz
 MFMA_F64_PEAK_TFLOPS = 78.6
 MFMA_I8_PEAK_TOPS = 5000.0
 
@@ -75,6 +78,7 @@ KERNEL_SOURCES = {
     "explicit": ["fem_kernels.hip", "fem_device.h", "fem_internal.h"],
     "manipulated": ["fem_manip.hip", "fem_device.h", "fem_internal.h"],
     "dense": ["fem_dense.hip", "fem_dense.h", "fem_device.h", "fem_internal.h"],
+    "resident": ["fem_resident.hip", "fem_resident.h", "fem_device.h", "fem_internal.h"],
 }
 
 
@@ -235,7 +239,7 @@ def main():
                     default="batch512",
                     help="batch512 (default): 512 uneven MaxCut instances, R = 32, in one launch per step, with time "
                          "to target; maxcut1e5: N = 10^5, R = 256; bmincut1e6 / max3sat1e5: the Potts and Max-3-SAT "
-                         "kernels at full size; er800: a G-set-sized instance (800 nodes, R = 16), launch-bound; "
+                         "kernels at full size; er800: a G-set-sized instance (800 nodes, R = 16), resident; "
                          "k2000dense: the dense-W (matrix-core) path on a complete 2000-node graph; "
                          "infer512: the warm-start network's proposal for every replica of the 512-instance batch "
                          "(--steps calls, timed on the device); "
@@ -398,7 +402,7 @@ WORKLOADS = {
                        name="max3sat_n100000_m800000", counters="max3sat_1e5_R64",
                        data="random 3-SAT, distinct variables, fair signs, ratio 8"),
     "er800": dict(kind="maxcut", recipe=1, R=16, seed=101, T=500,
-                  name="maxcut_er_n800_e19176", counters="maxcut_er800_R16",
+                  name="maxcut_er_n800_e19176", counters="maxcut_er800_R16", resident=True,
                   data="Erdos-Renyi G(800, 19176), unit weights"),
     "k2000dense": dict(kind="maxcut_dense", n=2000, R=1000, seed=105, T=1000,
                        name="maxcut_complete_n2000_pm1_dense", counters="maxcut_dense_k2000_R1000",
@@ -489,9 +493,13 @@ def throughput(args):
     s = fem.Solver(prob, fem.default_params(replicas=R, steps=T, marginal_dtype=dtype, **extra), stream=stream)
     s.set_fields(h0)
     tile = s.tile()
-    if not args.no_tune:
+    # a small instance runs its steps on one compute unit per replica, where
+    # no launch shape applies
+    resident = wl.get("resident", False)
+    if not args.no_tune and not resident:
         tile = s.tune(trial_steps=10, use_cache=not args.retune)
-    log(f"launch shape (vec, waves, rows, nt, lanes) = {tile}")
+    log("resident, one workgroup per replica" if resident else
+        f"launch shape (vec, waves, rows, nt, lanes) = {tile}")
     # warm-up: W eager steps, then capture the K-step graph
     s.set_fields(h0)
     s.step(min(Wm, T))
@@ -499,7 +507,7 @@ def throughput(args):
     s.set_fields(h0)
     s.capture(K)
     s.sync()
-    # timed region: one graph launch of all K steps
+    # timed region: one graph (or resident) launch of all K steps
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     s.run_until(K)
@@ -560,6 +568,19 @@ def throughput(args):
                 "hbm_achieved_GBps": round(achieved, 1), "kernel": kname, "kernel_avg_ms": round(kern_ms, 5),
                 "kernel_launches": n_k, "alg_bytes_per_launch": int(alg_bytes),
                 "kernel_sources_sha256": kernel_sources_sha(src)}
+    if resident:
+        # neither the state nor the entries leave the compute unit within a
+        # range: per step and replica each directed entry is two bytes of
+        # offset and four of value read from LDS, on one compute unit of 256
+        lds = 6.0 * nnz * R
+        peak = LDS_PEAK_GBS_PER_CU * R
+        rate = lds / (kern_ms * 1e-3) / 1e9
+        roof = {"bound": "lds", "achieved": round(rate, 1), "peak": round(peak, 1), "unit": "GB/s",
+                "frac": round(rate / peak, 4), "traffic": None, "kernel": "res_maxcut_kernel",
+                "kernel_avg_ms": round(kern_ms, 5), "kernel_launches": 1, "steps_per_launch": n_k,
+                "compute_units": R, "alg_lds_bytes_per_step": int(lds),
+                "alg_bytes_per_launch": 24 * n * R + 4 * nnz,
+                "kernel_sources_sha256": kernel_sources_sha("resident")}
     label = {"maxcut": "cut", "maxcut_dense": "cut", "bmincut": "2 cut + lambda sum |Pi|(|Pi|-1)",
              "maxsat": "unsatisfied clauses"}[kind]
     out = {
@@ -584,8 +605,8 @@ def throughput(args):
                    "state_layout": args.state_layout,
                    "schedule": ("inverse-proportional T 1.16->6e-5, RMSprop lr 0.03 alpha 0.56 momentum 0.63 "
                                 "weight decay 0.013" if kind == "maxcut_dense" else "linear beta 0.01->5, Adam lr 0.1"),
-                   "tile": list(tile),
-                   "parallelism": "single GPU",
+                   "tile": None if resident else list(tile),
+                   "parallelism": "single GPU" if not resident else "single GPU, one compute unit per replica",
                    "node_order": args.order if kind == "bmincut" else "as generated",
                    "order_seconds": order_s if kind == "bmincut" else None},
         "result": {"best": float(val[0]), "best_is": label, "mean_integer": float(np.mean(ints)),
