@@ -445,8 +445,9 @@ struct fem_solver {
     bool always_res = false;  // its steps are part of a caller's graph, which moves the fields unseen
     bool tuning = false;      // the tuner times the row-tiled kernels
     // Side streams for the resident classes after the first, which run beside
-    // it within a range of steps.
+    // it within a range of steps: made once res_steps says that they pay.
     static constexpr int N_SIDE = 2;
+    int64_t res_steps = 0;    // resident steps so far
     hipStream_t side[N_SIDE] = {nullptr, nullptr};
     hipEvent_t fork = nullptr, join[N_SIDE] = {nullptr, nullptr};
     char* block = nullptr;   // the allocation behind the small arrays below
@@ -825,38 +826,6 @@ static fem_status readout_eval(fem_solver* s, bool update_best)
     return FEM_OK;
 }
 
-// Side streams are handed on from solver to solver: creating one takes 80 to
-// 125 us, more than the rest of a small solver.  A stream is returned once the
-// work queued on it is waited for by its solver's stream, and at most 16 are
-// kept per device.
-static std::mutex side_lock;
-static std::map<int, std::vector<hipStream_t>> side_free;
-static hipError_t side_stream(int device, hipStream_t* st)
-{
-    {
-        std::lock_guard<std::mutex> lock(side_lock);
-        std::vector<hipStream_t>& v = side_free[device];
-        if (!v.empty()) {
-            *st = v.back();
-            v.pop_back();
-            return hipSuccess;
-        }
-    }
-    return hipStreamCreateWithFlags(st, hipStreamNonBlocking);
-}
-static void return_side_stream(int device, hipStream_t st)
-{
-    {
-        std::lock_guard<std::mutex> lock(side_lock);
-        std::vector<hipStream_t>& v = side_free[device];
-        if (v.size() < 16) {
-            v.push_back(st);
-            return;
-        }
-    }
-    (void)hipStreamDestroy(st);
-}
-
 // An interval of the profile on the solver's stream, covering n steps: the
 // start is recorded here, *end is what the caller records after its launch
 // (null when not profiling).
@@ -875,6 +844,31 @@ static fem_status profile_begin(fem_solver* s, int n, hipEvent_t* end)
     ++s->prof_used;
     s->prof_steps += n;
     return FEM_OK;
+}
+
+// Whether the solver's stream is being captured (by the caller: not asked
+// during a capture of the solver's own).
+static bool stream_capturing(const fem_solver* s)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return s->stream && hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive;
+}
+
+// Streams and events to run resident classes side by side.  A pair takes 160 to
+// 250 us to make, which the 1.5 to 3.4 us a step that they save give back within
+// some hundred steps.  They are a solver's own: a new stream goes to the least
+// used hardware queue, and one that another solver made before may share the
+// queue of this one's stream, which undoes them (8.3 instead of 4.9 us a step with
+// every second stream).
+static void make_side_streams(fem_solver* s)
+{
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < fem_solver::N_SIDE && e == hipSuccess; ++k) {
+        if (!s->side[k]) e = hipStreamCreateWithFlags(&s->side[k], hipStreamNonBlocking);
+        if (e == hipSuccess && !s->join[k]) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
+    }
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
+    if (e != hipSuccess) (void)hipGetLastError();   // one after the other, then
 }
 
 // Steps [s->t, t_end) of a resident solver, a launch per class.  A class is a
@@ -900,13 +894,15 @@ static fem_status resident_steps(fem_solver* s, int t_end)
     a.bf16 = s->dtype == FEM_BF16;
     const int classes = (int)s->res.t->classes.size();
     s->marg_ok = false;
+    s->res_steps += t_end - s->t;
+    if (classes > 1 && !s->fork && s->res_steps >= 100 && !stream_capturing(s)) make_side_streams(s);
     hipEvent_t end = nullptr;
     STCHK(profile_begin(s, t_end - s->t, &end));
     const int side = s->fork ? std::min(classes - 1, fem_solver::N_SIDE) : 0;   // side streams in use
     if (side) HIPCHK(hipEventRecord(s->fork, s->stream));
-    for (int k = 0; k < side; ++k) HIPCHK(hipStreamWaitEvent(s->side[k], s->fork, 0));
     for (int c = 0; c < classes; ++c) {
         const int k = c % (side + 1);
+        if (k && c == k) HIPCHK(hipStreamWaitEvent(s->side[k - 1], s->fork, 0));
         HIPCHK(resident_launch(*s->prob, s->res, c, s->manip, a, k ? s->side[k - 1] : s->stream));
     }
     for (int k = 0; k < side; ++k) {
@@ -926,9 +922,7 @@ static bool takes_resident(fem_solver* s, int t_end)
     int steps = t_end - s->t;
     if (s->prm.eval_every > 0) steps = std::min(steps, s->prm.eval_every);
     if (steps >= s->res.min_steps || s->always_res) return true;
-    if (!s->stream || s->capturing) return false;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s->stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusActive) s->always_res = true;
+    if (!s->capturing && stream_capturing(s)) s->always_res = true;
     return s->always_res;
 }
 
@@ -1020,7 +1014,7 @@ static void destroy_solver(fem_solver* s)
     drop_graphs(s);
     // the solver's stream waits for the side streams, so they are idle too
     for (int k = 0; k < fem_solver::N_SIDE; ++k) {
-        if (s->side[k]) return_side_stream(s->prob->device, s->side[k]);
+        if (s->side[k]) (void)hipStreamDestroy(s->side[k]);
         if (s->join[k]) (void)hipEventDestroy(s->join[k]);
     }
     if (s->fork) (void)hipEventDestroy(s->fork);
@@ -1531,13 +1525,6 @@ static fem_status create_solver_or_throw(const fem_problem* fp, const fem_params
     }
     if (!evaluation && !s->dense && P.steps <= RES_MAX_STEPS) {
         e = resident_choose(*s->owner, s->R, s->manip, P.eval_every, s->res);
-        if (e == hipSuccess && s->res.all && s->res.t->classes.size() > 1) {
-            for (int k = 0; k < fem_solver::N_SIDE && e == hipSuccess; ++k) {
-                e = side_stream(p.device, &s->side[k]);
-                if (e == hipSuccess) e = hipEventCreateWithFlags(&s->join[k], hipEventDisableTiming);
-            }
-            if (e == hipSuccess) e = hipEventCreateWithFlags(&s->fork, hipEventDisableTiming);
-        }
         if (e != hipSuccess)
             return bail(fail(e == hipErrorOutOfMemory ? FEM_E_NOMEM : FEM_E_HIP, "resident instances: %s",
                              hipGetErrorString(e)));
@@ -1751,7 +1738,11 @@ fem_status fem_run_until(fem_solver* s, int32_t t_end)
     const int t0 = s->t;
     // graph capture needs a non-null stream: run eagerly on the null stream;
     // resident steps are a launch or two per range and need no graph
-    if (!s->stream || takes_resident(s, t_end)) return do_steps(s, t_end);
+    // (a graph of up to four steps costs more than their launches: 8000 nodes,
+    // R = 16, manipulated gradients, one step 14.4 us as a graph, 5.0 eagerly,
+    // sixteen 4.7 and 5.0 each)
+    if (!s->stream || (s->res.all && t_end - t0 <= 4 && s->prm.eval_every == 0) || takes_resident(s, t_end))
+        return do_steps(s, t_end);
     if (!s->marg_ok) STCHK(init_marginals(s));
     STCHK(capture_range(s, t_end));
     auto it = s->graphs.find(std::make_pair(t0, (int)t_end));

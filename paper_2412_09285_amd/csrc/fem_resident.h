@@ -43,6 +43,7 @@ struct ResInst {
 // The instances of one launch: same workgroup size and rows per thread.
 struct ResClass {
     int threads = 0, rpt = 0;
+    int rows = 0;          // most rows of an instance
     int n_inst = 0;
     int first = 0;         // offset into ResTables::inst
     bool adj_lds = false;  // every instance's entries fit in LDS beside the marginals
