@@ -971,10 +971,19 @@ static fem_status do_steps(fem_solver* s, int t_end)
 
 // Marginal copy (and column sums) of the fields.  src: new fields on the
 // device, to set with cleared moments in the same pass (sets_fields says
-// whether this solver's pass does).
+// whether this solver's pass does).  A Potts lane stores its q states of four
+// arrays at a stride of 4 q bytes, which the caches merge while they hold the
+// lines: fields of 16 and 32 states, of 8 in more than 12 million values, and
+// of 4 whose lanes leave part of a wavefront idle are set by a pass of
+// contiguous stores first.  us in one pass and in two:
+//   n, q, R = 60000,  2, 256:  147  172     20000,  8,  32:    42   48
+//             60000,  4, 256:  265  305     60000,  8,  32:   108   90
+//             20000,  4, 100:   48   61      5000, 16,  32:    42   40
+//             60000,  4, 100:  159  145     60000, 16, 256:  1478 1243
 static bool sets_fields(const fem_solver* s)
 {
-    return !s->res.all && !s->manip;
+    if (s->res.all || s->manip) return false;
+    return s->Q <= 2 || (s->Q <= 8 && (int64_t)s->n * s->R * s->Q <= 12000000) || (s->Q == 4 && s->R % 64 == 0);
 }
 
 static fem_status init_marginals(fem_solver* s, const float* src)

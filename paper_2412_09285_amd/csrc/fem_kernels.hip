@@ -640,7 +640,7 @@ __global__ void __launch_bounds__(step_max_threads(KIND_BMINCUT, Q)) potts_init_
             const size_t base = ((size_t)i * R + r) * Q;
             const size_t sbase = (size_t)i * a.srow + (size_t)r * Q;   // h, m1, m2 rows
             float hv[Q];
-            if (src) {
+            if (Q <= 8 && src) {   // not called with more
                 const float zero[Q] = {};
                 ld_f32<Q>(src + base, hv);
                 st_f32<Q>(a.h + sbase, hv);
