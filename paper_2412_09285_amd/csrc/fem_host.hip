@@ -359,6 +359,7 @@ static fem_status build_sat(int device, int32_t n_vars, int64_t n_clauses, const
     p.q = 2;
     p.n_clauses = (int64_t)cls.size();
     p.sat_width = kmax <= 3 ? 2 : 3;
+    p.sat_k = std::max(kmax, 2);
     p.inst_off = {0, n_vars};
     p.inst_wtot = {0.0};
     std::vector<int64_t>& ro = p.h_row_off;
@@ -1179,7 +1180,10 @@ fem_status fem_batch_create(int32_t nparts, fem_problem* const* parts, fem_probl
     p.q = p0.q;
     p.integral = true;
     p.sat_width = 2;
-    for (int b = 0; b < nparts; ++b) p.sat_width = std::max(p.sat_width, parts[b]->p.sat_width);
+    for (int b = 0; b < nparts; ++b) {
+        p.sat_width = std::max(p.sat_width, parts[b]->p.sat_width);
+        p.sat_k = std::max(p.sat_k, parts[b]->p.sat_k);
+    }
     p.inst_off.assign(1, 0);
     p.h_row_off.assign(1, 0);
     bool weighted = false;
@@ -1581,7 +1585,7 @@ static fem_status create_solver_or_throw(const fem_problem* fp, const fem_params
         if (e != hipSuccess) return bail(fail(FEM_E_HIP, "copy of instance weights: %s", hipGetErrorString(e)));
     }
     TileShape sh = evaluation ? eval_shape(s->kind, s->R)
-                              : default_shape(s->kind, s->manip, s->n, s->R, s->q, (int)msz);
+                              : default_shape(s->kind, s->manip, s->n, s->R, s->q, p.sat_k, (int)msz);
     if (!valid_shape(s, sh)) sh = eval_shape(s->kind, s->R);
     while (!valid_shape(s, sh) && sh.waves > 1) sh.waves /= 2;
     while (!valid_shape(s, sh) && sh.vec > 1) sh.vec /= 2;

@@ -30,6 +30,7 @@ struct Problem {
     int64_t nnz = 0;       // adjacency entries or literal incidences
     int32_t n_inst = 1;
     int32_t sat_width = 2; // Max-k-SAT: other literals stored per incidence (2 or 3)
+    int32_t sat_k = 2;     // Max-k-SAT: most literals of a clause (2 to 4)
     int64_t n_clauses = 0;
     bool integral = true;  // all weights integral (exact integer cut values)
     std::vector<int32_t> inst_off;   // host [n_inst+1] node offsets
@@ -164,7 +165,13 @@ inline TileShape eval_shape(int kind, int R)
 //    one value 36, two 26; 11361 rows, R = 20, 14.5 / 13.5; 300000 rows, one 119,
 //    four 89.  Max-k-SAT stays at
 //    two (rounds of four incidences): 20000 variables, R = 64, 44 / 34; and
-//    where one would take a second segment: 8000, k = 3, R = 76, 31 / 26.  It
+//    where one would take a second segment: 8000, k = 3, R = 76, 31 / 26.  Four
+//    where they leave no more lanes idle: at two literals a clause (70000, R =
+//    200: two 190, four 160; R = 288, half the lanes of a second segment idle: 264
+//    / 286), at three from 30000 variables on in idle lanes (36000, R = 160:
+//    126 / 120; 20000, ratio 8, R = 200: 122 / 131; 36000, R = 256: 153 / 166), at
+//    four in idle lanes (36000, R = 160: 371 / 316; R = 256: 442 / 480).  In bf16
+//    only at four literals (36000, R = 256: 309 / 275; three, R = 200: 120 / 172).  It
 //    also stays at two rows (100000 variables, R = 64: four 198, two 182; 12000,
 //    R = 200: 61 / 55), one row for longer in a single segment of two values
 //    (12000, ratio 8, R = 76: two 49, one 45; in two segments, 5000, R = 200: one
@@ -199,7 +206,7 @@ inline TileShape eval_shape(int kind, int R)
 //    manipulated gradients the copy is the read-out, a bit or a byte per (node,
 //    replica): MaxCut 60000 rows, cached and non-temporal, R = 332 (244 MB) 146 /
 //    172, R = 364 (267 MB) 176 / 175, R = 416 193 / 175.
-inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, int marg_bytes)
+inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, int sat_k, int marg_bytes)
 {
     TileShape t;
     const double vals = (double)n * R * (kind == KIND_BMINCUT ? q : 1);
@@ -208,11 +215,12 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
     t.nt = vals * (12 + 2 * copy_bytes) > 256e6 && !(kind == KIND_BMINCUT && q >= 16) ? 1 : 0;
     int cap = 4;
     double blocks = 1024;
+    // share of the lanes of R's segments that hold a replica
+    const auto used = [&](int l, int vec = 1) {
+        const LaunchGeom g = make_geom(vec, R, t.waves, l);
+        return (double)R / ((double)g.nseg * g.lanes * vec);
+    };
     if (kind == KIND_BMINCUT) {
-        const auto used = [&](int l) {   // share of the lanes of R's segments that hold a replica
-            const LaunchGeom g = make_geom(1, R, t.waves, l);
-            return (double)R / ((double)g.nseg * g.lanes);
-        };
         blocks = q == 32 && n > 6500 ? 180 : 448;
         t.lanes = 64;
         const bool two_waves = q == 16 && n >= 2000 && R > 128 && R < 192;
@@ -229,7 +237,11 @@ inline TileShape default_shape(int kind, bool manip, int64_t n, int R, int q, in
     } else if (kind == KIND_MAXSAT) {
         t.vec = R % 2 == 0 && (R > 64 || (R == 64 && vals >= 1e6)) ? 2 : 1;
         cap = 2;
-        if (t.vec == 2 && R <= 128) blocks = 2048;
+        const double used4 = used(64, 4);
+        if (R % 4 == 0 && R > 128 && used4 >= used(64, 2) &&
+            (marg_bytes == 2 ? sat_k == 4 : sat_k == 2 || (used4 < 0.8 && (sat_k == 4 || n >= 30000))))
+            t.vec = 4;
+        if (t.vec == 4 || (t.vec == 2 && R <= 128)) blocks = 2048;
     } else if (manip) {
         t.vec = R % 4 == 0 && vals >= 4e5 ? 4 : R % 2 == 0 && vals >= 1e5 ? 2 : 1;
         const bool single = t.vec == 1 && R > 64;

@@ -145,3 +145,24 @@ def test_fields_from_device_and_host(n, q, R):
     ref.step(2)
     assert torch.equal(s.fields(torch.empty_like(h0)), ref.fields(torch.empty_like(h0)))
     assert np.array_equal(s.energies(), ref.energies())
+
+
+@pytest.mark.parametrize("n,k,R,dtype,vec", [(6000, 2, 132, "f32", 4), (6000, 2, 130, "f32", 2), (6000, 2, 288, "f32", 2), (6000, 2, 400, "bf16", 2),
+                                             (30000, 3, 200, "f32", 4), (29999, 3, 200, "f32", 2), (30000, 3, 256, "f32", 2), (30000, 3, 160, "bf16", 2),
+                                             (9000, 4, 160, "f32", 4), (9000, 4, 128, "f32", 2), (9000, 4, 256, "f32", 2), (9000, 4, 256, "bf16", 4)])
+def test_values_per_lane_of_max_sat(n, k, R, dtype, vec):
+    """Both sides of the rule's lines, and the fields of another shape."""
+    prob = fem.Problem.from_cnf(W.random_ksat(n, 2 * n, k, seed=1))
+    h0 = torch.randn((n, R), device="cuda", generator=torch.Generator("cuda").manual_seed(R)) * 0.3
+    out = []
+    for tile in (None, (1, 2, 3, 0, 0)):
+        s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, marginal_dtype=fem.BF16 if dtype == "bf16" else fem.F32))
+        if tile:
+            s.set_tile(*tile)
+        else:
+            assert s.tile()[0] == vec
+        s.set_fields(h0)
+        s.step(2)
+        out.append(s.fields(torch.empty_like(h0)))
+        s.close()
+    assert torch.equal(*out)
