@@ -1751,10 +1751,12 @@ fem_status fem_run_until(fem_solver* s, int32_t t_end)
     const int t0 = s->t;
     // graph capture needs a non-null stream: run eagerly on the null stream;
     // resident steps are a launch or two per range and need no graph
-    // (a graph of up to four steps costs more than their launches: 8000 nodes,
-    // R = 16, manipulated gradients, one step 14.4 us as a graph, 5.0 eagerly,
-    // sixteen 4.7 and 5.0 each)
-    if (!s->stream || (s->res.all && t_end - t0 <= 4 && s->prm.eval_every == 0) || takes_resident(s, t_end))
+    // (a graph of up to four steps without a read-out costs more than their
+    // launches: 8000 nodes, R = 16, manipulated gradients, one step 14.4 us as a
+    // graph, 5.0 eagerly, sixteen 4.7 and 5.0 each)
+    const bool reads_out = s->prm.eval_every > 0 &&
+                           (t_end / s->prm.eval_every != t0 / s->prm.eval_every || t_end == s->prm.steps);
+    if (!s->stream || (s->res.all && t_end - t0 <= 4 && !reads_out) || takes_resident(s, t_end))
         return do_steps(s, t_end);
     if (!s->marg_ok) STCHK(init_marginals(s));
     STCHK(capture_range(s, t_end));

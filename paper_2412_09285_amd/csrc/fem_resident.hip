@@ -719,21 +719,21 @@ static hipError_t res_build(const Problem& p, ResTables& t)
 // so one step where the workgroup is not the largest, else by the rows: 1.5 steps
 // for each 1024, 0.75 where the replicas fill the chip and are not more than it holds
 // (n = 4000, degree 6, R = 64: 27.7 15.7 10.2 7.0 5.4, row-tiled 12.6), one for a single
-// replica, whose lines of state are shared by rows (n = 3000, R = 1: 11.9 7.6 5.5 4.2 3.7,
-// row-tiled 7.9).  Twice as many with manipulated gradients, whose row-tiled
+// replica, whose lines of state are shared by rows, less half a step (n = 3000, R = 1:
+// 11.9 7.6 5.5 4.2 3.7, row-tiled 7.9; 1200 6.8 4.3 3.1, 8.1).  Twice as many with manipulated gradients, whose row-tiled
 // kernels gather bits (n = 2000, R = 16: 16.6 9.7 6.4 4.7 3.9, row-tiled 5.7) and fill the
 // chip later; with eight rows per thread and few replicas they are the faster
 // ones at any length (n = 8000, degree 4, R = 16, 32 steps 6.3, row-tiled 5.0).
 // Several classes are several launches, in turn until a solver has side streams
-// (make_side_streams).  us a step of 16 and 48 steps in turn, of 96 side by side, and
-// row-tiled:
-//   2 sizes, 1100 and 2500, R =   8:  6.1  4.7   2.9    9.1
-//   5 sizes, 100 .. 3000,   R =   8: 10.6  8.6   5.4    9.2
-//                           R =  50: 11.2  8.7   4.4   12
-//                           R = 200: 12.1  9.0   8.4   20
-//   8 sizes, 40 .. 6000,    R =   8: 21.5 17.9   8.8    9.3
-//                           R =  50: 22.5 17.9  14.5   16
-//                           R = 200: 24.2 18.4  15.1   29
+// (make_side_streams).  us a step of 8, 16 and 48 steps in turn, of 96 side by
+// side, and row-tiled:
+//   2 sizes, 1100 and 2500, R =   8:  8.1  6.1  4.7   2.9    9.1 .. 10
+//   5 sizes, 100 .. 3000,   R =   8:       10.6  8.6   5.4    9.2
+//                           R =  50:       11.2  8.7   4.4   12
+//                           R = 200: 16.8 12.1  9.0   8.4   20
+//   8 sizes, 40 .. 6000,    R =   8:       21.5 17.9   8.8    9.3
+//                           R =  50:       22.5 17.9  14.5   16
+//                           R = 200:       24.2 18.4  15.1   29
 // A read-out by bytes is five launches, which a graph of row-tiled steps replays
 // faster (67 nodes, real weights, R = 1, every step: 19.4 / 13).
 hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, ResData& r)
@@ -745,11 +745,12 @@ hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, R
     if (!t.planned) res_plan_all(p, t);
     if (!t.fits || t.threads * (uint64_t)R > UINT32_MAX) return hipSuccess;
     const size_t classes = t.classes.size();
-    int steps = classes == 1 ? 1 : classes <= 3 || R >= 128 ? 16 : classes <= 5 ? 24 : 48;
+    int steps = classes == 1 ? 1 : classes <= 3 || (classes <= 5 && R >= 128) ? 8 : R >= 128 ? 16 : classes <= 5 ? 24 : 48;
     const ResClass& big = t.classes.front();
     if (big.threads == 1024) {
         const double f = R == 1 ? 1.0 : R > 256 || R < (manip ? 128 : 64) ? 1.5 : 0.75;
-        steps = std::max(steps, (int)std::ceil(f * (manip ? 2 : 1) * big.rows / 1024));
+        const double rows = big.rows / 1024.0 - (R == 1 ? 0.5 : 0.0);
+        steps = std::max(steps, (int)std::ceil(f * (manip ? 2 : 1) * rows));
     }
     if ((manip && big.rpt == 8 && R < 64) || (classes > 5 && R < 32)) return hipSuccess;
     if (eval_every > 0 && eval_every < std::max(steps, bit_evaluation(p) ? 1 : 4)) return hipSuccess;
