@@ -974,17 +974,19 @@ static fem_status do_steps(fem_solver* s, int t_end)
 // device, to set with cleared moments in the same pass (sets_fields says
 // whether this solver's pass does).  A Potts lane stores its q states of four
 // arrays at a stride of 4 q bytes, which the caches merge while they hold the
-// lines: fields of 16 and 32 states, of 8 in more than 12 million values, and
-// of 4 whose lanes leave part of a wavefront idle are set by a pass of
-// contiguous stores first.  us in one pass and in two:
-//   n, q, R = 60000,  2, 256:  147  172     20000,  8,  32:    42   48
-//             60000,  4, 256:  265  305     60000,  8,  32:   108   90
-//             20000,  4, 100:   48   61      5000, 16,  32:    42   40
-//             60000,  4, 100:  159  145     60000, 16, 256:  1478 1243
+// lines: fields of 16 and 32 states are set by a pass of contiguous stores
+// first, and of more than 12 million values those of 4 and 8 states whose rows
+// end within a wave's segment, and of 8 with a float32 copy.  us in one pass and
+// in two, by n R q (millions):
+//   q, R:  4, 100,  10:  54  71      8, 100,  10:  66  70     16, 256, 20:  151  116
+//          4, 100,  60: 381 332      8, 100,  60: 394 334     16, 256, 246: 1478 1243
+//          4, 128,  60: 257 301      8, 128,  60: 326 308, bfloat16 273 291
 static bool sets_fields(const fem_solver* s)
 {
     if (s->res.all || s->manip) return false;
-    return s->Q <= 2 || (s->Q <= 8 && (int64_t)s->n * s->R * s->Q <= 12000000) || (s->Q == 4 && s->R % 64 == 0);
+    if (s->Q <= 2 || (s->Q <= 8 && (int64_t)s->n * s->R * s->Q <= 12000000)) return true;
+    const bool whole = s->R <= 64 || s->R % 64 == 0;
+    return whole && (s->Q == 4 || (s->Q == 8 && s->dtype == FEM_BF16));
 }
 
 static fem_status init_marginals(fem_solver* s, const float* src)

@@ -127,20 +127,22 @@ def test_evaluation_of_large_tiles(q, R, tile):
     assert np.array_equal(s.anytime_best()[0], -best if q == 1 else best)
 
 
-@pytest.mark.parametrize("n,q,R", [(60000, 8, 25), (60000, 8, 26), (60000, 4, 64), (60000, 4, 65), (60000, 2, 101), (300, 16, 5), (300, 32, 70)])
-def test_fields_from_device_and_host(n, q, R):
+@pytest.mark.parametrize("n,q,R,dtype", [(60000, 8, 25, "f32"), (60000, 8, 26, "f32"), (60000, 8, 26, "bf16"), (25000, 8, 65, "bf16"), (60000, 4, 64, "f32"),
+                                         (60000, 4, 65, "f32"), (60000, 2, 101, "f32"), (300, 16, 5, "f32"), (300, 32, 70, "f32")])
+def test_fields_from_device_and_host(n, q, R, dtype):
     """Both sides of the line between one pass and two: fields set over a run are
     those of a fresh solver set from the host, and so are the steps after them."""
     g = W.random_sparse_graph(n, 2 * n, seed=1, weights="one")
     prob = fem.Problem.bmincut(n, g.u, g.v, g.w, q)
     h0 = torch.randn((n, R, q), device="cuda", generator=torch.Generator("cuda").manual_seed(R)) * 0.3
-    s = fem.Solver(prob, fem.default_params(replicas=R, steps=5, lam=0.1))
+    par = fem.default_params(replicas=R, steps=5, lam=0.1, marginal_dtype=fem.BF16 if dtype == "bf16" else fem.F32)
+    s = fem.Solver(prob, par)
     s.set_fields(h0 + 1)
     s.step(2)
     s.set_fields(h0)
     assert torch.equal(s.fields(torch.empty_like(h0)), h0)
     s.step(2)
-    ref = fem.Solver(prob, fem.default_params(replicas=R, steps=5, lam=0.1))
+    ref = fem.Solver(prob, par)
     ref.set_fields(h0.cpu().numpy())
     ref.step(2)
     assert torch.equal(s.fields(torch.empty_like(h0)), ref.fields(torch.empty_like(h0)))
