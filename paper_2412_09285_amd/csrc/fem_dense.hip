@@ -287,14 +287,17 @@ __device__ __forceinline__ int dense_i8_lane(int row, int k)
 // A workgroup owns 32 BM x 32 outputs; wave w takes operands w, w + 4, ... of
 // each of its row blocks.
 //
-// Bound by the L2, which passes every operand once per block, and by the step
-// itself around it (n = 2000, R = 1000, 32 x 32 blocks: 796 MB of L2 requests,
-// 21 TB/s, and 67 MB of state and planes from memory in 38 us; matrix cores 7
-// us, vector units 12); by the chain of one workgroup while the chip is not
-// full.  With operands that lay row by row (32 bytes of each line per load)
-// the same kernel took 100 us instead of 45 (n = 2000, R = 1000) and 19
-// instead of 12 (R = 50).  Three blocks of operands in flight keep three
-// waves a SIMD: two, or four with fewer waves, measured 3 to 10% slower.
+// Bound by the chain of a workgroup (state loads, a quarter of the contraction,
+// LDS, the step, stores) with few of them at once: n = 2000, R = 1000 is 1024
+// workgroups of 64 x 32 outputs, two rounds of the 512 that fit at two waves a
+// SIMD, whose phases coincide.  No unit is full in its 37 us: 112 MB past L2, 3
+// TB/s; 4.1 M requests to the L2, 44% of one a cycle and channel, 78% hits;
+// vector units 25 k and matrix cores 16 k of the 72 k cycles that the shaders are
+// busy.  32 x 32 blocks, 660 MB of operands from the L2 instead of 403, took 3%
+// longer.  With operands that lay row by row (32 bytes of each line per load)
+// 32 x 32 blocks took 100 us instead of 45 (n = 2000, R = 1000) and 19 instead
+// of 12 (R = 50).  Three K blocks of operands in flight leave these three waves
+// a SIMD: two, or four with fewer waves, measured 3 to 10% slower.
 template <bool EN, bool NT, int BM>
 __global__ void __launch_bounds__(256, BM == 1 ? 3 : 2) maxcut_dense_i8_step_kernel(StepArgs a,
                                                                                     const int8_t* __restrict__ W8,

@@ -17,13 +17,13 @@
 // neighbours in CSR order in double, and the update is the tiled kernels', so
 // the fields are bit-identical to theirs.
 //
-// Measured per step with energies (MI355X; resident / best of six row-tiled
-// shapes), MaxCut +-1 at R = 16 and R = 512:
-//   n =  200, degree  20:  1.57 /  7.1 us    1.87 /  8.2 us
-//   n =  800, degree  48:  3.55 /  8.8 us    7.23 / 18.0 us
-//   n = 2000, degree  20:  3.81 /  9.6 us    8.18 / 16.2 us
-//   n = 8000, degree   3:  7.58 / 11.0 us   16.5  / 36.9 us
-// Max-3-SAT, 200 variables, 1200 clauses: 2.28 / 8.3 us and 2.88 / 10.3 us.
+// Measured per step with energies in a long range (MI355X; resident / best of
+// seven row-tiled shapes), MaxCut +-1 at R = 16 and R = 512:
+//   n =  200, degree  20:  1.13 /  6.9 us    1.37 /  7.3 us
+//   n =  800, degree  48:  3.00 /  8.5 us    5.85 / 13.6 us
+//   n = 2000, degree  20:  3.31 /  8.2 us    6.38 / 15.9 us
+//   n = 8000, degree   3:  6.38 /  8.9 us   12.8  / 32.6 us
+// Max-3-SAT, 200 variables, 1200 clauses: 1.96 / 8.5 us and 2.36 / 9.7 us.
 #include "fem_resident.h"
 
 #include <algorithm>
@@ -717,13 +717,14 @@ static hipError_t res_build(const Problem& p, ResTables& t)
 //   n = 8000, degree  3, R =  16:  46.6  26.9  16.6  11.7   9.1   10.5
 //   n = 8000, degree  3, R = 256:  69.6  38.3  22.7  14.8  11.0   22.6
 // so one step where the workgroup is not the largest, else by the rows: 1.5 steps
-// for each 1024, 0.75 where the replicas fill the chip and are not more than it holds
-// (n = 4000, degree 6, R = 64: 27.7 15.7 10.2 7.0 5.4, row-tiled 12.6), one for a single
-// replica, whose lines of state are shared by rows, less half a step (n = 3000, R = 1:
-// 11.9 7.6 5.5 4.2 3.7, row-tiled 7.9; 1200 6.8 4.3 3.1, 8.1).  Twice as many with manipulated gradients, whose row-tiled
-// kernels gather bits (n = 2000, R = 16: 16.6 9.7 6.4 4.7 3.9, row-tiled 5.7) and fill the
-// chip later; with eight rows per thread and few replicas they are the faster
-// ones at any length (n = 8000, degree 4, R = 16, 32 steps 6.3, row-tiled 5.0).
+// for each 1024, 0.75 where the replicas fill the chip and are not more than it
+// holds (n = 4000, degree 6, R = 64: 27.7 15.7 10.2 7.0 5.4, row-tiled 12.6), one for
+// a single replica, whose lines of state are shared by rows, less half a step (n =
+// 3000, R = 1: 11.9 7.6 5.5 4.2 3.7, row-tiled 7.9; 1200: 6.8 4.3 3.1, 8.1).  Twice
+// as many with manipulated gradients, whose row-tiled kernels gather bits (n =
+// 2000, R = 16: 16.6 9.7 6.4 4.7 3.9, row-tiled 5.7) and fill the chip later; with
+// eight rows per thread and few replicas they are the faster ones at any length
+// (n = 8000, degree 4, R = 16, 32 steps 6.3, row-tiled 5.0).
 // Several classes are several launches, in turn until a solver has side streams
 // (make_side_streams).  us a step of 8, 16 and 48 steps in turn, of 96 side by
 // side, and row-tiled:
