@@ -695,12 +695,15 @@ static hipError_t res_build(const Problem& p, ResTables& t)
 //   n = 4000, others, 24 k            7.9/9.1   8.2/14.0   7.2/5.7   7.5/7.1
 //   n = 4000, others, 48 k           13.7/9.8  13.8/17.1  13.0/7.6  13.4/9.4
 //   n = 4000, 3-SAT,  45 k           13.4/11.5 13.7/17.4
-// (R = 128, n = 4000, 48 k: 12.1/20.7 and 11.3/12.1).  So RES_MAX_STREAM entries of
-// one row per thread, three quarters of two, half of four (a quarter with
-// manipulated gradients, three quarters for Max-k-SAT), times three quarters for
-// other weights, twice as many from R = 64 on, four times from 128 on.  Eight rows
-// per thread are instantiated only where they fit the registers: +-1 weights,
-// entries in LDS.
+// (R = 128, n = 4000, 48 k: 12.1/20.7 and 11.3/12.1; R = 24 and 40, +-1 11.6/12.1
+// 11.6/15.2, others 13.3/12.9 13.3/15.9; n = 4000, others, 25 k, R = 16 8.1/9.7, 29 k
+// 9.8/9.7).  So RES_MAX_STREAM entries of one row per thread, three quarters of
+// two, half of four (a quarter with manipulated gradients, three fifths for
+// Max-k-SAT), times three quarters for other weights (nine tenths of four rows with
+// explicit gradients), and more the more of the chip the row-tiled kernels need: a
+// quarter more from R = 24, twice from 40 (manipulated from 64), four times from
+// 128 on.  Eight rows per thread are instantiated only where they fit the
+// registers: +-1 weights, entries in LDS.
 // A launch has a workgroup per (instance, replica), and HIP takes fewer than
 // 2^32 threads.
 //
@@ -756,8 +759,11 @@ hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, R
     if ((manip && big.rpt == 8 && R < 64) || (classes > 5 && R < 32)) return hipSuccess;
     if (eval_every > 0 && eval_every < std::max(steps, bit_evaluation(p) ? 1 : 4)) return hipSuccess;
     for (const ResClass& c : t.classes) {
-        const double rows = c.rpt == 1 ? 1.0 : c.rpt == 2 || p.kind == KIND_MAXSAT ? 0.75 : manip ? 0.25 : 0.5;
-        const double limit = rows * (t.pm1 || p.kind == KIND_MAXSAT ? 1.0 : 0.75) * (R < 64 ? 1 : R < 128 ? 2 : 4);
+        const bool sat = p.kind == KIND_MAXSAT;
+        const double rows = c.rpt == 1 ? 1.0 : c.rpt == 2 ? 0.75 : sat ? 0.6 : manip ? 0.25 : 0.5;
+        const double weights = t.pm1 || sat ? 1.0 : c.rpt == 4 && !manip ? 0.9 : 0.75;
+        const double fill = R >= 128 ? 4.0 : R >= (manip ? 64 : 40) ? 2.0 : R >= 24 && !manip ? 1.25 : 1.0;
+        const double limit = rows * weights * fill;
         if ((double)c.stream > limit * (double)RES_MAX_STREAM) return hipSuccess;
     }
     if (!t.block) {
