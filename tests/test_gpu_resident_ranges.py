@@ -221,7 +221,9 @@ def test_solvers_of_one_problem_share_its_tables(kind):
     (1000, 250, "pm1", 16, False, True), (1000, 250, "real", 16, False, False), (1000, 180, "real", 16, False, True),
     (2000, 100, "one", 16, False, False), (2000, 90, "one", 16, False, True), (2000, 100, "real", 64, False, True),
     (4000, 48, "pm1", 16, False, False), (4000, 48, "pm1", 64, False, True), (4000, 24, "pm1", 16, True, False),
-    (4000, 24, "pm1", 64, True, True), (4000, 20, "real", 63, True, False), (4000, 20, "real", 64, True, True)])
+    (4000, 24, "pm1", 64, True, True), (4000, 20, "real", 63, True, False), (4000, 20, "real", 64, True, True),
+    (4000, 35, "pm1", 23, False, False), (4000, 35, "pm1", 24, False, True), (4000, 46, "pm1", 39, False, False), (4000, 46, "pm1", 40, False, True),
+    (4000, 26, "real", 23, False, True), (4000, 32, "real", 23, False, False), (4000, 32, "real", 24, False, True)])
 def test_entries_that_stream(n, deg, weights, R, manip, resident):
     """Long ranges with entries beyond LDS, on both sides of the rule: resident
     energies round otherwise than the shaped kernels' where a thread holds several
