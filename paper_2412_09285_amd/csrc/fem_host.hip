@@ -901,15 +901,18 @@ static fem_status resident_steps(fem_solver* s, int t_end)
     STCHK(profile_begin(s, t_end - s->t, &end));
     const int side = s->fork ? std::min(classes - 1, fem_solver::N_SIDE) : 0;   // side streams in use
     if (side) HIPCHK(hipEventRecord(s->fork, s->stream));
-    for (int c = 0; c < classes; ++c) {
+    hipError_t e = hipSuccess;
+    for (int c = 0; c < classes && e == hipSuccess; ++c) {
         const int k = c % (side + 1);
-        if (k && c == k) HIPCHK(hipStreamWaitEvent(s->side[k - 1], s->fork, 0));
-        HIPCHK(resident_launch(*s->prob, s->res, c, s->manip, a, k ? s->side[k - 1] : s->stream));
+        if (k && c == k) e = hipStreamWaitEvent(s->side[k - 1], s->fork, 0);
+        if (e == hipSuccess) e = resident_launch(*s->prob, s->res, c, s->manip, a, k ? s->side[k - 1] : s->stream);
     }
+    // also after an error: what was launched uses the solver's memory
     for (int k = 0; k < side; ++k) {
         HIPCHK(hipEventRecord(s->join[k], s->side[k]));
         HIPCHK(hipStreamWaitEvent(s->stream, s->join[k], 0));
     }
+    HIPCHK(e);
     if (end) HIPCHK(hipEventRecord(end, s->stream));
     return FEM_OK;
 }
