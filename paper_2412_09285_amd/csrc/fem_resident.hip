@@ -30,6 +30,7 @@
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <utility>
 
 #include "fem_device.h"
 #include "fem_readout.h"
@@ -530,7 +531,7 @@ static void res_plan_all(const Problem& p, ResTables& t)
         ResInst in{};
         in.pos0 = (int32_t)t.h_perm.size();
         const ResPlan plan = res_plan(p, b, t.planes, t.pm1 || sat, (size_t)t.dev_lds, count, t.h_perm);
-        if (!plan.ok) {
+        if (!plan.ok || t.h_perm.size() > (size_t)INT32_MAX) {   // positions are 32-bit
             t = ResTables{};
             t.planned = true;
             return;
@@ -746,7 +747,11 @@ hipError_t resident_choose(fem_problem& fp, int R, bool manip, int eval_every, R
     std::lock_guard<std::mutex> lock(fp.lock);
     if (!fp.res) fp.res = new ResTables;
     ResTables& t = *fp.res;
-    if (!t.planned) res_plan_all(p, t);
+    if (!t.planned) {
+        ResTables plan;   // whole or, where host memory runs out, not at all
+        res_plan_all(p, plan);
+        t = std::move(plan);
+    }
     if (!t.fits || t.threads * (uint64_t)R > UINT32_MAX) return hipSuccess;
     const size_t classes = t.classes.size();
     int steps = classes == 1 ? 1 : classes <= 3 || (classes <= 5 && R >= 128) ? 8 : R >= 128 ? 16 : classes <= 5 ? 24 : 48;
